@@ -125,11 +125,12 @@ int me_set_precision(me_ctx *ctx, int mode, double rel_tol);
  * lanes-th filtered helicity and the lanes' partial sums are added when the
  * event is done.  lanes = 0 (the default): chosen per call, the smallest
  * power of two with nevt * lanes >= 65536, at most 64 and at most the number
- * of helicities kept (one lane per event from 65536 events up), and at least
- * a measured per-process floor (8 for "gg_ttgg", 1 otherwise).  The result
+ * of helicities kept (one lane per event from 65536 events up).  The result
  * equals the one-lane result up to the order of the helicity sum.  Applies to
  * the float64 form of me_eval only (the mixed form, its float64 rerun,
- * me_eval_helicities and unweighting keep one lane per event).  Errors:
+ * me_eval_helicities and unweighting keep one lane per event).  "gg_ttgg"
+ * always spreads an event over a whole wave: there the setting is accepted and
+ * every setting gives the same result.  Errors:
  * ME_EINVAL (null context, lanes neither 0 nor a power of two up to 64).
  */
 int me_set_helicity_lanes(me_ctx *ctx, int lanes);
@@ -201,7 +202,9 @@ int me_eval_mixed_noalloc(me_ctx *ctx, const double *momenta, int64_t nevt, doub
  *           J_h^dag C J_h (before averaging) for every helicity combination
  *           h in 0..nhel-1 (particle i has helicity + when bit (npart-1-i)
  *           of h is set), including those the filter dropped.
- * out_me2:  as in me_eval, but summed over all helicities (no filter).
+ * out_me2:  as in me_eval, but summed over all helicities (no filter).  Where
+ *           me_eval sums over real polarisation vectors ("gg_ttgg") it is
+ *           that sum, equal to the sum of out_qhel up to rounding.
  */
 int me_eval_helicities(me_ctx *ctx, const double *momenta, int64_t nevt, double *out_me2, double *out_qhel,
                        void *stream);

@@ -28,6 +28,9 @@ COOP = {"gg_ttggg"}
 # always get it
 CM = {"gg_ttgg"}
 
+# processes whose float64 sum runs with one event per wave (me_wave.h)
+WAVE = {"gg_ttgg": "k_me_gg4_wave"}
+
 # Calibration of the mixed form's amplitude error estimate (multiplies
 # u32 * 2 lambda_max(|N|) |S| |J| / Q); fixed by comparing float32 results
 # with the oracle (see the mixed-precision tests).
@@ -66,7 +69,7 @@ static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, c
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_QEW, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, nullptr, 8.0,
-    0.0, nullptr, nullptr, 0, nullptr}};
+    0.0, nullptr, nullptr, 0, nullptr, nullptr}};
 #endif
 """
 
@@ -94,7 +97,7 @@ static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, c
 extern const me_process_desc me_desc_{name} = {{
     "{name}", {kind}, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, {mixed_ptr}, {cest},
-    {colerr}, {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}}};
+    {colerr}, {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}}};
 #endif
 """
 
@@ -106,6 +109,33 @@ hipError_t me_launch_mc_{name}(const double* mom, int64_t nevt, double* out, con
 extern const int me_nchan_{name};
 extern const char* const* const me_chan_desc_{name};
 #endif
+"""
+
+_WAVE_DECL = """
+#ifndef __HIP_DEVICE_COMPILE__
+hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, unsigned spins, const me_params& prm,
+                                const int* idx, const int* count, bool mfma, hipStream_t s);
+#endif
+"""
+
+_TU_WAVE = """// Generated translation unit: spin-summed float64 kernel of {name} (one event per wave).
+#include "me_wave.h"
+#include "gen/proc_{name}.h"
+
+hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, unsigned spins, const me_params& prm,
+                                const int* idx, const int* count, bool mfma, hipStream_t s) {{
+    // events per block and turn: see me_wave_events
+    const int eb = me_wave_events(nevt);
+    const int64_t turns = (nevt + eb - 1) / eb;
+    const dim3 grid((unsigned)(turns < ME_WAVE_BLOCKS ? turns : ME_WAVE_BLOCKS));
+    if (mfma)
+        hipLaunchKernelGGL(({kernel}<proc_{name}, true>), grid, dim3(64), 0, s, mom, nevt, out, spins, prm, idx,
+                           count, eb);
+    else
+        hipLaunchKernelGGL(({kernel}<proc_{name}, false>), grid, dim3(64), 0, s, mom, nevt, out, spins, prm, idx,
+                           count, eb);
+    return hipGetLastError();
+}}
 """
 
 _TU_MC = """// Generated translation unit: multi-channel kernel of {name}.
@@ -167,7 +197,7 @@ hipError_t me_launch_f64_cm_{name}(const double* mom, int64_t nevt, double* out,
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_GG, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, me_launch_mixed_{name}, {cest},
-    {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr}};
+    {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr, nullptr}};
 #endif
 """
 
@@ -271,9 +301,16 @@ def generate_sources(processes):
             path_mc = os.path.join(GEN, f"tu_{name}_mc.hip")
             _write(path_mc, _TU_MC.format(name=name))
             tus.append(path_mc)
+        sum_ptr = "nullptr"
+        if name in WAVE:
+            cm += _WAVE_DECL.format(name=name)
+            sum_ptr = f"me_launch_sum_{name}"
+            path_w = os.path.join(GEN, f"tu_{name}_wave.hip")
+            _write(path_w, _TU_WAVE.format(name=name, kernel=WAVE[name]))
+            tus.append(path_w)
         _write(path, _TU.format(name=name, include=inc, kernel=kernel, proc=proc, kind=kind, mixed=mixed,
                                 mixed_ptr=mixed_ptr, cest=MIXED_CEST.get(name, 8.0), colerr=colerr, cm=cm,
-                                cm_ptr=cm_ptr, mc_ptr=mc_ptr, mc_n=mc_n, mc_desc=mc_desc))
+                                cm_ptr=cm_ptr, mc_ptr=mc_ptr, mc_n=mc_n, mc_desc=mc_desc, sum_ptr=sum_ptr))
         tus.append(path)
     decls = "\n".join(f"extern const me_process_desc me_desc_{n};" for n in processes)
     ptrs = ", ".join(f"&me_desc_{n}" for n in processes)

@@ -166,39 +166,51 @@ static int helicity_filter(me_ctx* c) {
         if (nz) c->good.push_back(h);
     }
     c->nhel_good = (int)c->good.size();
+    // spin bits of particles 2 and 3 (t, tbar) in a helicity index
+    c->spins = 0;
+    for (int h : c->good) c->spins |= 1u << (((h >> (pd->npart - 3)) & 1) + 2 * ((h >> (pd->npart - 4)) & 1));
     HIP_CHECK(hipMalloc(&c->d_good, std::max(1, c->nhel_good) * sizeof(int)));
     if (c->nhel_good)
         HIP_CHECK(hipMemcpy(c->d_good, c->good.data(), c->nhel_good * sizeof(int), hipMemcpyHostToDevice));
     return ME_OK;
 }
 
-// The float64 launcher of the context's colour form.
 // Lanes per event when the caller has not fixed them: the smallest 2^k with
-// nevt 2^k >= 2^16 lanes in flight (on g g -> t tbar g g the rate is flat
-// from there: 2^10 events at 64 lanes run at 94 % of the 2^20-event rate, at
-// one lane at 1.6 %), at most 64 and at most the number of helicities kept,
-// and at least the process's own floor: g g -> t tbar g g runs 2^20 events
-// about 1 % faster at 8 lanes per event (8 helicities per lane) than at one
-// (measured: 44.4 against 44.9 ms; gg -> tt, gg -> ttg and the quark-line
-// process gain nothing from more lanes at that size).
-static int auto_lanes_lg(int64_t nevt, int nhel, const char* process) {
+// nevt 2^k >= 2^16 lanes in flight (the rate of the one-event-per-lane kernels
+// is flat from there), at most 64 and at most the number of helicities kept.
+static int auto_lanes_lg(int64_t nevt, int nhel) {
     int lg = 0;
     while (lg < 6 && (nevt << lg) < (int64_t(1) << 16) && (2 << lg) <= nhel) ++lg;
-    const int floor_lg = std::strcmp(process, "gg_ttgg") == 0 ? 3 : 0;
-    while (lg < floor_lg && (2 << lg) <= nhel) ++lg;
     return lg;
 }
 
+// The float64 launcher of the context's colour form.
 static me_launch_fn f64_launcher(const me_ctx* c) {
     return (c->colour_form == ME_COLOUR_MFMA && c->proc->launch_f64_cm) ? c->proc->launch_f64_cm
                                                                        : c->proc->launch_f64;
 }
 
-// The float64 form of me_eval: the context's colour form and lane count.
+// Spin sum over the given spin pairs of t and tbar, one event per wave.
+static hipError_t launch_sum(const me_ctx* c, const double* momenta, int64_t nevt, double* out, unsigned spins,
+                             hipStream_t s) {
+    return c->proc->launch_sum(momenta, nevt, out, spins, c->prm, nullptr, nullptr, c->colour_form == ME_COLOUR_MFMA,
+                               s);
+}
+
+// The float64 form of me_eval: the spin-summed kernel where the process has
+// one (it uses a whole wave per event at any count of events, so the lane
+// setting does not enter), else the context's colour form and lane count.
 static hipError_t launch_f64_form(const me_ctx* c, const double* momenta, int64_t nevt, double* out,
                                   hipStream_t s) {
-    const int lg = c->hel_lg >= 0 ? c->hel_lg : auto_lanes_lg(nevt, c->nhel_good, c->proc->name);
+    if (c->proc->launch_sum) return launch_sum(c, momenta, nevt, out, c->spins, s);
+    const int lg = c->hel_lg >= 0 ? c->hel_lg : auto_lanes_lg(nevt, c->nhel_good);
     return f64_launcher(c)(momenta, nevt, out, c->d_good, c->nhel_good, c->prm, nullptr, lg, s);
+}
+
+hipError_t me_launch_idx(const me_ctx* c, const double* mom, int64_t nevt, double* out, const int* idx,
+                         const int* count, hipStream_t s) {
+    if (c->proc->launch_sum) return c->proc->launch_sum(mom, nevt, out, c->spins, c->prm, idx, count, false, s);
+    return c->proc->launch_f64_idx(mom, nevt, out, c->d_good, c->nhel_good, c->prm, idx, count, s);
 }
 
 extern "C" {
@@ -234,6 +246,7 @@ int me_init(const char* process, const double* couplings, int n_couplings, const
     c->prm.sw2 = sw2;
     c->d_good = nullptr;
     c->d_all = nullptr;
+    c->spins = 0;
     c->mode = ME_FP64;
     c->hel_lg = -1;  // automatic
     c->colour_form = ME_COLOUR_VALU;
@@ -283,8 +296,7 @@ int me_eval(me_ctx* c, const double* momenta, int64_t nevt, double* out_me2, voi
         HIP_CHECK(c->proc->launch_mixed(momenta, nevt, out_me2, c->d_good, c->nhel_good, c->prm, (float)c->tol,
                                         (float)c->proc->mixed_cest, c->d_count, c->d_idx, nullptr, nullptr, s));
         // float64 rerun of the flagged events, in place, on the same stream
-        HIP_CHECK(c->proc->launch_f64_idx(momenta, nevt, out_me2, c->d_good, c->nhel_good, c->prm, c->d_idx,
-                                          c->d_count, s));
+        HIP_CHECK(me_launch_idx(c, momenta, nevt, out_me2, c->d_idx, c->d_count, s));
         return ME_OK;
     }
     HIP_CHECK(launch_f64_form(c, momenta, nevt, out_me2, s));
@@ -335,7 +347,7 @@ int me_eval_mixed_noalloc(me_ctx* c, const double* momenta, int64_t nevt, double
     // the mixed launch clears the counter with a kernel before it appends
     HIP_CHECK(c->proc->launch_mixed(momenta, nevt, out_me2, c->d_good, c->nhel_good, c->prm, (float)c->tol,
                                     (float)c->proc->mixed_cest, d_count, d_idx, nullptr, nullptr, s));
-    HIP_CHECK(c->proc->launch_f64_idx(momenta, nevt, out_me2, c->d_good, c->nhel_good, c->prm, d_idx, d_count, s));
+    HIP_CHECK(me_launch_idx(c, momenta, nevt, out_me2, d_idx, d_count, s));
     return ME_OK;
 }
 
@@ -381,6 +393,8 @@ int me_eval_helicities(me_ctx* c, const double* momenta, int64_t nevt, double* o
     if (!momenta || !out_me2 || !out_qhel) return fail(ME_EINVAL, "null buffer");
     HIP_CHECK(f64_launcher(c)(momenta, nevt, out_me2, c->d_all, c->proc->nhel, c->prm, out_qhel, 0,
                                   (hipStream_t)stream));
+    // the total as me_eval forms it, over every helicity
+    if (c->proc->launch_sum) HIP_CHECK(launch_sum(c, momenta, nevt, out_me2, 0xfu, (hipStream_t)stream));
     return ME_OK;
 }
 

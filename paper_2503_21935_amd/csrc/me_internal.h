@@ -23,6 +23,7 @@ struct me_ctx {
     std::vector<int> good;  // host copy of the filtered helicities
     int* d_good;            // device copy
     int* d_all;             // device list 0..nhel-1
+    unsigned spins;         // spin pairs of t and tbar among the filtered helicities (launch_sum)
     int mode;               // ME_FP64 or ME_MIXED
     int hel_lg;             // float64 form: 2^hel_lg lanes per event (helicity parallelism), -1 automatic
     int colour_form;        // float64 form: ME_COLOUR_VALU or ME_COLOUR_MFMA
@@ -39,6 +40,10 @@ struct me_ctx {
     int* uw_idx1;
     int64_t uw_cap;
 };
+
+// Float64 |M|^2 of the events idx[0..*count) (both on the device).
+hipError_t me_launch_idx(const me_ctx* c, const double* mom, int64_t nevt, double* out, const int* idx,
+                         const int* count, hipStream_t s);
 
 struct me_mlp;
 int mlp_forward_internal(me_mlp* p, const float* x, int64_t n, float* y, hipStream_t s);

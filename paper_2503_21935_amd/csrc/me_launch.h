@@ -28,6 +28,21 @@ typedef hipError_t (*me_launch_mixed_fn)(const double* mom, int64_t nevt, double
 typedef hipError_t (*me_launch_mc_fn)(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                       const me_params& prm, const int* chan, double* alpha, hipStream_t stream);
 
+// Blocks of a grid whose blocks stride over the events, one event per block at a time.
+#define ME_WAVE_BLOCKS 8192
+
+// Events that such a block sets up together: two, which fills the lanes of
+// the setup phases, once there are enough events to keep every CU's eight waves
+// busy that way; below that one, since a call then takes as long as one block.
+static inline int me_wave_events(int64_t nevt) { return nevt > 4096 ? 2 : 1; }
+
+// Spin sum with one event per wave: |M|^2 only, no single helicities.  spins:
+// bit s3 + 2 s4 for each spin pair of t and tbar to sum; idx, count as in the
+// indexed variant or null; mfma: colour sum on the matrix cores.
+typedef hipError_t (*me_launch_sum_fn)(const double* mom, int64_t nevt, double* out, unsigned spins,
+                                       const me_params& prm, const int* idx, const int* count, bool mfma,
+                                       hipStream_t stream);
+
 enum { ME_KIND_EE = 0, ME_KIND_GG = 1, ME_KIND_QEW = 2 };
 
 struct me_process_desc {
@@ -45,6 +60,7 @@ struct me_process_desc {
     me_launch_mc_fn launch_mc;        // multi-channel form (nullptr: none)
     int nchan;                        // its channels
     const char* const* chan_desc;     // their descriptors
+    me_launch_sum_fn launch_sum;      // spin sum with one event per wave (nullptr: none)
 };
 
 const me_process_desc* me_find_process(const char* name);

@@ -112,7 +112,7 @@ extern "C" int unweight_two_stage(me_ctx* c, me_mlp* mlp, const double* momenta,
     hipLaunchKernelGGL(k_uw_stage1, grid, dim3(256), 0, s, c->uw_y, w_ps, uniforms, n, y_mu, y_sigma, s_max, c->uw_s,
                        c->uw_idx1, out_count);
     // exact float64 matrix element of the stage-1 survivors only
-    HCHK(c->proc->launch_f64_idx(momenta, n, c->uw_me2, c->d_good, c->nhel_good, c->prm, c->uw_idx1, out_count, s));
+    HCHK(me_launch_idx(c, momenta, n, c->uw_me2, c->uw_idx1, out_count, s));
     hipLaunchKernelGGL(k_uw_stage2, grid, dim3(256), 0, s, c->uw_idx1, c->uw_me2, w_ps, c->uw_s, uniforms, s_max,
                        r_max, out_count, out_idx, out_w);
     HCHK(hipGetLastError());

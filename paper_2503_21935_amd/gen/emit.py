@@ -11,6 +11,7 @@ Output: a header with one struct per process holding
 """
 from __future__ import annotations
 
+import itertools
 import math
 
 from .colour import colour_matrix_exact, mfma_fragments, orderings
@@ -499,6 +500,49 @@ class GGEmitter:
         out.append("    return acc;")
         return out
 
+    def emit_colour_blocks(self):
+        """J^dag N J in blocks.  N does not change when the same relabelling acts
+        on both orderings, so it commutes with any group of relabellings; under
+        an elementary 2-group (the Klein four-group on gluons 0..3, or the swap
+        of 0 and 1 for fewer gluons) sums and differences of the J of relabelled
+        orderings split it into one block per sign pattern: for 24 flows 4 blocks
+        of 6, 312 operations per part of J instead of 648."""
+        n = self.n
+        gens = [[1, 0, 3, 2], [2, 3, 0, 1]] if n >= 4 else [[1, 0]]
+        group = [(tuple(range(n)), ())]
+        for g in gens:
+            g = tuple(g) + tuple(range(len(g), n))
+            group = [(e, c + (0,)) for e, c in group] + [(tuple(g[x] for x in e), c + (1,)) for e, c in group]
+        chars = list(itertools.product((0, 1), repeat=len(gens)))
+        seen, reps = set(), []
+        for s in self.perms:
+            if s not in seen:
+                reps.append(s)
+                seen |= {tuple(e[x] for x in s) for e, _ in group}
+        at = lambda e, s: self.kindex[tuple(e[x] for x in s)]  # noqa: E731
+        out = ["    T acc = T(0);"]
+        for ch in chars:
+            sign = [(-1) ** sum(a * b for a, b in zip(c, ch)) for _, c in group]
+            out.append("    {  // signs " + " ".join(f"{v:+d}" for v in sign))
+            for i, s in enumerate(reps):
+                for part in "ri":
+                    terms = "".join(f" {'+' if v > 0 else '-'} J[{at(e, s)}].{part}" for v, (e, _) in zip(sign, group))
+                    out.append(f"        const T h{i}{part} ={terms[2:]};")
+            B = [[sum(v * self.num[at(group[0][0], s)][at(e, t)] for v, (e, _) in zip(sign, group)) for t in reps]
+                 for s in reps]
+            if any(B[i][j] != B[j][i] for i in range(len(reps)) for j in range(len(reps))):
+                raise ValueError("blocks of the colour matrix are not symmetric")
+            for i in range(len(reps)):
+                for part in "ri":
+                    z = f"T({B[i][i]}) * h{i}{part}"
+                    for j in range(i + 1, len(reps)):
+                        if B[i][j]:
+                            z = f"fma(T({2 * B[i][j]}), h{j}{part}, {z})"
+                    out.append(f"        acc = fma(h{i}{part}, {z}, acc);")
+            out.append("    }")
+        out.append(f"    return acc * T({1.0 / len(group)!r});")
+        return out
+
     def colour_flops(self):
         ncol = len(self.num)
         return 2 * ncol * ncol + 6 * ncol
@@ -675,6 +719,12 @@ class GGEmitter:
         h.append("    template <typename T>")
         h.append("    static MEV T colour_sum(const cx<T>* __restrict__ J) {")
         h.extend(self.emit_colour())
+        h.append("    }")
+        h.append("")
+        h.append("    // the same in blocks under relabellings of the gluons")
+        h.append("    template <typename T>")
+        h.append("    static MEV T colour_blocks(const cx<T>* __restrict__ J) {")
+        h.extend(self.emit_colour_blocks())
         h.append("    }")
         h.append("")
         import numpy as np
