@@ -87,10 +87,10 @@ int me_init(const char *process, const double *couplings, int n_couplings, const
  * stream:  hipStream_t (NULL = default stream); no host synchronisation.
  * nevt == 0 launches nothing.  Errors: ME_EINVAL (null pointer, nevt < 0),
  * ME_EDEVICE (launch failure).
- * Reproducibility: results are deterministic for every process except
- * "gg_ttggg", whose kernel adds the contributions of four waves into shared
- * colour-flow amplitudes with atomic float64 adds; its results agree from run
- * to run to rounding (relative 1e-15 level), not bit for bit.
+ * Reproducibility: results are deterministic, the same input gives the same
+ * bits (me_eval_helicities of "gg_ttggg" is the exception for out_qhel: its
+ * kernel adds the contributions of four waves into shared colour-flow
+ * amplitudes with atomic float64 adds and agrees from run to run to rounding).
  */
 int me_eval(me_ctx *ctx, const double *momenta, int64_t nevt, double *out_me2, void *stream);
 
@@ -129,8 +129,8 @@ int me_set_precision(me_ctx *ctx, int mode, double rel_tol);
  * equals the one-lane result up to the order of the helicity sum.  Applies to
  * the float64 form of me_eval only (the mixed form, its float64 rerun,
  * me_eval_helicities and unweighting keep one lane per event).  "gg_ttgg"
- * always spreads an event over a whole wave: there the setting is accepted and
- * every setting gives the same result.  Errors:
+ * and "gg_ttggg" always spread an event over a whole wave or workgroup: there
+ * the setting is accepted and every setting gives the same result.  Errors:
  * ME_EINVAL (null context, lanes neither 0 nor a power of two up to 64).
  */
 int me_set_helicity_lanes(me_ctx *ctx, int lanes);
@@ -203,7 +203,7 @@ int me_eval_mixed_noalloc(me_ctx *ctx, const double *momenta, int64_t nevt, doub
  *           h in 0..nhel-1 (particle i has helicity + when bit (npart-1-i)
  *           of h is set), including those the filter dropped.
  * out_me2:  as in me_eval, but summed over all helicities (no filter).  Where
- *           me_eval sums over real polarisation vectors ("gg_ttgg") it is
+ *           me_eval sums over real polarisation vectors ("gg_ttgg", "gg_ttggg") it is
  *           that sum, equal to the sum of out_qhel up to rounding.
  */
 int me_eval_helicities(me_ctx *ctx, const double *momenta, int64_t nevt, double *out_me2, double *out_qhel,

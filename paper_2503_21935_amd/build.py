@@ -29,7 +29,7 @@ COOP = {"gg_ttggg"}
 CM = {"gg_ttgg"}
 
 # processes whose float64 sum runs with one event per wave (me_wave.h)
-WAVE = {"gg_ttgg": "k_me_gg4_wave"}
+WAVE = {"gg_ttgg": "k_me_gg4_wave", "gg_ttggg": "k_me_gg5_wave"}
 
 # Calibration of the mixed form's amplitude error estimate (multiplies
 # u32 * 2 lambda_max(|N|) |S| |J| / Q); fixed by comparing float32 results
@@ -119,13 +119,17 @@ hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, un
 """
 
 _TU_WAVE = """// Generated translation unit: spin-summed float64 kernel of {name} (one event per wave).
-#include "me_wave.h"
+#include "{header}"
 #include "gen/proc_{name}.h"
 
 hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, unsigned spins, const me_params& prm,
                                 const int* idx, const int* count, bool mfma, hipStream_t s) {{
-    // events per block and turn: see me_wave_events
-    const int eb = me_wave_events(nevt);
+{launch}    return hipGetLastError();
+}}
+"""
+
+# one wave per block, one or two events at a time
+_LAUNCH_WAVE = """    const int eb = me_wave_events(nevt);
     const int64_t turns = (nevt + eb - 1) / eb;
     const dim3 grid((unsigned)(turns < ME_WAVE_BLOCKS ? turns : ME_WAVE_BLOCKS));
     if (mfma)
@@ -134,9 +138,23 @@ hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, un
     else
         hipLaunchKernelGGL(({kernel}<proc_{name}, false>), grid, dim3(64), 0, s, mom, nevt, out, spins, prm, idx,
                            count, eb);
-    return hipGetLastError();
-}}
 """
+# one event per workgroup
+_LAUNCH_GROUP = """    const dim3 grid((unsigned)(nevt < ME_GROUP_BLOCKS ? nevt : ME_GROUP_BLOCKS));
+    if (mfma)
+        hipLaunchKernelGGL(({kernel}<proc_{name}, true>), grid, dim3(w5::THREADS), 0, s, mom, nevt, out, spins, prm,
+                           idx, count);
+    else
+        hipLaunchKernelGGL(({kernel}<proc_{name}, false>), grid, dim3(w5::THREADS), 0, s, mom, nevt, out, spins, prm,
+                           idx, count);
+"""
+
+
+def _wave_tu(name):
+    group = name in COOP
+    launch = (_LAUNCH_GROUP if group else _LAUNCH_WAVE).format(name=name, kernel=WAVE[name])
+    return _TU_WAVE.format(name=name, header="me_wave5.h" if group else "me_wave.h", launch=launch)
+
 
 _TU_MC = """// Generated translation unit: multi-channel kernel of {name}.
 #include "me_kernels.h"
@@ -194,10 +212,12 @@ hipError_t me_launch_mixed_{name}(const double* mom, int64_t nevt, double* out, 
                                   float* err_out, unsigned char* flag_out, hipStream_t s);
 hipError_t me_launch_f64_cm_{name}(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                    const me_params& prm, double* qhel, int lg, hipStream_t s);
+hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, unsigned spins, const me_params& prm,
+                                const int* idx, const int* count, bool mfma, hipStream_t s);
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_GG, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, me_launch_mixed_{name}, {cest},
-    {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr, nullptr}};
+    {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}}};
 #endif
 """
 
@@ -290,6 +310,9 @@ def generate_sources(processes):
             path_c = os.path.join(GEN, f"tu_{name}_cm.hip")
             _write(path_c, _TU_COOP_CM.format(name=name, include=inc, proc=proc))
             tus.append(path_c)
+            path_w = os.path.join(GEN, f"tu_{name}_wave.hip")
+            _write(path_w, _wave_tu(name))
+            tus.append(path_w)
             continue
         cm, cm_ptr = ("", "nullptr")
         if name in CM:
@@ -306,7 +329,7 @@ def generate_sources(processes):
             cm += _WAVE_DECL.format(name=name)
             sum_ptr = f"me_launch_sum_{name}"
             path_w = os.path.join(GEN, f"tu_{name}_wave.hip")
-            _write(path_w, _TU_WAVE.format(name=name, kernel=WAVE[name]))
+            _write(path_w, _wave_tu(name))
             tus.append(path_w)
         _write(path, _TU.format(name=name, include=inc, kernel=kernel, proc=proc, kind=kind, mixed=mixed,
                                 mixed_ptr=mixed_ptr, cest=MIXED_CEST.get(name, 8.0), colerr=colerr, cm=cm,

@@ -31,6 +31,9 @@ typedef hipError_t (*me_launch_mc_fn)(const double* mom, int64_t nevt, double* o
 // Blocks of a grid whose blocks stride over the events, one event per block at a time.
 #define ME_WAVE_BLOCKS 8192
 
+// Blocks of the kernel with one event per workgroup and CU.
+#define ME_GROUP_BLOCKS 1024
+
 // Events that such a block sets up together: two, which fills the lanes of
 // the setup phases, once there are enough events to keep every CU's eight waves
 // busy that way; below that one, since a call then takes as long as one block.

@@ -109,12 +109,47 @@ MEV row current(const row& f, const row& r) {
     const c2 e = f.s[2] * r.s[1], g = f.s[3] * r.s[0], h = f.s[2] * r.s[0], k = f.s[3] * r.s[1];
     return {{(a - b) + (g - e), (c - d) + (h - k), times_mi((d + c) + (h + k)), -((b + a) + (e + g))}};
 }
-// sum over mu of V_mu W^mu
+// acc + sum over mu of V_mu W^mu
+MEV c2 cdot_acc(const row& V, const vec& W, c2 acc) {
+    acc = axpy(W.v[0], V.s[0], acc);
+    acc = axpy(W.v[1], V.s[1], acc);
+    acc = axpy(W.v[2], V.s[2], acc);
+    return axpy(W.v[3], V.s[3], acc);
+}
 MEV c2 cdot(const row& V, const vec& W) {
     c2 r = rmul(W.v[0], V.s[0]);
     r = axpy(W.v[1], V.s[1], r);
     r = axpy(W.v[2], V.s[2], r);
     return axpy(W.v[3], V.s[3], r);
+}
+
+// Real transverse vectors of a gluon of momentum k (those that gluon_eps
+// combines): e1 = (cos th cos ph, cos th sin ph, -sin th), e2 = (-sin ph, cos ph, 0);
+// along the z axis the azimuth is taken as 0.
+MEV vec polarisation(const vec& k, bool e2) {
+    const double kx = k.v[1], ky = k.v[2], kz = k.v[3];
+    const double kt2 = kx * kx + ky * ky, kk = sqrt(kt2 + kz * kz), kt = sqrt(kt2);
+    const bool axis = !(kt > 0.0);
+    const double ikt = 1.0 / kt, ikk = 1.0 / kk, c = kz * ikk;
+    vec e;
+    e.v[0] = 0.0;
+    e.v[1] = axis ? (e2 ? 0.0 : (kz >= 0.0) ? 1.0 : -1.0) : e2 ? -ky * ikt : c * kx * ikt;
+    e.v[2] = axis ? (e2 ? 1.0 : 0.0) : e2 ? kx * ikt : c * ky * ikt;
+    e.v[3] = (axis || e2) ? 0.0 : -kt * ikk;
+    return e;
+}
+// ubar(p3) (e = 0) and v(p4) as a row (e = 1) at helicity lam.
+MEV row end_row(const vec& q, double m, int e, int lam) {
+    const mom4<double> p{q.v[0], q.v[1], q.v[2], q.v[3]};
+    double pabs, wm, wp;
+    spinor_weights(p, m, pabs, wm, wp);
+    c2 h0, h1;
+    helicity_chi(p, pabs, e ? -lam : lam, h0, h1);
+    // ubar = (conj of the right, conj of the left half); v as the row (v1, -v0, -v3, v2)
+    const double a = ((lam > 0) != (e == 1)) ? wm : wp;
+    const double b = e ? ((lam > 0) ? wm : wp) : ((lam > 0) ? wp : wm);
+    return e ? row{{rmul(a, h1), rmul(-a, h0), rmul(b, h1), rmul(-b, h0)}}
+             : row{{conj(rmul(b, h0)), conj(rmul(b, h1)), conj(rmul(a, h0)), conj(rmul(a, h1))}};
 }
 
 // f(0), f(1), ... f(N - 1) with constant arguments, so that registers can be indexed.
@@ -427,33 +462,13 @@ __global__ __launch_bounds__(64, CM ? 1 : 2) void k_me_gg4_wave(const double* __
             if (hl < 8) {
                 const int a = hl >> 1;
                 const vec q = ld_vec(T, B + q_at(a), 1);
-                const double sg = a < 2 ? 1.0 : -1.0;
-                const double kx = sg * q.v[1], ky = sg * q.v[2], kz = sg * q.v[3];
-                const double kt2 = kx * kx + ky * ky, kk = sqrt(kt2 + kz * kz), kt = sqrt(kt2);
-                const bool axis = !(kt > 0.0);
-                const double ikt = 1.0 / kt, ikk = 1.0 / kk, c = kz * ikk;
-                const bool e2 = hl & 1;
-                vec e;
-                e.v[0] = 0.0;
-                e.v[1] = axis ? (e2 ? 0.0 : (kz >= 0.0) ? 1.0 : -1.0) : e2 ? -ky * ikt : c * kx * ikt;
-                e.v[2] = axis ? (e2 ? 1.0 : 0.0) : e2 ? kx * ikt : c * ky * ikt;
-                e.v[3] = (axis || e2) ? 0.0 : -kt * ikk;
-                st_vec(T, B + 16 * (S_EPS + 4 * a + (hl & 1)), 2, mul(prm.gs, e));
+                st_vec(T, B + 16 * (S_EPS + 4 * a + (hl & 1)), 2,
+                       mul(prm.gs, polarisation(a < 2 ? q : mul(-1.0, q), hl & 1)));
             }
             // end rows: lane (end, spin)
             if (hl < 4) {
-                const int e = hl >> 1, lam = (hl & 1) ? 1 : -1;
-                const vec q = ld_vec(T, 16 * (S_P + 12 * j + 2 * (4 + e)), 1);
-                const mom4<double> p{q.v[0], q.v[1], q.v[2], q.v[3]};
-                double pabs, wm, wp;
-                spinor_weights(p, m, pabs, wm, wp);
-                c2 h0, h1;
-                helicity_chi(p, pabs, e ? -lam : lam, h0, h1);
-                // ubar = (conj of the right, conj of the left half); v as the row (v1, -v0, -v3, v2)
-                const double a = ((lam > 0) != (e == 1)) ? wm : wp;
-                const double b = e ? ((lam > 0) ? wm : wp) : ((lam > 0) ? wp : wm);
-                const row f = e ? row{{rmul(a, h1), rmul(-a, h0), rmul(b, h1), rmul(-b, h0)}}
-                                : row{{conj(rmul(b, h0)), conj(rmul(b, h1)), conj(rmul(a, h0)), conj(rmul(a, h1))}};
+                const int e = hl >> 1;
+                const row f = end_row(ld_vec(T, 16 * (S_P + 12 * j + 2 * (4 + e)), 1), m, e, (hl & 1) ? 1 : -1);
                 st_row(T, B + 16 * (S_N0 + 8 * e + (hl & 1)), 2, f);
             }
             __syncthreads();

@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import os
 
+from . import wave5
 from .coop import GGCoopEmitter
 from .emit import GGEmitter
 from .qew import QEWEmitter
@@ -93,6 +94,13 @@ def generate(outdir: str, processes=None, merge: bool = True) -> dict:
             with open(path, "w") as f:
                 f.write(src)
         info[name] = dict(em.plan.stats(), lcd=em.lcd, ncol=len(em.perms))
+        if n == wave5.N:
+            src = wave5.render()
+            path = os.path.join(outdir, f"proc_{name}_wave.h")
+            old = open(path).read() if os.path.exists(path) else None
+            if old != src:
+                with open(path, "w") as f:
+                    f.write(src)
         if name in MULTICHANNEL:
             mc = GGEmitter(name, n, merge=False, cap=MC_LIVE_CAP[name])
             src = mc.render_mc()
