@@ -46,8 +46,16 @@ HIPFLAGS = [
 ]
 
 _TU_QEW = """// Generated translation unit: kernels of {name} (quark line + lepton pair).
-#include "me_qew.h"
+#include "me_qew_pol.h"
 {include}
+
+static hipError_t launch_sum(const double* mom, int64_t nevt, double* out, unsigned, const me_params& prm,
+                             const int* idx, const int* count, bool, hipStream_t s) {{
+    const int64_t per = 64 >> {proc}::ngluon;  // events per wave
+    const dim3 grid((unsigned)((nevt + per - 1) / per));
+    hipLaunchKernelGGL((k_me_qew_pol<{proc}>), grid, dim3(64), 0, s, mom, nevt, out, prm, idx, count);
+    return hipGetLastError();
+}}
 
 static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                              const me_params& prm, double* qhel, int lg, hipStream_t s) {{
@@ -69,7 +77,7 @@ static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, c
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_QEW, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, nullptr, 8.0,
-    0.0, nullptr, nullptr, 0, nullptr, nullptr}};
+    0.0, nullptr, nullptr, 0, nullptr, launch_sum}};
 #endif
 """
 

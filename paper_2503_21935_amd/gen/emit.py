@@ -508,7 +508,7 @@ class GGEmitter:
         orderings split it into one block per sign pattern: for 24 flows 4 blocks
         of 6, 312 operations per part of J instead of 648."""
         n = self.n
-        gens = [[1, 0, 3, 2], [2, 3, 0, 1]] if n >= 4 else [[1, 0]]
+        gens = [[1, 0, 3, 2], [2, 3, 0, 1]] if n >= 4 else [[1, 0]] if n >= 2 else []
         group = [(tuple(range(n)), ())]
         for g in gens:
             g = tuple(g) + tuple(range(len(g), n))

@@ -248,6 +248,12 @@ class QEWEmitter(GGEmitter):
         h.append("    static MEV T colour_sum(const cx<T>* __restrict__ J) {")
         h.extend(self.emit_colour())
         h.append("    }")
+        h.append("")
+        h.append("    // the same in blocks under relabellings of the gluons")
+        h.append("    template <typename T>")
+        h.append("    static MEV T colour_blocks(const cx<T>* __restrict__ J) {")
+        h.extend(self.emit_colour_blocks())
+        h.append("    }")
         h.append("};")
         return "\n".join(h) + "\n"
 

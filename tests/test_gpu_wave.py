@@ -1,6 +1,7 @@
-"""The spin-summed float64 kernels with one event per wave (run on an MI355X).
+"""The spin-summed float64 kernels with shared wavefunctions (run on an MI355X).
 
-Sizes at the edges of the grid (8192 waves, or 1024 workgroups, that stride over the events), the
+Sizes at the edges of the grid (8192 waves, or 1024 workgroups, that stride over the events; partly
+filled waves of several events), the
 indexed form, and a massless top, where the helicity filter drops the spin
 pairs that vanish.  Against the oracle, event by event: both sides work in
 float64 with the same momenta, so all but the ill-conditioned events agree to
@@ -32,7 +33,9 @@ def close(got, want):
 
 
 @pytest.mark.parametrize("proc,n", [("gg_ttgg", 1), ("gg_ttgg", 2), ("gg_ttgg", 8191), ("gg_ttgg", 8193),
-                                    ("gg_ttgg", 20000), ("gg_ttggg", 1), ("gg_ttggg", 255), ("gg_ttggg", 1025)])
+                                    ("gg_ttgg", 20000), ("gg_ttggg", 1), ("gg_ttggg", 255), ("gg_ttggg", 1025),
+                                    ("gux_taptamux", 1), ("gux_taptamux", 33), ("gux_taptamgux", 15),
+                                    ("gux_taptamgux", 4099), ("gux_taptamggux", 7), ("gux_taptamggux", 2049)])
 def test_edges_of_the_grid(env, proc, n):
     torch, me = env
     print(f"[wave] {proc} n={n}", flush=True)
