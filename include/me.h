@@ -128,10 +128,10 @@ int me_set_precision(me_ctx *ctx, int mode, double rel_tol);
  * of helicities kept (one lane per event from 65536 events up).  The result
  * equals the one-lane result up to the order of the helicity sum.  Applies to
  * the float64 form of me_eval only (the mixed form, its float64 rerun,
- * me_eval_helicities and unweighting keep one lane per event).  "gg_ttgg",
- * "gg_ttggg" and the quark-line processes always spread an event over the lanes
- * that suit them: there the setting is accepted and every setting gives the
- * same result.  Errors:
+ * me_eval_helicities and unweighting keep one lane per event).Only
+ * "ee_mumu" is evaluated that way: the other processes always spread an event
+ * over the lanes that suit them, and there the setting is accepted and every
+ * setting gives the same result.  Errors:
  * ME_EINVAL (null context, lanes neither 0 nor a power of two up to 64).
  */
 int me_set_helicity_lanes(me_ctx *ctx, int lanes);
@@ -204,8 +204,7 @@ int me_eval_mixed_noalloc(me_ctx *ctx, const double *momenta, int64_t nevt, doub
  *           h in 0..nhel-1 (particle i has helicity + when bit (npart-1-i)
  *           of h is set), including those the filter dropped.
  * out_me2:  as in me_eval, but summed over all helicities (no filter).  Where
- *           me_eval sums over real polarisation vectors (every process but "ee_mumu", "gg_tt"
- *           and "gg_ttg") it is
+ *           me_eval sums over real polarisation vectors (every process but "ee_mumu") it is
  *           that sum, equal to the sum of out_qhel up to rounding.
  */
 int me_eval_helicities(me_ctx *ctx, const double *momenta, int64_t nevt, double *out_me2, double *out_qhel,

@@ -28,8 +28,10 @@ COOP = {"gg_ttggg"}
 # always get it
 CM = {"gg_ttgg"}
 
-# processes whose float64 sum runs with one event per wave (me_wave.h)
-WAVE = {"gg_ttgg": "k_me_gg4_wave", "gg_ttggg": "k_me_gg5_wave"}
+# kernels of the float64 sum over spins with real polarisation vectors
+WAVE = {"gg_tt": "k_me_gg2_pol", "gg_ttg": "k_me_gg3_pol", "gg_ttgg": "k_me_gg4_wave", "gg_ttggg": "k_me_gg5_wave"}
+# events per wave of those that hold several
+EVENTS_PER_WAVE = {"gg_tt": 64, "gg_ttg": 8}
 
 # Calibration of the mixed form's amplitude error estimate (multiplies
 # u32 * 2 lambda_max(|N|) |S| |J| / Q); fixed by comparing float32 results
@@ -156,9 +158,17 @@ _LAUNCH_GROUP = """    const dim3 grid((unsigned)(nevt < ME_GROUP_BLOCKS ? nevt 
         hipLaunchKernelGGL(({kernel}<proc_{name}, false>), grid, dim3(w5::THREADS), 0, s, mom, nevt, out, spins, prm,
                            idx, count);
 """
+# several events per wave
+_LAUNCH_LANES = """    (void)mfma;
+    const dim3 grid((unsigned)((nevt + {per} - 1) / {per}));
+    hipLaunchKernelGGL(({kernel}<proc_{name}>), grid, dim3(64), 0, s, mom, nevt, out, spins, prm, idx, count);
+"""
 
 
 def _wave_tu(name):
+    if name in EVENTS_PER_WAVE:
+        return _TU_WAVE.format(name=name, header="me_gg_pol.h",
+                               launch=_LAUNCH_LANES.format(name=name, kernel=WAVE[name], per=EVENTS_PER_WAVE[name]))
     group = name in COOP
     launch = (_LAUNCH_GROUP if group else _LAUNCH_WAVE).format(name=name, kernel=WAVE[name])
     return _TU_WAVE.format(name=name, header="me_wave5.h" if group else "me_wave.h", launch=launch)

@@ -32,7 +32,8 @@ def close(got, want):
     assert np.all(np.isfinite(got)) and rel.max() <= 1e-9 and np.mean(rel > 1e-12) <= 0.02, rel.max()
 
 
-@pytest.mark.parametrize("proc,n", [("gg_ttgg", 1), ("gg_ttgg", 2), ("gg_ttgg", 8191), ("gg_ttgg", 8193),
+@pytest.mark.parametrize("proc,n", [("gg_tt", 1), ("gg_tt", 127), ("gg_ttg", 9), ("gg_ttg", 4103),
+                                    ("gg_ttgg", 1), ("gg_ttgg", 2), ("gg_ttgg", 8191), ("gg_ttgg", 8193),
                                     ("gg_ttgg", 20000), ("gg_ttggg", 1), ("gg_ttggg", 255), ("gg_ttggg", 1025),
                                     ("gux_taptamux", 1), ("gux_taptamux", 33), ("gux_taptamgux", 15),
                                     ("gux_taptamgux", 4099), ("gux_taptamggux", 7), ("gux_taptamggux", 2049)])
@@ -52,7 +53,7 @@ def test_edges_of_the_grid(env, proc, n):
     m.close()
 
 
-@pytest.mark.parametrize("proc,n", [("gg_ttgg", 9000), ("gg_ttgg", 777), ("gg_ttggg", 300)])
+@pytest.mark.parametrize("proc,n", [("gg_tt", 1000), ("gg_ttg", 1001), ("gg_ttgg", 9000), ("gg_ttgg", 777), ("gg_ttggg", 300)])
 def test_indexed_form(env, proc, n):
     """A tolerance no float32 result meets sends every event through the
     indexed form: the same values bit for bit."""
@@ -67,10 +68,10 @@ def test_indexed_form(env, proc, n):
     m.close()
 
 
-@pytest.mark.parametrize("proc", ["gg_ttgg", "gg_ttggg"])
+@pytest.mark.parametrize("proc", ["gg_tt", "gg_ttg", "gg_ttgg", "gg_ttggg"])
 def test_massless_top(env, proc):
     torch, me = env
-    nf = {"gg_ttgg": 4, "gg_ttggg": 5}[proc]
+    nf = {"gg_tt": 2, "gg_ttg": 3, "gg_ttgg": 4, "gg_ttggg": 5}[proc]
     mom = rambo(200 if nf < 5 else 12, 13000.0, [0.0] * nf, 63)
     m = me.MatrixElement(proc, masses=(91.188, 2.4414, 0.0, 0.0))
     assert len(m.good_helicities()) < 1 << (nf + 2)
