@@ -128,7 +128,7 @@ int me_set_precision(me_ctx *ctx, int mode, double rel_tol);
  * of helicities kept (one lane per event from 65536 events up).  The result
  * equals the one-lane result up to the order of the helicity sum.  Applies to
  * the float64 form of me_eval only (the mixed form, its float64 rerun,
- * me_eval_helicities and unweighting keep one lane per event).Only
+ * me_eval_helicities and unweighting keep one lane per event).  Only
  * "ee_mumu" is evaluated that way: the other processes always spread an event
  * over the lanes that suit them, and there the setting is accepted and every
  * setting gives the same result.  Errors:
