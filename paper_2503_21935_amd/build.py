@@ -79,7 +79,7 @@ static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, c
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_QEW, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, nullptr, 8.0,
-    0.0, nullptr, nullptr, 0, nullptr, launch_sum}};
+    0.0, nullptr, nullptr, 0, nullptr, launch_sum, nullptr}};
 #endif
 """
 
@@ -107,7 +107,7 @@ static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, c
 extern const me_process_desc me_desc_{name} = {{
     "{name}", {kind}, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, {mixed_ptr}, {cest},
-    {colerr}, {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}}};
+    {colerr}, {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}, {chan_ptr}}};
 #endif
 """
 
@@ -116,6 +116,8 @@ _MC_DECL = """
 // the multi-channel kernel is compiled in a translation unit of its own
 hipError_t me_launch_mc_{name}(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                const me_params& prm, const int* chan, double* alpha, hipStream_t s);
+hipError_t me_launch_chan_{name}(const double* mom, int64_t nevt, double* out, const me_params& prm, const int* chan,
+                                 double* alpha, hipStream_t s);
 extern const int me_nchan_{name};
 extern const char* const* const me_chan_desc_{name};
 #endif
@@ -161,7 +163,8 @@ _LAUNCH_GROUP = """    const dim3 grid((unsigned)(nevt < ME_GROUP_BLOCKS ? nevt 
 # several events per wave
 _LAUNCH_LANES = """    (void)mfma;
     const dim3 grid((unsigned)((nevt + {per} - 1) / {per}));
-    hipLaunchKernelGGL(({kernel}<proc_{name}>), grid, dim3(64), 0, s, mom, nevt, out, spins, prm, idx, count);
+    hipLaunchKernelGGL(({kernel}<proc_{name}>), grid, dim3(64), 0, s, mom, nevt, out, spins, prm, idx, count, nullptr,
+                       nullptr);
 """
 
 
@@ -191,6 +194,42 @@ extern const int me_nchan_{name} = proc_{name}_mc::nchan;
 extern const char* const* const me_chan_desc_{name} = channel_desc_{name};
 #endif
 """
+
+_TU_CHAN = """// Generated translation unit: multi-channel form of {name} with shared wavefunctions.
+#include "{header}"
+#include "gen/proc_{name}.h"
+#include "gen/proc_{name}_mc.h"
+
+hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, unsigned spins, const me_params& prm,
+                                const int* idx, const int* count, bool mfma, hipStream_t s);
+
+hipError_t me_launch_chan_{name}(const double* mom, int64_t nevt, double* out, const me_params& prm, const int* chan,
+                                 double* alpha, hipStream_t s) {{
+{launch}    return hipGetLastError();
+}}
+"""
+
+# weights in a kernel of their own
+_LAUNCH_CHAN_WAVE = """    const hipError_t e = me_launch_sum_{name}(mom, nevt, out, 0xfu, prm, nullptr, nullptr, false, s);
+    if (e != hipSuccess) return e;
+    const int eb = me_wave_events(nevt);
+    const int64_t turns = (nevt + eb - 1) / eb;
+    const dim3 grid((unsigned)(turns < ME_WAVE_BLOCKS ? turns : ME_WAVE_BLOCKS));
+    hipLaunchKernelGGL((k_me_gg4_chan<chan_ids_{name}>), grid, dim3(64), 0, s, mom, nevt, chan, alpha, prm, eb);
+"""
+# with |M|^2 in one kernel
+_LAUNCH_CHAN_LANES = """    const dim3 grid((unsigned)((nevt + {per} - 1) / {per}));
+    hipLaunchKernelGGL(({kernel}<proc_{name}, chan_ids_{name}>), grid, dim3(64), 0, s, mom, nevt, out, 0xfu, prm,
+                       nullptr, nullptr, chan, alpha);
+"""
+
+
+def _chan_tu(name):
+    if name in EVENTS_PER_WAVE:
+        launch = _LAUNCH_CHAN_LANES.format(name=name, kernel=WAVE[name], per=EVENTS_PER_WAVE[name])
+        return _TU_CHAN.format(name=name, header="me_gg_pol.h", launch=launch)
+    return _TU_CHAN.format(name=name, header="me_chan.h", launch=_LAUNCH_CHAN_WAVE.format(name=name))
+
 
 _CM = """
 static hipError_t launch_f64_cm(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
@@ -235,7 +274,7 @@ hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, un
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_GG, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, me_launch_mixed_{name}, {cest},
-    {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}}};
+    {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}, nullptr}};
 #endif
 """
 
@@ -335,13 +374,17 @@ def generate_sources(processes):
         cm, cm_ptr = ("", "nullptr")
         if name in CM:
             cm, cm_ptr = _CM.format(proc=proc), "launch_f64_cm"
-        mc_ptr, mc_n, mc_desc = "nullptr", "0", "nullptr"
+        mc_ptr, mc_n, mc_desc, chan_ptr = "nullptr", "0", "nullptr", "nullptr"
         if name in MULTICHANNEL:
             cm += _MC_DECL.format(name=name)
             mc_ptr, mc_n, mc_desc = f"me_launch_mc_{name}", f"me_nchan_{name}", f"me_chan_desc_{name}"
             path_mc = os.path.join(GEN, f"tu_{name}_mc.hip")
             _write(path_mc, _TU_MC.format(name=name))
             tus.append(path_mc)
+            path_ch = os.path.join(GEN, f"tu_{name}_chan.hip")
+            _write(path_ch, _chan_tu(name))
+            tus.append(path_ch)
+            chan_ptr = f"me_launch_chan_{name}"
         sum_ptr = "nullptr"
         if name in WAVE:
             cm += _WAVE_DECL.format(name=name)
@@ -351,7 +394,7 @@ def generate_sources(processes):
             tus.append(path_w)
         _write(path, _TU.format(name=name, include=inc, kernel=kernel, proc=proc, kind=kind, mixed=mixed,
                                 mixed_ptr=mixed_ptr, cest=MIXED_CEST.get(name, 8.0), colerr=colerr, cm=cm,
-                                cm_ptr=cm_ptr, mc_ptr=mc_ptr, mc_n=mc_n, mc_desc=mc_desc, sum_ptr=sum_ptr))
+                                cm_ptr=cm_ptr, mc_ptr=mc_ptr, mc_n=mc_n, mc_desc=mc_desc, sum_ptr=sum_ptr, chan_ptr=chan_ptr))
         tus.append(path)
     decls = "\n".join(f"extern const me_process_desc me_desc_{n};" for n in processes)
     ptrs = ", ".join(f"&me_desc_{n}" for n in processes)

@@ -434,6 +434,13 @@ int me_eval_multichannel(me_ctx* c, const double* momenta, const int32_t* chan, 
     if (nevt == 0) return ME_OK;
     if (!momenta || !chan || !out_me2 || !out_alpha) return fail(ME_EINVAL, "null buffer");
     if (nevt > 0x7fffffffLL) return fail(ME_EINVAL, "nevt above 2^31 - 1");
+    // The kernels with shared wavefunctions sum over every helicity.  Where the
+    // filter has dropped some (a massless top: |M|^2 vanishes there, single
+    // diagrams need not), the sums run over the kept ones, one by one.
+    if (c->proc->launch_chan && c->nhel_good == c->proc->nhel) {
+        HIP_CHECK(c->proc->launch_chan(momenta, nevt, out_me2, c->prm, chan, out_alpha, (hipStream_t)stream));
+        return ME_OK;
+    }
     HIP_CHECK(c->proc->launch_mc(momenta, nevt, out_me2, c->d_good, c->nhel_good, c->prm, chan, out_alpha,
                                  (hipStream_t)stream));
     return ME_OK;

@@ -2,8 +2,8 @@
 // polarisation vectors.  Rules, signs and the row form of columns as in
 // me_wave.h.
 //
-// Two gluons: one event per lane, everything in registers.  All sixteen
-// configurations share four one-gluon rows per ordering and end.
+// Two gluons: one event per lane, everything in registers.  The configurations
+// share four one-gluon rows per ordering and spin.
 //   J_ab = L(a) W(b) v + ubar W(ab) v.
 // Three gluons: eight lanes per event, lane l the gluon polarisations l; the
 // externals, one-gluon rows, pair currents and the current of the line's ends
@@ -11,18 +11,23 @@
 // polarisations and the four spin pairs.
 //   J_abc = L(a) [W(b) R(c) + W(bc) v] + ubar W(ab) R(c) + ubar W(abc) v.
 //
-// Both are bound by VALU issue (2,600 vector instructions per wave of 64 events
-// and of eight events).  Against one helicity per pass over the diagram program
-// (k_me_gg): 2^20 events of g g -> t tbar take 127 us against 521 us, 2^18
-// events of g g -> t tbar g 0.30 ms against 2.7 ms.
+// Both are bound by VALU issue (2,900 vector instructions per wave of 64 events
+// and 2,600 per wave of eight).  Against one helicity per pass over the diagram program
+// (k_me_gg): 2^20 events of g g -> t tbar take 110 us against 521 us, 2^18
+// events of g g -> t tbar g 0.30 ms against 2.7 ms; with the weights of the
+// events' channels 2^19 events of g g -> t tbar 74 us against 316 us, 2^17 events
+// of g g -> t tbar g 0.24 ms against 0.55 ms (k_me_gg_mc).
 #pragma once
 #include "me_qew_pol.h"
 
-// idx, count and spins as for k_me_gg4_wave.
-template <class P>
+// idx, count and spins as for k_me_gg4_wave.  With IDS (the channel numbers of
+// the diagrams) also the single-diagram weight of each event's channel, as k_me_gg4_chan.
+template <class P, class IDS = void>
 __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__ mom, int64_t nevt,
                                                       double* __restrict__ out, unsigned spins, me_params prm,
-                                                      const int* __restrict__ idx, const int* __restrict__ count) {
+                                                      const int* __restrict__ idx, const int* __restrict__ count,
+                                                      const int* __restrict__ chan = nullptr,
+                                                      double* __restrict__ alpha = nullptr) {
     using namespace wv;
     static_assert(P::ngluon == 2 && P::ncol == 2, "two gluons");
     int64_t ev = (int64_t)blockIdx.x * 64 + threadIdx.x;
@@ -32,7 +37,16 @@ __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__
     } else if (ev >= nevt) {
         return;
     }
+    constexpr bool MC = !std::is_void_v<IDS>;
     const double m = prm.mt;
+    const int ch = MC ? chan[ev] : 0;
+    double num = 0.0, den = 0.0;
+    auto found = [&](auto id, c2 a) __attribute__((always_inline)) {
+        const double a2 = fma(a.r, a.r, a.i * a.i);
+        den += a2;
+        num += id == ch ? a2 : 0.0;
+        asm volatile("" : "+v"(den), "+v"(num));
+    };
     vec q[2], p3, p4;
     {
         const double* pe = mom + ev * 16;
@@ -46,56 +60,60 @@ __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__
         n3[S] = end_row(p3, m, 0, S ? 1 : -1);
         n4[S] = end_row(p4, m, 1, S ? 1 : -1);
     });
-    vec e[2][2];
-    each<4>([&](auto K) __attribute__((always_inline)) {
-        e[K / 2][K % 2] = mul(prm.gs, polarisation(q[K / 2], K % 2));
+    vec e[2][2], K[2];
+    c2 f[2];
+    each<2>([&](auto A) __attribute__((always_inline)) {
+        e[A][0] = mul(prm.gs, polarisation(q[A], false));
+        e[A][1] = mul(prm.gs, polarisation(q[A], true));
+        K[A] = add(p3, mul(-1.0, q[A]));
+        f[A] = crecip(mdot(K[A], K[A]) - m * m, m * prm.wt);
     });
-    auto line = [&](auto A) __attribute__((always_inline)) {  // L(a) up to the sign, by polarisation and spin
-        const vec K = add(p3, mul(-1.0, q[A]));
-        const c2 f = crecip(K.v[0] * K.v[0] - K.v[1] * K.v[1] - K.v[2] * K.v[2] - K.v[3] * K.v[3] - m * m, m * prm.wt);
-        return [=, &n3, &e](auto PS) __attribute__((always_inline)) {
-            return scale(f, slash_m(slash(n3[PS / 2], e[A][PS % 2]), K, m));
-        };
-    };
-    // J_01 without the tree: [L of gluon 0 (pol, spin of t)][gluon 1's pol, spin of tbar]
-    c2 J[4][4];
+    vec w[4];  // W(01) by polarisations
     {
-        const auto L = line(std::integral_constant<int, 0>{});
-        row x[4];
-        each<4>([&](auto K) __attribute__((always_inline)) { x[K] = slash(n4[K / 2], e[1][K % 2]); });
-        each<4>([&](auto A) __attribute__((always_inline)) {
-            const row l = L(A);
-            each<4>([&](auto B) __attribute__((always_inline)) { J[A][B] = wedge(l, x[B], c2{0.0, 0.0}); });
-            settle(J[A]);
+        const vec Q = add(q[0], q[1]);
+        const double iq = 1.0 / mdot(Q, Q);
+        each<4>([&](auto PP) __attribute__((always_inline)) {
+            vec t{{0.0, 0.0, 0.0, 0.0}};
+            sub_vvv(t, e[0][PP % 2], q[0], e[1][PP / 2], q[1]);
+            w[PP] = mul(iq, t);
         });
     }
+    // Spin by spin: the rows L of all sixteen at once, and those of the other end,
+    // do not fit in registers (2^20 events took 126 us); slashing the latter anew costs less (110 us).
     double acc = 0.0;
-    const vec Q = add(q[0], q[1]);
-    const double iq = 1.0 / (Q.v[0] * Q.v[0] - Q.v[1] * Q.v[1] - Q.v[2] * Q.v[2] - Q.v[3] * Q.v[3]);
-    const auto L = line(std::integral_constant<int, 1>{});
-    vec w[4];  // W(01) by polarisations
-    each<4>([&](auto K) __attribute__((always_inline)) {
-        vec t{{0.0, 0.0, 0.0, 0.0}};
-        sub_vvv(t, e[0][K % 2], q[0], e[1][K / 2], q[1]);
-        w[K] = mul(iq, t);
-    });
-    row x[4];
-    each<4>([&](auto K) __attribute__((always_inline)) { x[K] = slash(n4[K / 2], e[0][K % 2]); });
     each<2>([&](auto S3) __attribute__((always_inline)) {
-        const row l[2] = {L(std::integral_constant<int, 2 * S3>{}), L(std::integral_constant<int, 2 * S3 + 1>{})};
+        settle(n4[0].s), settle(n4[1].s);  // what is formed from them is not kept for the other spin
+        row L[2][2];  // L(a) up to the sign, by gluon and polarisation
+        each<4>([&](auto I) __attribute__((always_inline)) {
+            L[I / 2][I % 2] = scale(f[I / 2], slash_m(slash(n3[S3], e[I / 2][I % 2]), K[I / 2], m));
+        });
         each<2>([&](auto S4) __attribute__((always_inline)) {
-            const row V = current(n3[S3], n4[S4]);
+            c2 t[4], J01[4], J10[4];  // by polarisations
+            {
+                const row V = current(n3[S3], n4[S4]);
+                each<4>([&](auto PP) __attribute__((always_inline)) { t[PP] = cdot(V, w[PP]); });
+                settle(t);
+            }
+            each<2>([&](auto B) __attribute__((always_inline)) {
+                const row x = slash(n4[S4], e[1][B]), y = slash(n4[S4], e[0][B]);
+                each<2>([&](auto A) __attribute__((always_inline)) {
+                    J01[A + 2 * B] = wedge(L[0][A], x, c2{0.0, 0.0});
+                    J10[B + 2 * A] = wedge(L[1][A], y, c2{0.0, 0.0});
+                });
+            });
+            settle(J01), settle(J10);
             double part = 0.0;
             each<4>([&](auto PP) __attribute__((always_inline)) {
-                constexpr int P0 = PP % 2, P1 = PP / 2;
-                const c2 t = cdot(V, w[PP]);
-                c2 f[2] = {J[P0 + 2 * S3][P1 + 2 * S4] + t, wedge(l[P1], x[P0 + 2 * S4], -t)};
-                part += P::colour_blocks(f);
+                if constexpr (MC) found(IDS::tree[0], t[PP]), found(IDS::order[0], J01[PP]), found(IDS::order[1], J10[PP]);
+                c2 J[2] = {J01[PP] + t[PP], J10[PP] - t[PP]};
+                part += P::colour_blocks(J);
             });
             acc += ((spins >> (S3 + 2 * S4)) & 1) ? part : 0.0;
+            asm volatile("" : "+v"(acc));  // or the sums sink below the next ones, their operands held
         });
     });
     out[ev] = acc * (1.0 / (256.0 * P::identical * P::lcd));
+    if constexpr (MC) alpha[ev] = num / den;
 }
 
 namespace g3 {
@@ -128,10 +146,12 @@ MEV void st8(double* p, const row& f) {
 
 }  // namespace g3
 
-template <class P>
+template <class P, class IDS = void>
 __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__ mom, int64_t nevt,
                                                       double* __restrict__ out, unsigned spins, me_params prm,
-                                                      const int* __restrict__ idx, const int* __restrict__ count) {
+                                                      const int* __restrict__ idx, const int* __restrict__ count,
+                                                      const int* __restrict__ chan = nullptr,
+                                                      double* __restrict__ alpha = nullptr) {
     using namespace g3;
     static_assert(P::ngluon == 3 && P::ncol == 6, "three gluons");
     __shared__ double2 mem[8 * (STRIDE / 2)];
@@ -144,6 +164,15 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
     const bool valid = i < n;
     if (!valid) i = n - 1;
     const int64_t ev = count ? (int64_t)idx[i] : i;
+    constexpr bool MC = !std::is_void_v<IDS>;
+    const int ch = MC ? chan[ev] : 0;
+    double num = 0.0, den = 0.0;
+    auto found = [&](auto id, c2 a) __attribute__((always_inline)) {
+        const double a2 = fma(a.r, a.r, a.i * a.i);
+        den += a2;
+        num += id == ch ? a2 : 0.0;
+        asm volatile("" : "+v"(den), "+v"(num));
+    };
     double* const D = reinterpret_cast<double*>(mem) + e * STRIDE;
     if (l < 5) {  // slots: gluons 0, 1, 2 (particle 4), p3, p4
         const double* p = mom + ev * 20 + 4 * (l < 2 ? l : l == 2 ? 4 : l - 1);
@@ -211,6 +240,14 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
     vec eps[3];
     each<3>([&](auto A) __attribute__((always_inline)) { eps[A] = ld4(D + EPS + 8 * A + 4 * pol[A]); });
     vec W3[2];  // middle 0: (1, 0, 2); middle 1: (0, 1, 2); without their propagator
+    vec X3[3];  // the trees that join a pair and the third gluon
+    if constexpr (MC) {
+        each<3>([&](auto K) __attribute__((always_inline)) {
+            constexpr int c = 2 - K, a = c == 0 ? 1 : 0, b = c == 2 ? 1 : 2;
+            X3[K] = vec{{0.0, 0.0, 0.0, 0.0}};
+            sub_vvv(X3[K], W[K], add(ld4(D + Q + 4 * a), ld4(D + Q + 4 * b)), eps[c], ld4(D + Q + 4 * c));
+        });
+    }
     {
         const vec q0 = ld4(D + Q), q1 = ld4(D + Q + 4), q2 = ld4(D + Q + 8), q01 = add(q0, q1);
         vec a{{0.0, 0.0, 0.0, 0.0}}, b{{0.0, 0.0, 0.0, 0.0}};
@@ -223,27 +260,39 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
         W3[1] = a;
         W3[0] = b;
     }
+    // With the weights also in registers these are read again where they are used.
+    auto pair = [&](auto K, int at) __attribute__((always_inline)) {
+        constexpr int a = K == 2, b = K == 0 ? 1 : 2;
+        return MC ? ld4(D + W2 + 16 * K + 4 * (bit(at, a) + 2 * bit(at, b))) : W[K];
+    };
     double acc = 0.0;
 #pragma unroll 1
     for (int s4 = 0; s4 < 2; ++s4) {
+        int l4 = l;
+        if constexpr (MC) asm volatile("" : "+v"(l4));
         // rows from p4: R(c), and W(b) R(c) + W(bc) v as r(c) slash(b) + r0 slash W(bc)
         const row r0 = ld8(D + N0 + 16 + 8 * s4);
         row r1[3], r2[3][2], rw[3];
         each<3>([&](auto C) __attribute__((always_inline)) {
             r1[C] = ld8(D + N1 + 96 + 32 * C + 16 * pol[C] + 8 * s4);
-            rw[C] = slash(r0, W[C]);
+            if constexpr (!MC) rw[C] = slash(r0, W[C]);
         });
         each<3>([&](auto C) __attribute__((always_inline)) {
             each<2>([&](auto H) __attribute__((always_inline)) {  // b: the H-th gluon other than C
                 constexpr int b = H < C ? H : H + 1, p = b + C - 1;
-                const row t = slash(r1[C], eps[b]);
+                const row t = slash(r1[C], MC ? ld4(D + EPS + 8 * b + 4 * bit(l4, b)) : eps[b]);
                 const double sg = b < C ? 1.0 : -1.0;
-                r2[C][H] = row{{axpy(sg, rw[p].s[0], t.s[0]), axpy(sg, rw[p].s[1], t.s[1]),
-                                axpy(sg, rw[p].s[2], t.s[2]), axpy(sg, rw[p].s[3], t.s[3])}};
+                if constexpr (MC)
+                    r2[C][H] = t;
+                else
+                    r2[C][H] = row{{axpy(sg, rw[p].s[0], t.s[0]), axpy(sg, rw[p].s[1], t.s[1]),
+                                    axpy(sg, rw[p].s[2], t.s[2]), axpy(sg, rw[p].s[3], t.s[3])}};
             });
         });
 #pragma unroll 1
         for (int s3 = 0; s3 < 2; ++s3) {
+            int l3 = l;
+            if constexpr (MC) asm volatile("" : "+v"(l3));
             const row f0 = ld8(D + N0 + 8 * s3), V = ld8(D + C0 + 8 * (s3 + 2 * s4));
             c2 J[6];
             {
@@ -252,9 +301,11 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
                 J[1] = t2, J[3] = t2;  // 021, 120
                 J[2] = t0, J[4] = t0;  // 102, 201
             }
+            if constexpr (MC) each<3>([&](auto K) __attribute__((always_inline)) { found(IDS::tree[K], cdot(V, X3[K])); });
             each<3>([&](auto C) __attribute__((always_inline)) {  // ubar W(ab) R(c)
                 constexpr int a = C == 0 ? 1 : 0, b = C == 2 ? 1 : 2, p = a + b - 1;
-                const c2 t = wedge(slash(f0, W[p]), r1[C], c2{0.0, 0.0});
+                const c2 t = wedge(slash(f0, pair(std::integral_constant<int, p>{}, l3)), r1[C], c2{0.0, 0.0});
+                if constexpr (MC) found(IDS::last[p], t);
                 constexpr int kab = 2 * a + (b > C), kba = 2 * b + (a > C);
                 J[kab] += t;
                 J[kba] -= t;
@@ -263,8 +314,22 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
                 const row f = ld8(D + N1 + 32 * A + 16 * pol[A] + 8 * s3);
                 each<2>([&](auto H) __attribute__((always_inline)) {  // c: the H-th gluon other than a
                     constexpr int c = H < A ? H : H + 1, b = 3 - A - c, k = 2 * A + (b > c);
-                    J[k] = wedge(f, r2[c][b < c ? b : b - 1], J[k]);
+                    if constexpr (MC) {
+                        const c2 t = wedge(f, r2[c][b < c ? b : b - 1], c2{0.0, 0.0});
+                        found(IDS::order[k], t);
+                        J[k] += t;
+                    } else {
+                        J[k] = wedge(f, r2[c][b < c ? b : b - 1], J[k]);
+                    }
                 });
+                if constexpr (MC) {  // and the pair of the others
+                    constexpr int p = 2 - A;
+                    const c2 t = cdot(current(f, r0), pair(std::integral_constant<int, p>{}, l3));
+                    found(IDS::first[p], t);
+                    J[2 * A] -= t;  // a row takes the vertex with the other sign
+                    J[2 * A + 1] += t;
+                    settle(J);
+                }
             });
             const double q = P::colour_blocks(J);
             acc += ((spins >> (s3 + 2 * s4)) & 1) ? q : 0.0;
@@ -272,4 +337,9 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
     }
     const double tot = group_sum(acc, 3);
     if (valid && l == 0) out[ev] = tot * (1.0 / (256.0 * P::identical * P::lcd));
+    if constexpr (MC) {
+        num = group_sum(num, 3);
+        den = group_sum(den, 3);
+        if (valid && l == 0) alpha[ev] = num / den;
+    }
 }

@@ -46,6 +46,10 @@ typedef hipError_t (*me_launch_sum_fn)(const double* mom, int64_t nevt, double* 
                                        const me_params& prm, const int* idx, const int* count, bool mfma,
                                        hipStream_t stream);
 
+// Multi-channel form with shared wavefunctions: sums over all helicities.
+typedef hipError_t (*me_launch_chan_fn)(const double* mom, int64_t nevt, double* out, const me_params& prm,
+                                        const int* chan, double* alpha, hipStream_t stream);
+
 enum { ME_KIND_EE = 0, ME_KIND_GG = 1, ME_KIND_QEW = 2 };
 
 struct me_process_desc {
@@ -64,6 +68,7 @@ struct me_process_desc {
     int nchan;                        // its channels
     const char* const* chan_desc;     // their descriptors
     me_launch_sum_fn launch_sum;      // spin sum with one event per wave (nullptr: none)
+    me_launch_chan_fn launch_chan;    // multi-channel form with shared wavefunctions (nullptr: none)
 };
 
 const me_process_desc* me_find_process(const char* name);

@@ -320,6 +320,82 @@ MEV int minus(int a, int b) { return a > b ? (int)0x80000000 : 0; }
 MEV int eps_at(int a, int pol) { return 16 * (S_EPS + 4 * a + pol); }
 MEV int q_at(int a) { return 16 * (S_Q + 2 * a); }
 
+// The blocks of one or two events (ne): lanes 0..31 the first, 32..63 the second
+// (or the first again).
+MEV void gg4_setup(double2* T, const double* __restrict__ mom, int64_t base, int ne, const int* __restrict__ idx,
+                   const int* __restrict__ count, const me_params& prm, int lane) {
+    constexpr int NP = 6;
+    const double m = prm.mt;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));  // addresses are formed here, not kept across the events
+    const int j = ln >> 5, hl = ln & 31;
+    const int64_t i = base + (j < ne ? j : 0);
+    const int64_t ev = count ? (int64_t)idx[i] : i;
+    const int B = 16 * (j ? (int)S_B : 0);  // this event's block
+    // momenta: lane (slot, component); slots the gluons in incoming flow, p3, p4
+    if (hl < 24) {
+        const int slot = hl >> 2, part = slot < 2 ? slot : slot < 4 ? slot + 2 : slot - 2;
+        const double v = mom[ev * (NP * 4) + 4 * part + (hl & 3)];
+        const double q = (slot == 2 || slot == 3) ? -v : v;
+        reinterpret_cast<double*>(T + S_P + 12 * j)[hl] = q;
+        if (slot < 4) reinterpret_cast<double*>(lds_at(T, B + 16 * S_Q))[hl] = q;
+    }
+    __syncthreads();
+    // summed momenta and propagators
+    if (hl < 25) {
+        const unsigned c = k_of(hl);
+        vec K{{0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int s = 0; s < 6; ++s) {
+            const double w = (double)((int)((c >> 2 * s) & 1) - (int)((c >> (2 * s + 1)) & 1));
+            const vec q = ld_vec(T, 16 * (S_P + 12 * j + 2 * s), 1);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) K.v[k] = fma(w, q.v[k], K.v[k]);
+        }
+        const bool top = hl >= 10 && hl < 24;
+        const double d = K.v[0] * K.v[0] - K.v[1] * K.v[1] - K.v[2] * K.v[2] - K.v[3] * K.v[3];
+        const c2 f = crecip(top ? d - m * m : d, top ? m * prm.wt : 0.0);
+        if (top) st_vec(T, B + 16 * (S_K + 2 * (hl - 10)), 1, K);
+        *lds_at(T, B + 16 * (S_F + hl)) = double2{f.r, f.i};
+    }
+    // polarisation vectors: lane (gluon, pol)
+    if (hl < 8) {
+        const int a = hl >> 1;
+        const vec q = ld_vec(T, B + q_at(a), 1);
+        st_vec(T, B + 16 * (S_EPS + 4 * a + (hl & 1)), 2,
+               mul(prm.gs, polarisation(a < 2 ? q : mul(-1.0, q), hl & 1)));
+    }
+    // end rows: lane (end, spin)
+    if (hl < 4) {
+        const int e = hl >> 1;
+        const row f = end_row(ld_vec(T, 16 * (S_P + 12 * j + 2 * (4 + e)), 1), m, e, (hl & 1) ? 1 : -1);
+        st_row(T, B + 16 * (S_N0 + 8 * e + (hl & 1)), 2, f);
+    }
+    __syncthreads();
+    // pair currents: lane (pair, pols); the other lanes: current of the ends (spins)
+    if (hl < 24) {
+        const int p = hl >> 2, a = pair_lo(p), b = pair_hi(p);
+        vec w{{0.0, 0.0, 0.0, 0.0}};
+        sub_vvv(w, ld_vec(T, B + eps_at(a, bit(hl, 0)), 2), ld_vec(T, B + q_at(a), 1),
+                ld_vec(T, B + eps_at(b, bit(hl, 1)), 2), ld_vec(T, B + q_at(b), 1));
+        st_vec(T, B + 16 * (S_W2 + 8 * p + (hl & 3)), 4, mul(lds_at(T, B + 16 * (S_F + p))->x, w));
+    } else if (hl < 28) {
+        const double iq = lds_at(T, B + 16 * (S_F + 24))->x;
+        const row V = current(ld_row(T, B + 16 * (S_N0 + bit(hl, 0)), 2),
+                              ld_row(T, B + 16 * (S_N0 + 8 + bit(hl, 1)), 2));
+        st_row(T, B + 16 * (S_C0 + (hl & 3)), 4, scale(c2{iq, 0.0}, V));
+    }
+    // one-gluon rows: lane (end, gluon, pol, spin)
+    {
+        const int e = hl >> 4, a = (hl >> 2) & 3, k = 10 * e + a;
+        const row f = slash_m(slash(ld_row(T, B + 16 * (S_N0 + 8 * e + bit(hl, 1)), 2),
+                                    ld_vec(T, B + eps_at(a, bit(hl, 0)), 2)),
+                              ld_vec(T, B + 16 * (S_K + 2 * k), 1), m);
+        const double2 d = *lds_at(T, B + 16 * (S_F + 10 + k));
+        st_row(T, B + 16 * (S_N1 + 16 * (4 * e + a) + (hl & 3)), 4, scale(e ? c2{d.x, d.y} : c2{-d.x, -d.y}, f));
+    }
+}
+
 }  // namespace wv
 
 // idx, count as for k_me_gg.  spins: bit s3 + 2 s4 set for the spin pairs of t
@@ -333,7 +409,6 @@ __global__ __launch_bounds__(64, CM ? 1 : 2) void k_me_gg4_wave(const double* __
                                                                const int* __restrict__ count, int eb) {
     using namespace wv;
     static_assert(P::ngluon == 4 && P::ncol == 24, "four gluons");
-    constexpr int NP = 6;
     __shared__ double2 T[S_END];
     const int lane = threadIdx.x;
     const int64_t n = count ? (int64_t)*count : nevt;
@@ -424,77 +499,7 @@ __global__ __launch_bounds__(64, CM ? 1 : 2) void k_me_gg4_wave(const double* __
     for (int64_t base = (int64_t)blockIdx.x * eb; base < n; base += (int64_t)gridDim.x * eb) {
         const int ne = (eb == 2 && base + 1 < n) ? 2 : 1;
         __syncthreads();  // the previous event's reads are done
-        // ---- both events: lanes 0..31 the first, 32..63 the second (or the first again) ----
-        {
-            int ln = lane;
-            asm volatile("" : "+v"(ln));  // addresses are formed here, not kept across the events
-            const int j = ln >> 5, hl = ln & 31;
-            const int64_t i = base + (j < ne ? j : 0);
-            const int64_t ev = count ? (int64_t)idx[i] : i;
-            const int B = 16 * (j ? (int)S_B : 0);  // this event's block
-            // momenta: lane (slot, component); slots the gluons in incoming flow, p3, p4
-            if (hl < 24) {
-                const int slot = hl >> 2, part = slot < 2 ? slot : slot < 4 ? slot + 2 : slot - 2;
-                const double v = mom[ev * (NP * 4) + 4 * part + (hl & 3)];
-                const double q = (slot == 2 || slot == 3) ? -v : v;
-                reinterpret_cast<double*>(T + S_P + 12 * j)[hl] = q;
-                if (slot < 4) reinterpret_cast<double*>(lds_at(T, B + 16 * S_Q))[hl] = q;
-            }
-            __syncthreads();
-            // summed momenta and propagators
-            if (hl < 25) {
-                const unsigned c = k_of(hl);
-                vec K{{0.0, 0.0, 0.0, 0.0}};
-#pragma unroll
-                for (int s = 0; s < 6; ++s) {
-                    const double w = (double)((int)((c >> 2 * s) & 1) - (int)((c >> (2 * s + 1)) & 1));
-                    const vec q = ld_vec(T, 16 * (S_P + 12 * j + 2 * s), 1);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) K.v[k] = fma(w, q.v[k], K.v[k]);
-                }
-                const bool top = hl >= 10 && hl < 24;
-                const double d = K.v[0] * K.v[0] - K.v[1] * K.v[1] - K.v[2] * K.v[2] - K.v[3] * K.v[3];
-                const c2 f = crecip(top ? d - m * m : d, top ? m * prm.wt : 0.0);
-                if (top) st_vec(T, B + 16 * (S_K + 2 * (hl - 10)), 1, K);
-                *lds_at(T, B + 16 * (S_F + hl)) = double2{f.r, f.i};
-            }
-            // polarisation vectors: lane (gluon, pol)
-            if (hl < 8) {
-                const int a = hl >> 1;
-                const vec q = ld_vec(T, B + q_at(a), 1);
-                st_vec(T, B + 16 * (S_EPS + 4 * a + (hl & 1)), 2,
-                       mul(prm.gs, polarisation(a < 2 ? q : mul(-1.0, q), hl & 1)));
-            }
-            // end rows: lane (end, spin)
-            if (hl < 4) {
-                const int e = hl >> 1;
-                const row f = end_row(ld_vec(T, 16 * (S_P + 12 * j + 2 * (4 + e)), 1), m, e, (hl & 1) ? 1 : -1);
-                st_row(T, B + 16 * (S_N0 + 8 * e + (hl & 1)), 2, f);
-            }
-            __syncthreads();
-            // pair currents: lane (pair, pols); the other lanes: current of the ends (spins)
-            if (hl < 24) {
-                const int p = hl >> 2, a = pair_lo(p), b = pair_hi(p);
-                vec w{{0.0, 0.0, 0.0, 0.0}};
-                sub_vvv(w, ld_vec(T, B + eps_at(a, bit(hl, 0)), 2), ld_vec(T, B + q_at(a), 1),
-                        ld_vec(T, B + eps_at(b, bit(hl, 1)), 2), ld_vec(T, B + q_at(b), 1));
-                st_vec(T, B + 16 * (S_W2 + 8 * p + (hl & 3)), 4, mul(lds_at(T, B + 16 * (S_F + p))->x, w));
-            } else if (hl < 28) {
-                const double iq = lds_at(T, B + 16 * (S_F + 24))->x;
-                const row V = current(ld_row(T, B + 16 * (S_N0 + bit(hl, 0)), 2),
-                                      ld_row(T, B + 16 * (S_N0 + 8 + bit(hl, 1)), 2));
-                st_row(T, B + 16 * (S_C0 + (hl & 3)), 4, scale(c2{iq, 0.0}, V));
-            }
-            // one-gluon rows: lane (end, gluon, pol, spin)
-            {
-                const int e = hl >> 4, a = (hl >> 2) & 3, k = 10 * e + a;
-                const row f = slash_m(slash(ld_row(T, B + 16 * (S_N0 + 8 * e + bit(hl, 1)), 2),
-                                            ld_vec(T, B + eps_at(a, bit(hl, 0)), 2)),
-                                      ld_vec(T, B + 16 * (S_K + 2 * k), 1), m);
-                const double2 d = *lds_at(T, B + 16 * (S_F + 10 + k));
-                st_row(T, B + 16 * (S_N1 + 16 * (4 * e + a) + (hl & 3)), 4, scale(e ? c2{d.x, d.y} : c2{-d.x, -d.y}, f));
-            }
-        }
+        gg4_setup(T, mom, base, ne, idx, count, prm, lane);
 #pragma unroll 1
         for (int j = 0; j < ne; ++j) {
             int ln = lane;

@@ -602,6 +602,61 @@ class GGEmitter:
         found.sort(key=lambda t: t[1])
         return {i: k for k, (i, _) in enumerate(found)}, [d for _, d in found]
 
+    def emit_channel_ids(self, descs):
+        """struct chan_ids_{name}: the channel of each diagram, in the order in
+        which the kernels of me_chan.h form them."""
+        pos = {d: i for i, d in enumerate(descs)}
+        pairs = list(itertools.combinations(range(self.n), 2))
+
+        def t(*parts):  # the tree joining the parts, each (text, smallest gluon)
+            parts = sorted(parts, key=lambda x: x[1])
+            return "(" + ",".join(x[0] for x in parts) + ")", parts[0][1]
+
+        def g(a):
+            return str(a), a
+
+        def line(*blocks):
+            return pos["|".join(b[0] for b in blocks)]
+
+        def others(*used):
+            return [a for a in range(self.n) if a not in used]
+
+        tab = {}
+        if self.n == 2:
+            tab["order"] = [line(g(0), g(1)), line(g(1), g(0))]  # 0|1, 1|0
+            tab["tree"] = [line(t(g(0), g(1)))]
+        elif self.n == 3:
+            rest = [others(*p)[0] for p in pairs]
+            tab["order"] = [line(*map(g, o)) for o in itertools.permutations(range(3))]
+            tab["tree"] = [line(t(t(g(p[0]), g(p[1])), g(r))) for p, r in zip(pairs, rest)]   # by pair
+            tab["first"] = [line(g(r), t(g(p[0]), g(p[1]))) for p, r in zip(pairs, rest)]     # rest|pair
+            tab["last"] = [line(t(g(p[0]), g(p[1])), g(r)) for p, r in zip(pairs, rest)]      # pair|rest
+        else:
+            def kinds(p):  # lo|hi, hi|lo, (lo,hi)
+                a, b = g(p[0]), g(p[1])
+                return [[a, b], [b, a], [t(a, b)]]
+
+            def triple(mg, k):  # the k-th of the three gluons other than mg joins last
+                o = others(mg)
+                c = o.pop(k)
+                return t(t(g(o[0]), g(o[1])), g(c))
+
+            # split [pair][left kind][right kind]; middle [pair of the outer two][hi first]
+            tab["split"] = [line(*x, *y) for p in pairs for x in kinds(p) for y in kinds(others(*p))]
+            tab["middle"] = [line(g(a), t(*map(g, others(*p))), g(d)) for p in pairs for a, d in (p, p[::-1])]
+            # three [end][gluon][k]: 0 gluon|tree, 1 tree|gluon
+            tab["three"] = [line(*(b if e == 0 else b[::-1])) for e in range(2) for mg in range(4) for k in range(3)
+                            for b in [[g(mg), triple(mg, k)]]]
+            # four [gluon that joins last][k], then the pairs (0, b) with the other two
+            tab["four"] = [line(t(triple(mg, k), g(mg))) for mg in range(4) for k in range(3)] + [
+                line(t(t(*map(g, p)), t(*map(g, others(*p))))) for p in pairs[:3]]
+        assert sorted(x for v in tab.values() for x in v) == list(range(len(descs)))
+        h = [f"// the channel of each diagram, in the order of the kernels of me_chan.h", f"struct chan_ids_{self.name} {{"]
+        for k, v in tab.items():
+            h.append(f"    static constexpr unsigned char {k}[{len(v)}] = {{{', '.join(map(str, v))}}};")
+        h.append("};")
+        return h
+
     def render_mc(self) -> str:
         """Header of the multi-channel program: the unmerged plan (one amplitude
         per Feynman diagram and four-gluon colour channel) accumulating, besides
@@ -648,6 +703,8 @@ class GGEmitter:
         h.extend(self.emit_colour())
         h.append("    }")
         h.append("};")
+        h.append("")
+        h.extend(self.emit_channel_ids(descs))
         h.append("")
         h.append(f"// channel descriptors (host side), channel order")
         h.append(f"static const char* const channel_desc_{self.name}[{len(descs)}] = {{")

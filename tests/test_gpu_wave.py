@@ -87,3 +87,42 @@ def test_five_gluons_are_deterministic(env):
     t = torch.from_numpy(process_points("gg_ttggg", 700, 64)).cuda()
     assert torch.equal(m.eval(t), m.eval(t))
     m.close()
+
+
+@pytest.mark.parametrize("proc,n", [("gg_tt", 1), ("gg_tt", 65), ("gg_ttg", 1), ("gg_ttg", 9), ("gg_ttgg", 1),
+                                    ("gg_ttgg", 2), ("gg_ttgg", 4097), ("gg_ttgg", 16387)])
+def test_channel_weights_at_the_edges_of_the_grid(env, proc, n):
+    """Every event in another channel; nothing written past the end.  Weights
+    to 1e-10 relative, as ratios of sums of squares of the amplitudes."""
+    torch, me = env
+    print(f"[wave] channels {proc} n={n}", flush=True)
+    mom = process_points(proc, n, 62)
+    m = me.MatrixElement(proc)
+    descs = m.channels()
+    chan = np.random.default_rng(62).integers(0, len(descs), n).astype(np.int32)
+    me2, alpha = (torch.full((n + 64,), -7.0, dtype=torch.float64, device="cuda") for _ in range(2))
+    me.me_eval_multichannel(m.ctx, torch.from_numpy(mom).cuda(), torch.from_numpy(chan).cuda(), n, me2, alpha)
+    torch.cuda.synchronize()
+    me2, alpha = me2.cpu().numpy(), alpha.cpu().numpy()
+    assert np.all(me2[n:] == -7.0) and np.all(alpha[n:] == -7.0)
+    sel = np.unique(np.r_[np.arange(min(n, 40)), np.arange(max(0, n - 40), n)])
+    odescs, sums = oracle.diagram_sums(proc, mom[sel])
+    col = np.array([odescs.index(d) for d in descs])
+    want = (sums / sums.sum(axis=1, keepdims=True))[np.arange(len(sel)), col[chan[sel]]]
+    assert np.all(np.abs(alpha[sel] / want - 1) <= 1e-10)
+    close(me2[sel], oracle.me2(proc, mom[sel]))
+    m.close()
+
+
+def test_channel_weights_with_helicities_dropped(env):
+    """A massless top: the filter drops helicities whose |M|^2 vanishes though
+    single diagrams do not; the weights are those over the kept ones and add up to 1."""
+    torch, me = env
+    m = me.MatrixElement("gg_ttg", masses=(91.188, 2.4414, 0.0, 0.0))
+    assert len(m.good_helicities()) < 32
+    mom = torch.from_numpy(rambo(300, 1500.0, [0.0] * 3, 63)).cuda()
+    total = 0
+    for c in range(len(m.channels())):
+        total = total + m.eval_multichannel(mom, torch.full((300,), c, dtype=torch.int32, device="cuda"))[1]
+    np.testing.assert_allclose(total.cpu().numpy(), 1.0, rtol=1e-12)
+    m.close()
