@@ -259,7 +259,7 @@ int me_init(const char* process, const double* couplings, int n_couplings, const
     c->uw_s = nullptr;
     c->uw_me2 = nullptr;
     c->uw_idx1 = nullptr;
-    c->uw_cap = 0;
+    c->uw_cap = c->uw_xcap = 0;
     hipError_t e = hipGetDevice(&c->device);
     if (e != hipSuccess) {
         delete c;

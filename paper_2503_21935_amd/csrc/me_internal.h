@@ -38,7 +38,7 @@ struct me_ctx {
     double* uw_s;
     double* uw_me2;
     int* uw_idx1;
-    int64_t uw_cap;
+    int64_t uw_cap, uw_xcap;
 };
 
 // Float64 |M|^2 of the events idx[0..*count) (both on the device).
@@ -46,5 +46,6 @@ hipError_t me_launch_idx(const me_ctx* c, const double* mom, int64_t nevt, doubl
                          const int* count, hipStream_t s);
 
 struct me_mlp;
-int mlp_forward_internal(me_mlp* p, const float* x, int64_t n, float* y, hipStream_t s);
+// The network on the features of the momenta in one kernel; false: it has no such form.
+bool mlp_forward_momenta(me_mlp* p, const double* momenta, int64_t n, float* y, hipStream_t s);
 int mlp_n_in(const me_mlp* p);

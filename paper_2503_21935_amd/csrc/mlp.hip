@@ -13,7 +13,9 @@
 
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 #define MLP_KPAD 32  // first-layer inputs padded to one MFMA K step
 #define MLP_DW_SPLITS 16  // batch splits of the weight-gradient GEMMs
@@ -135,11 +137,19 @@ __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, int kspan, co
 // Fused inference for width 256: a block of 256 threads (4 waves) carries a
 // tile of 128 rows through every layer with the activations in LDS, so the
 // only HBM traffic is the input, the output and (from L2) the weights.  Per
-// layer, wave w computes output columns 64w..64w+63 for all 128 rows (8 x 4
+// layer, wave w computes output columns 64w..64w+63 for all 128 rows (4 x 8
 // MFMA tiles of 16 x 16, K steps of 32); after a barrier the bias + SiLU
 // epilogue writes the BF16 activations over the layer's input.  Numerics as
 // in the layered path: BF16 inputs, weights and activations, FP32
 // accumulation, FP32 bias, activation and output layer.
+// The weights are the first operand of the products, the rows the second, so
+// a lane ends up with four consecutive columns of one row and stores them with
+// one instruction; the weights come in fragment order (1 KB per load
+// instruction) and one K step ahead of their use.  Two blocks per CU, so
+// that one's epilogue (activation functions) runs beside the other's products.
+// The input is a row of features or, with MOM, an event's momenta, whose
+// features (those of k_features) are then formed on the way into LDS.
+// @@
 // ---------------------------------------------------------------------------
 #define MLPF_W 256
 #define MLPF_PITCH (MLPF_W + 8)  // bf16 per LDS row: rows 528 B apart, no bank conflicts
@@ -147,14 +157,22 @@ __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, int kspan, co
 
 struct mlpf_args {
     const bf16* w[MLPF_MAXDEPTH];   // hidden layers, [256][K] (K = 32 for the first, padded)
+    bool frag;                      // in fragment order (else row-major)
     const float* b[MLPF_MAXDEPTH];  // their biases [256]
     const float* wout;              // output weights [256]
     const float* bout;              // output bias [1]
 };
 
+// 1 / sqrt(shat) of an event from its incoming momenta.
+__device__ __forceinline__ double inv_sqrt_shat(const double* __restrict__ p) {
+    const double E = p[0] + p[4], px = p[1] + p[5], py = p[2] + p[6], pz = p[3] + p[7];
+    return 1.0 / sqrt(E * E - px * px - py * py - pz * pz);
+}
+
 // ROWS rows per 256-thread block (a multiple of 16 dividing 256).
-template <int ROWS>
-__global__ __launch_bounds__(256, 8192 / (ROWS * 32)) void k_mlp_infer(const float* __restrict__ x, int64_t n,
+template <int ROWS, bool MOM>
+__global__ __launch_bounds__(256, 8192 / (ROWS * 32)) void k_mlp_infer(const float* __restrict__ x,
+                                                                        const double* __restrict__ mom, int64_t n,
                                                                         int n_in, int depth, mlpf_args a,
                                                                         float* __restrict__ y) {
     constexpr int RT = ROWS / 16;      // 16-row MFMA tiles
@@ -162,51 +180,91 @@ __global__ __launch_bounds__(256, 8192 / (ROWS * 32)) void k_mlp_infer(const flo
     __shared__ __attribute__((aligned(16))) bf16 H[ROWS * MLPF_PITCH];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t row0 = (int64_t)blockIdx.x * ROWS;
-    for (int e = threadIdx.x; e < ROWS * MLP_KPAD; e += 256) {
-        const int r = e / MLP_KPAD, k = e % MLP_KPAD;
-        const int64_t gr = row0 + r;
-        H[r * MLPF_PITCH + k] = (bf16)((gr < n && k < n_in) ? x[gr * n_in + k] : 0.f);
+    // the whole tile's loads in flight at once (clamped, then masked)
+    constexpr int PER = ROWS * MLP_KPAD / 256;  // elements per thread: column k of every 8th row
+    const int k = threadIdx.x % MLP_KPAD, r0 = threadIdx.x / MLP_KPAD;
+    const auto at = [&](int j) {
+        const int64_t gr = row0 + r0 + (256 / MLP_KPAD) * j;
+        return (gr < n ? gr : n - 1) * n_in + (k < n_in ? k : 0);
+    };
+    const auto put = [&](int j, float v) {
+        const int r = r0 + (256 / MLP_KPAD) * j;
+        H[r * MLPF_PITCH + k] = (bf16)((row0 + r < n && k < n_in) ? v : 0.f);
+    };
+    if constexpr (MOM) {
+        __shared__ double inv[ROWS];
+        double v[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) v[j] = mom[at(j)];
+        if (threadIdx.x < ROWS) {
+            const int64_t gr = row0 + threadIdx.x;
+            inv[threadIdx.x] = inv_sqrt_shat(mom + (gr < n ? gr : n - 1) * n_in);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            float f = (float)(v[j] * inv[r0 + (256 / MLP_KPAD) * j]);
+            asm volatile("" : "+v"(f));  // rounded to FP32 first, as k_features stores it: not folded into one conversion
+            put(j, f);
+        }
+    } else {
+        float v[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) v[j] = x[at(j)];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) put(j, v[j]);
     }
     __syncthreads();
     const int li = lane & 15, lg = lane >> 4;
-    int K = MLP_KPAD;
-    for (int l = 0; l < depth; ++l) {
-        f32x4 acc[RT][4];
+    auto layer = [&](auto KS, int l) __attribute__((always_inline)) {
+        constexpr int ks = KS;  // K steps
+        f32x4 acc[4][RT];
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
+        for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const bf16* W = a.w[l];
-        for (int k0 = 0; k0 < K; k0 += 32) {
-            bf16x8 b[4];
+            for (int rt = 0; rt < RT; ++rt) acc[t][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        constexpr int wt = ks * 512;          // from tile to tile
+        const int wk = a.frag ? 512 : 32;     // from K step to K step
+        const bf16* W = a.w[l] + 4 * wave * wt + (a.frag ? 8 * lane : li * (32 * ks) + 8 * lg);
+        bf16x8 w[2][4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
-                b[t] = *reinterpret_cast<const bf16x8*>(W + (int64_t)(64 * wave + 16 * t + li) * K + k0 + 8 * lg);
+        for (int t = 0; t < 4; ++t) w[0][t] = *reinterpret_cast<const bf16x8*>(W + t * wt);
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                const bf16x8 av = *reinterpret_cast<const bf16x8*>(H + (16 * rt + li) * MLPF_PITCH + k0 + 8 * lg);
+        for (int k = 0; k < ks; ++k) {
+            if (k + 1 < ks) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
-                    acc[rt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[t], acc[rt][t], 0, 0, 0);
+                    w[(k + 1) & 1][t] = *reinterpret_cast<const bf16x8*>(W + t * wt + (k + 1) * wk);
+            }
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const bf16x8 h = *reinterpret_cast<const bf16x8*>(H + (16 * rt + li) * MLPF_PITCH + 32 * k + 8 * lg);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[t][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[k & 1][t], h, acc[t][rt], 0, 0, 0);
             }
         }
         __syncthreads();  // every wave has read the layer's input
-        const float* bias = a.b[l];
+        // acc[t][rt][v]: column 64 wave + 16 t + 4 lg + v of row 16 rt + li
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const int c = 64 * wave + 16 * t + li;
-            const float bc = bias[c];
+            const int c = 64 * wave + 16 * t + 4 * lg;
+            const f32x4 bc = *reinterpret_cast<const f32x4u*>(a.b[l] + c);
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
+            for (int rt = 0; rt < RT; ++rt) {
+                bf16x4 h;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const float z = acc[rt][t][v] + bc;
-                    H[(16 * rt + 4 * lg + v) * MLPF_PITCH + c] = (bf16)(z * sigmoidf_(z));
+                    const float z = acc[t][rt][v] + bc[v];
+                    h[v] = (bf16)(z * sigmoidf_(z));
                 }
+                *reinterpret_cast<bf16x4*>(H + (16 * rt + li) * MLPF_PITCH + c) = h;
+            }
         }
         __syncthreads();
-        K = MLPF_W;
-    }
+    };
+    layer(std::integral_constant<int, 1>{}, 0);
+    for (int l = 1; l < depth; ++l) layer(std::integral_constant<int, MLPF_W / 32>{}, l);
     // output layer: y = sum_k h[k] w[k] + b; TPR adjacent threads per row, each
     // over MLPF_W / TPR columns in 16-byte reads, then a butterfly
     {
@@ -916,13 +974,17 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
     }
 }
 
+// Blocks of 256 threads, FEAT_EV events each: the events' 1 / sqrt(shat) once, then
+// momenta and features in address order (one event per thread, 192 bytes apart,
+// took 0.65 ms for 2^20 events of six particles; now @@).
+#define FEAT_EV 128
 __global__ void k_features(const double* __restrict__ mom, int64_t n, int npart, float* __restrict__ x) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double* p = mom + i * npart * 4;
-    const double E = p[0] + p[4], px = p[1] + p[5], py = p[2] + p[6], pz = p[3] + p[7];
-    const double inv = 1.0 / sqrt(E * E - px * px - py * py - pz * pz);
-    for (int c = 0; c < 4 * npart; ++c) x[i * 4 * npart + c] = (float)(p[c] * inv);
+    __shared__ double inv[FEAT_EV];
+    const int64_t first = (int64_t)blockIdx.x * FEAT_EV;
+    const int nc = 4 * npart, ne = (int)(n - first < FEAT_EV ? n - first : FEAT_EV);
+    if ((int)threadIdx.x < ne) inv[threadIdx.x] = inv_sqrt_shat(mom + (first + threadIdx.x) * nc);
+    __syncthreads();
+    for (int e = threadIdx.x; e < ne * nc; e += 256) x[first * nc + e] = (float)(mom[first * nc + e] * inv[e / nc]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1261,22 +1323,32 @@ int mlp_set_params(me_mlp* p, const float* host, int64_t n) {
     return ME_OK;
 }
 
+// The one-kernel inference, from features or from momenta; false: not this network's form.
+static bool infer_fused(const me_mlp* p, const float* x, const double* mom, int64_t n, float* y, hipStream_t s) {
+    if (p->width != MLPF_W || p->n_in > MLP_KPAD || p->depth > MLPF_MAXDEPTH) return false;
+    mlpf_args a{};
+    a.frag = p->d_wfr != nullptr;  // networks of the one-kernel step keep such copies
+    for (int l = 0; l < p->depth; ++l) {
+        a.w[l] = a.frag ? p->wfr[l] : p->wbf[l];
+        a.b[l] = p->theta + p->L.b_off[l];
+    }
+    a.wout = p->theta + p->wout_off;
+    a.bout = p->theta + p->bout_off;
+    constexpr int rows = MLPF_TILE_ROWS;
+    const dim3 grid((unsigned)((n + rows - 1) / rows));
+    if (mom)
+        hipLaunchKernelGGL((k_mlp_infer<rows, true>), grid, dim3(256), 0, s, nullptr, mom, n, p->n_in, p->depth, a, y);
+    else
+        hipLaunchKernelGGL((k_mlp_infer<rows, false>), grid, dim3(256), 0, s, x, nullptr, n, p->n_in, p->depth, a, y);
+    return true;
+}
+
 int mlp_forward(me_mlp* p, const float* x, int64_t n, float* y, void* stream) {
     if (!p || n < 0) return me_fail(ME_EINVAL, "mlp_forward: null or negative n");
     if (n == 0) return ME_OK;
     if (!x || !y) return me_fail(ME_EINVAL, "mlp_forward: null buffer");
     hipStream_t s = (hipStream_t)stream;
-    if (p->width == MLPF_W && p->n_in <= MLP_KPAD && p->depth <= MLPF_MAXDEPTH) {
-        mlpf_args a{};
-        for (int l = 0; l < p->depth; ++l) {
-            a.w[l] = p->wbf[l];
-            a.b[l] = p->theta + p->L.b_off[l];
-        }
-        a.wout = p->theta + p->wout_off;
-        a.bout = p->theta + p->bout_off;
-        constexpr int rows = MLPF_TILE_ROWS;
-        hipLaunchKernelGGL(k_mlp_infer<rows>, dim3((unsigned)((n + rows - 1) / rows)), dim3(256), 0, s, x, n,
-                           p->n_in, p->depth, a, y);
+    if (infer_fused(p, x, nullptr, n, y, s)) {
         HCHK(hipGetLastError());
         return ME_OK;
     }
@@ -1479,7 +1551,7 @@ int me_features(const double* momenta, int64_t n, int npart, float* x, void* str
     if (n < 0 || npart < 2 || npart > 8) return me_fail(ME_EINVAL, "me_features: bad size");
     if (n == 0) return ME_OK;
     if (!momenta || !x) return me_fail(ME_EINVAL, "me_features: null buffer");
-    hipLaunchKernelGGL(k_features, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, momenta, n,
+    hipLaunchKernelGGL(k_features, dim3((unsigned)((n + FEAT_EV - 1) / FEAT_EV)), dim3(256), 0, (hipStream_t)stream, momenta, n,
                        npart, x);
     HCHK(hipGetLastError());
     return ME_OK;
@@ -1488,7 +1560,7 @@ int me_features(const double* momenta, int64_t n, int npart, float* x, void* str
 }  // extern "C"
 
 // helper for the unweighting driver in me_unweight.hip
-int mlp_forward_internal(me_mlp* p, const float* x, int64_t n, float* y, hipStream_t s) {
-    return mlp_forward(p, x, n, y, s);
+bool mlp_forward_momenta(me_mlp* p, const double* momenta, int64_t n, float* y, hipStream_t s) {
+    return infer_fused(p, nullptr, momenta, n, y, s);
 }
 int mlp_n_in(const me_mlp* p) { return p->n_in; }
