@@ -489,8 +489,17 @@ __global__ void k_to_bf16_t(const float* __restrict__ theta, int64_t o, int rows
 // per block, each wave over a quarter of the batch; the quarters are added in
 // LDS in a fixed order (the result does not depend on the grid) and the block
 // applies Adam to the tile's FP32 masters and refreshes their BF16 copies, so
-// every parameter is updated by the block that formed its gradient.  Rounding
-// points are those of the layered path.
+// every parameter is updated by the block that formed its gradient; where no
+// block has two tiles the masters and moments stay in its registers from step
+// to step.  Rounding points are those of the layered path.
+// A step of 4096 rows at depth 4 takes 47 us (68 before): 20 in phase 1, of
+// which 1 us per product is one CU's share of the weights through its L1, 15 in
+// phase 2 (half a megabyte of operands per block), the rest the two barriers and
+// the first reads behind each, which come from memory.  What the 21 us were: the
+// loss added in one chain of dependent loads by a block with an item of its own
+// (20), 256 LDS reads for 16 partial losses (2), operands left dirty for the
+// barrier to write back (3), moments read and written in every step (2); less
+// what two activation buffers and derivatives kept in registers gave.
 // ---------------------------------------------------------------------------
 #define FT_R 16        // rows per phase-1 tile
 #define FT_S 4         // batch quarters of the weight-gradient sums, one per wave
@@ -568,8 +577,9 @@ __device__ __forceinline__ const bf16* ft_chain_w(const bf16* const* wfr, const 
 // arrives on bar[0] and waits for the generation in bar[32] to move; the last
 // block to arrive resets the count and moves the generation.  One release
 // and one acquire per block, where a fence in every wave would write the L2
-// back once per wave.
-__device__ __forceinline__ void ft_grid_sync(unsigned* bar) {
+// back once per wave.  Wave 1 does `meanwhile` during the wait.
+template <class F>
+__device__ __forceinline__ void ft_grid_sync(unsigned* bar, F&& meanwhile) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -584,8 +594,21 @@ __device__ __forceinline__ void ft_grid_sync(unsigned* bar) {
                 __builtin_amdgcn_s_sleep(1);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    } else if ((threadIdx.x >> 6) == 1) {
+        meanwhile();
     }
     __syncthreads();
+}
+
+// Four batch rows of a feature, batch tile m0, to the [feature][batch] array dst in fragment order with K = M.  Written through
+// to memory as it is produced (17 MB per step in all): left dirty in the L2,
+// it is written back at the grid barrier, where every block waits for it.
+// Feature 16 f + li (f the same in the whole wave), rows 4 lg .. 4 lg + 3.
+__device__ __forceinline__ void ft_store4(bf16x4 h, int f, int li, int lg, bf16* dst, int64_t M, int64_t m0) {
+    const int b = (int)(m0 & 31) + 4 * lg;
+    bf16* at = dst + ((int64_t)f * (M >> 5) + (m0 >> 5)) * 512 + (128 * (b >> 3) + li * 8 + (b & 7));
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(at), __builtin_bit_cast(unsigned long long, h),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Column c of the 16-row LDS tile S (batch rows m0 .. m0 + 15) to the
@@ -603,17 +626,11 @@ __device__ __forceinline__ void ft_store_t(const bf16* S, int c, bf16* dst, int6
     *reinterpret_cast<bf16x8*>(dst + base + 128 * (q + 1)) = v1;
 }
 
-// Adam on parameter i (FP32 master, moments) with gradient g and the loaded
-// old values; returns the new master value.
-__device__ __forceinline__ float ft_adam(const ft_args& a, int64_t i, float g, float mo, float vo, float th, float lr,
-                                         float c1, float c2) {
-    const float mi = 0.9f * mo + 0.1f * g;
-    const float vi = 0.999f * vo + 0.001f * g * g;
-    a.m[i] = mi;
-    a.v[i] = vi;
-    const float t2 = th - lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
-    a.theta[i] = t2;
-    return t2;
+// Adam on a parameter (FP32 master, moments) with gradient g.
+__device__ __forceinline__ void ft_adam(float g, float& m, float& v, float& th, float lr, float c1, float c2) {
+    m = 0.9f * m + 0.1f * g;
+    v = 0.999f * v + 0.001f * g * g;
+    th = th - lr * (m / c1) / (sqrtf(v / c2) + 1e-8f);
 }
 
 // The update of a parameter without BF16 copies (biases, output layer), or
@@ -623,7 +640,11 @@ __device__ __forceinline__ void ft_update(const ft_args& a, int64_t i, float g, 
         a.grad_out[i] = g;
         return;
     }
-    ft_adam(a, i, g, a.m[i], a.v[i], a.theta[i], lr, c1, c2);
+    float m = a.m[i], v = a.v[i], th = a.theta[i];
+    ft_adam(g, m, v, th, lr, c1, c2);
+    a.m[i] = m;
+    a.v[i] = v;
+    a.theta[i] = th;
 }
 
 // The 16 input rows (padded to MLP_KPAD features) and targets of the tile at
@@ -660,15 +681,15 @@ __device__ __forceinline__ void ft_rows_store(const ft_rows& g, int tid, bf16* H
 __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
     constexpr int W = MLPF_W, P = MLPF_PITCH;
     static_assert(FT_R == 16 && W == 256, "one 16-row MFMA tile per phase-1 step, one thread per feature");
-    __shared__ __attribute__((aligned(16))) bf16 Hs[FT_R * P];   // layer input / output
-    __shared__ __attribute__((aligned(16))) bf16 Gs[FT_R * P];   // pre-activation gradient
-    __shared__ float Zs[FT_MAXDEPTH][FT_R][W];                  // pre-activations
+    // layer input and output, pre-activation gradients: two each, so that a layer
+    // needs one barrier (the first Hs is the tile's input)
+    __shared__ __attribute__((aligned(16))) bf16 Hs[2][FT_R * P], Gs[2][FT_R * P];
+    __shared__ float part[4096 + 128];                          // phase 2: [wave][32][32] partial tiles, [wave][32] of the biases
     __shared__ float bs[FT_MAXDEPTH][W];                        // hidden biases of this step
     __shared__ float wos[W + 1];                                // output weights and bias
-    __shared__ float dys[FT_R], tgs[FT_R];
-    __shared__ float red[256];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int li = lane & 15, lg = lane >> 4;
+    __shared__ float dys[FT_R], tgs[FT_R], sq[FT_R], corr[2];
+    __shared__ __attribute__((aligned(16))) float red[256];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t M = a.M;
     const int nrt = (int)(M / FT_R);
     // B fragments: bw0 the first layer's (one k-step); the products after it
@@ -676,16 +697,23 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
     // k + 2 are loaded into a buffer as soon as product k has used it, so
     // every load has a whole layer's work to arrive
     bf16x8 bw0[8][4], bwa[8][4], bwb[8][4];
+    // Masters and moments of this thread's four weights of the block's phase-2
+    // item.  Where no block has two items they stay here from the first step
+    // of the launch to the last.
+    float mo[4], vo[4], th[4];
     bool first_in_lds = false;   // the step's first tile is already in Hs / tgs
     for (int st = 0; st < a.nsteps; ++st) {
+        // Offsets are formed in each step and phase: kept from step to step they
+        // spill, and after a grid barrier a spilled value comes from memory.
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        int lane = tid & 63, li = lane & 15, lg = lane >> 4;
         float* loss = a.loss ? a.loss + st : nullptr;
         const float lr = a.lrs ? a.lrs[st] : a.lr;
-        const float c1 = a.lrs ? 1.f - powf(0.9f, (float)(a.step0 + st + 1)) : a.c1;
-        const float c2 = a.lrs ? 1.f - powf(0.999f, (float)(a.step0 + st + 1)) : a.c2;
         float loss_acc = 0.f;
-        for (int l = 0; l < a.depth; ++l) bs[l][tid] = a.theta[a.L.b_off[l] + tid];
-        wos[tid] = a.theta[a.wout_off + tid];
-        if (tid == 0) wos[W] = a.theta[a.bout_off];
+        float bv[FT_MAXDEPTH], wv = a.theta[a.wout_off + tid], wb = a.theta[a.bout_off];
+#pragma unroll
+        for (int l = 0; l < FT_MAXDEPTH; ++l) bv[l] = l < a.depth ? a.theta[a.L.b_off[l] + tid] : 0.f;
 
         // ---------------- phase 1: rows through forward and backward ----------------
         for (int rt = blockIdx.x; rt < nrt; rt += gridDim.x) {
@@ -695,137 +723,184 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
             ft_load_w<MLP_KPAD>(wfr[0], wave, lane, bw0);
             if (const bf16* w1 = ft_chain_w(wfr, wtfr, a.depth, 1)) ft_load_w<W>(w1, wave, lane, bwa);
             if (const bf16* w2 = ft_chain_w(wfr, wtfr, a.depth, 2)) ft_load_w<W>(w2, wave, lane, bwb);
+            if (rt == (int)blockIdx.x) {
+#pragma unroll
+                for (int l = 0; l < FT_MAXDEPTH; ++l) bs[l][tid] = bv[l];
+                wos[tid] = wv;
+                if (tid == 0) wos[W] = wb;
+            }
             if (!(first_in_lds && rt == (int)blockIdx.x)) {
                 ft_rows g;
                 ft_rows_load(a, st, m0, tid, g);
-                ft_rows_store(g, tid, Hs, tgs);
+                ft_rows_store(g, tid, Hs[0], tgs);
             }
             __syncthreads();
-            if (tid < MLP_KPAD) ft_store_t(Hs, tid, a.XT, M, m0);
+            if (tid < MLP_KPAD) ft_store_t(Hs[0], tid, a.XT, M, m0);
+            // A lane's elements of a layer: columns 64 wave + 16 t + li of rows 4 lg + v,
+            // the same in every layer and in both directions, so the activations'
+            // derivatives stay in registers.
+            float dact[FT_MAXDEPTH][4][4];
 #pragma unroll
             for (int l = 0; l < FT_MAXDEPTH; ++l) {
                 if (l >= a.depth) break;
                 f32x4 acc[4];
                 if (l == 0) {
-                    ft_mma<MLP_KPAD>(Hs, bw0, li, lg, acc);
+                    ft_mma<MLP_KPAD>(Hs[0], bw0, li, lg, acc);
                 } else if (l & 1) {  // product l
-                    ft_mma<W>(Hs, bwa, li, lg, acc);
+                    ft_mma<W>(Hs[l & 1], bwa, li, lg, acc);
                     if (const bf16* wn = ft_chain_w(wfr, wtfr, a.depth, l + 2)) ft_load_w<W>(wn, wave, lane, bwa);
                 } else {
-                    ft_mma<W>(Hs, bwb, li, lg, acc);
+                    ft_mma<W>(Hs[l & 1], bwb, li, lg, acc);
                     if (const bf16* wn = ft_chain_w(wfr, wtfr, a.depth, l + 2)) ft_load_w<W>(wn, wave, lane, bwb);
                 }
-                __syncthreads();  // the layer input has been read by every wave
+                bf16* out = Hs[(l + 1) & 1];
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int c = 64 * wave + 16 * t + li;
                     const float bc = bs[l][c];
+                    bf16x4 h;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int r = 4 * lg + v;
                         const float z = acc[t][v] + bc;
-                        Zs[l][r][c] = z;
-                        Hs[r * P + c] = (bf16)(z * sigmoidf_(z));
+                        const float s = sigmoidf_(z);
+                        h[v] = (bf16)(z * s);
+                        dact[l][t][v] = s * (1.f + z * (1.f - s));
+                        out[(4 * lg + v) * P + c] = h[v];
                     }
+                    if (l + 1 < a.depth) ft_store4(h, 4 * wave + t, li, lg, a.HT[l], M, m0);
                 }
                 __syncthreads();
-                ft_store_t(Hs, tid, a.HT[l], M, m0);
             }
+            const bf16* hl = Hs[a.depth & 1];
             // output layer, residual, loss (16 threads per row)
             {
-                const int r = tid >> 4, part = tid & 15;
-                const bf16x8* hr = reinterpret_cast<const bf16x8*>(Hs + r * P + part * 16);
+                const int r = tid >> 4, q16 = tid & 15;
+                const bf16x8* hr = reinterpret_cast<const bf16x8*>(hl + r * P + q16 * 16);
                 float s = 0.f;
 #pragma unroll
                 for (int k8 = 0; k8 < 2; ++k8) {
                     const bf16x8 hv = hr[k8];
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) s = fmaf((float)hv[q], wos[part * 16 + 8 * k8 + q], s);
+                    for (int q = 0; q < 8; ++q) s = fmaf((float)hv[q], wos[q16 * 16 + 8 * k8 + q], s);
                 }
 #pragma unroll
                 for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o);
-                if (part == 0) {
+                if (q16 == 0) {
                     const float res = s + wos[W] - tgs[r];
                     dys[r] = 2.f * res / (float)M;
                     loss_acc += res * res;
                 }
             }
             __syncthreads();
-            // this tile's share of the output layer's gradient, and dZ of the last hidden layer
+            // this tile's share of the output layer's gradient
             {
-                const int l = a.depth - 1, c = tid;
-                const float woc = wos[c];
+                const int c = tid;
                 float gw = 0.f, gb = 0.f;
 #pragma unroll
                 for (int r = 0; r < FT_R; ++r) {
-                    gw = fmaf(dys[r], (float)Hs[r * P + c], gw);
+                    gw = fmaf(dys[r], (float)hl[r * P + c], gw);
                     gb += dys[r];
-                    Gs[r * P + c] = (bf16)(dys[r] * woc * silu_d(Zs[l][r][c]));
                 }
                 a.opart[(int64_t)c * nrt + rt] = gw;
                 if (c == 0) a.opart[(int64_t)W * nrt + rt] = gb;
             }
+            // dZ of the last hidden layer
+#pragma unroll
+            for (int l = 0; l < FT_MAXDEPTH; ++l) {
+                if (l != a.depth - 1) continue;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int c = 64 * wave + 16 * t + li;
+                    const float woc = wos[c];
+                    bf16x4 g;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        g[v] = (bf16)(dys[4 * lg + v] * woc * dact[l][t][v]);
+                        Gs[0][(4 * lg + v) * P + c] = g[v];
+                    }
+                    ft_store4(g, 4 * wave + t, li, lg, a.DZT[l], M, m0);
+                }
+            }
             __syncthreads();
-            ft_store_t(Gs, tid, a.DZT[a.depth - 1], M, m0);
             // backward through the hidden layers: dZ_{l-1} = (dZ_l W_l) silu'(Z_{l-1})
             // (product 2 depth - 1 - l: bwa when l is even)
 #pragma unroll
             for (int l = FT_MAXDEPTH - 1; l >= 1; --l) {
                 if (l >= a.depth) continue;
                 f32x4 acc[4];
-                const int k = 2 * a.depth - 1 - l;
+                const int k = 2 * a.depth - 1 - l, in = (a.depth - 1 - l) & 1;
                 if ((l & 1) == 0) {
-                    ft_mma<W>(Gs, bwa, li, lg, acc);
+                    ft_mma<W>(Gs[in], bwa, li, lg, acc);
                     if (const bf16* wn = ft_chain_w(wfr, wtfr, a.depth, k + 2)) ft_load_w<W>(wn, wave, lane, bwa);
                 } else {
-                    ft_mma<W>(Gs, bwb, li, lg, acc);
+                    ft_mma<W>(Gs[in], bwb, li, lg, acc);
                     if (const bf16* wn = ft_chain_w(wfr, wtfr, a.depth, k + 2)) ft_load_w<W>(wn, wave, lane, bwb);
                 }
-                __syncthreads();  // Gs has been read by every wave
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    const int k = 64 * wave + 16 * t + li;
+                    const int c = 64 * wave + 16 * t + li;
+                    bf16x4 g;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int r = 4 * lg + v;
-                        Gs[r * P + k] = (bf16)(acc[t][v] * silu_d(Zs[l - 1][r][k]));
+                        g[v] = (bf16)(acc[t][v] * dact[l - 1][t][v]);
+                        Gs[1 - in][(4 * lg + v) * P + c] = g[v];
                     }
+                    ft_store4(g, 4 * wave + t, li, lg, a.DZT[l - 1], M, m0);
                 }
                 __syncthreads();
-                ft_store_t(Gs, tid, a.DZT[l - 1], M, m0);
             }
-            __syncthreads();  // Hs and Gs are rewritten by the next tile
         }
-        red[tid] = loss_acc;
+        if ((tid & 15) == 0) sq[tid >> 4] = loss_acc;  // the threads that hold any
         __syncthreads();
         if (tid == 0) {
             float s = 0.f;
-            for (int i = 0; i < 256; ++i) s += red[i];
+#pragma unroll
+            for (int i = 0; i < FT_R; ++i) s += sq[i];
             a.lossp[blockIdx.x] = s;
         }
-        ft_grid_sync(a.bar);
+        ft_grid_sync(a.bar, [&]() {
+            const float k = (float)(a.step0 + st + 1);
+            const float c1 = a.lrs ? 1.f - powf(0.9f, k) : a.c1, c2 = a.lrs ? 1.f - powf(0.999f, k) : a.c2;
+            if (lane == 0) corr[0] = c1, corr[1] = c2;
+        });
+        const float c1 = corr[0], c2 = corr[1];
+        tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        lane = tid & 63, li = lane & 15, lg = lane >> 4;
 
         // ---------------- phase 2: weight gradients and the update ----------------
-        if (blockIdx.x == 0 && loss && tid == 0) {
-            float s = 0.f;
-            for (int i = 0; i < (int)gridDim.x; ++i) s += a.lossp[i];
-            loss[0] = s / (float)M;
-        }
         // the next step's first tile, loaded across this phase and the barrier
         ft_rows nxt;
         const bool pre = st + 1 < a.nsteps && (int)blockIdx.x < nrt;
         if (pre) ft_rows_load(a, st + 1, (int64_t)blockIdx.x * FT_R, tid, nxt);
+        // the loss, by the last block (which seldom has an item), added in block order
+        if (blockIdx.x == gridDim.x - 1 && loss) {
+            float s = 0.f;
+            for (int o = 0; o < (int)gridDim.x; o += 256) {
+                __syncthreads();
+                red[tid] = o + tid < (int)gridDim.x ? a.lossp[o + tid] : 0.f;
+                __syncthreads();
+                if (tid == 0) {
+#pragma unroll 16
+                    for (int i = 0; i < 64; ++i) {
+                        const f32x4 v = reinterpret_cast<const f32x4*>(red)[i];
+                        s = (((s + v[0]) + v[1]) + v[2]) + v[3];
+                    }
+                }
+            }
+            if (tid == 0) loss[0] = s / (float)M;
+        }
         // items: per layer l, 8 x (padded fan-in / 32) tiles of 32 x 32 of dW_l
         // (n-tile major), then eight output-layer items
         int nw = 0;
         for (int l = 0; l < a.depth; ++l) nw += 8 * (((l == 0) ? MLP_KPAD : W) / 32);
         const int nitems = nw + 8;
-        float* part = &Zs[0][0][0];  // [wave][32][32] partial tiles, then [wave][32] bias partials
         // Items that share operand rows are neighbours in this order; blocks go
         // round-robin over the 8 XCDs, so slot v of XCD x takes item x q + v:
         // each XCD's L2 then fetches about an eighth of the operands instead
         // of nearly all of them.
         const int q8 = (nitems + 7) / 8;
+        const bool hold = 8 * q8 <= (int)gridDim.x, last = st + 1 == a.nsteps;
         for (int vb = blockIdx.x; vb < 8 * q8; vb += gridDim.x) {
             const int it = (vb % 8) * q8 + vb / 8;
             if (it >= nitems) continue;
@@ -837,7 +912,7 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
                 const int c = 32 * oq + (tid >> 3), q = tid & 7;
                 const float* src = a.opart + (int64_t)c * nrt;
                 float g = 0.f;
-#pragma unroll 8
+#pragma unroll 32
                 for (int i = q; i < nrt; i += 8) g += src[i];
                 g += __shfl_xor(g, 1);
                 g += __shfl_xor(g, 2);
@@ -846,7 +921,7 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
                 if (oq == 7 && wave == 0) {
                     const float* sb = a.opart + (int64_t)W * nrt;
                     float d = 0.f;
-#pragma unroll 8
+#pragma unroll 32
                     for (int i = lane & 7; i < nrt; i += 8) d += sb[i];
                     d += __shfl_xor(d, 1);
                     d += __shfl_xor(d, 2);
@@ -932,14 +1007,13 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
             __syncthreads();
             // the four quarters added in wave order, then four of the tile's 1024
             // weights per thread (every load first)
-            float g[4], mo[4], vo[4], th[4];
+            float g[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int e = tid + 256 * r, n = e >> 5, k = e & 31;
                 g[r] = ((part[n * 32 + k] + part[(32 + n) * 32 + k]) + part[(64 + n) * 32 + k]) + part[(96 + n) * 32 + k];
-                mo[r] = vo[r] = th[r] = 0.f;
                 const int64_t i = a.L.w_off[l] + (int64_t)(32 * nb + n) * fi + 32 * kb + k;
-                if (32 * kb + k < fi && !a.grad_out) {
+                if ((!hold || st == 0) && 32 * kb + k < fi && !a.grad_out) {
                     mo[r] = a.m[i];
                     vo[r] = a.v[i];
                     th[r] = a.theta[i];
@@ -955,15 +1029,20 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
                     a.grad_out[i] = g[r];
                     continue;
                 }
-                const float t2 = ft_adam(a, i, g[r], mo[r], vo[r], th[r], lr, c1, c2);
+                ft_adam(g[r], mo[r], vo[r], th[r], lr, c1, c2);
+                if (!hold || last) {
+                    a.m[i] = mo[r];
+                    a.v[i] = vo[r];
+                    a.theta[i] = th[r];
+                }
                 // the fragment-order copies feed the next step; the row-major
                 // ones only other kernels, so they are written by the last step
-                const bool last = st + 1 == a.nsteps;
-                a.wfr[l][frag_off(rr, kk, ld)] = (bf16)t2;
-                if (last) a.wbf[l][rr * ld + kk] = (bf16)t2;
+                const bf16 wq = (bf16)th[r];
+                a.wfr[l][frag_off(rr, kk, ld)] = wq;
+                if (last) a.wbf[l][rr * ld + kk] = wq;
                 if (l > 0) {
-                    a.wtfr[l][frag_off(kk, rr, W)] = (bf16)t2;
-                    if (last) a.wbft[l][kk * W + rr] = (bf16)t2;
+                    a.wtfr[l][frag_off(kk, rr, W)] = wq;
+                    if (last) a.wbft[l][kk * W + rr] = wq;
                 }
             }
             if (kb == 0 && tid < 32) {
@@ -972,9 +1051,9 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
             }
             __syncthreads();  // part is rewritten by the next item
         }
-        if (pre) ft_rows_store(nxt, tid, Hs, tgs);
+        if (pre) ft_rows_store(nxt, tid, Hs[0], tgs);
         first_in_lds = pre;
-        if (st + 1 < a.nsteps) ft_grid_sync(a.bar);  // the next step reads the updated weights
+        if (st + 1 < a.nsteps) ft_grid_sync(a.bar, []() {});  // the next step reads the updated weights
     }
 }
 
