@@ -57,13 +57,88 @@ __device__ __forceinline__ double u53(uint32_t hi, uint32_t lo) {
     return (double(v) + 0.5) * (1.0 / 9007199254740992.0);
 }
 
+// 1 / sqrt(s) from the hardware's estimate and one third-order step, and sqrt(s)
+// from it: 12 instructions, about 40 for sqrt and a division.
+__device__ __forceinline__ double rsqrt_fast(double s, double& root) {
+    const double y0 = __builtin_amdgcn_rsq(s);
+    const double e = fma(-s * y0, y0, 1.0);
+    const double y = fma(y0 * e, fma(0.375, e, 0.5), y0);
+    const double r = s * y;
+    root = fma(fma(-r, r, s), 0.5 * y, r);
+    return y;
+}
+
+// The xi in (0, 1] with sum_i sqrt(m_i^2 + xi^2 P_i^2) = roots (P_i = p[i][0]).
+// The sum is increasing and convex in xi, so a Newton step lands right of the root
+// and the next ones descend to it; steps that rounding takes out of the bracket
+// become bisections.  With f the sum, xi f'' <= f': a Newton step of relative
+// size d leaves an error of at most d^2 / 2, hence the end at 1e-8 (five steps
+// from the start value; ending only when a step changes nothing took three
+// times as many, the slowest lane of the wave's counting).
+template <int NF>
+__device__ __forceinline__ double rambo_xi(double roots, const ps_masses& ms, const double (&p)[NF][4]) {
+    double lo = 0.0, hi = 1.0, sm = 0.0;
+#pragma unroll
+    for (int i = 0; i < NF; ++i) sm += ms.m[i];
+    double xi = sqrt(fmax(1.0 - (sm / roots) * (sm / roots), 1e-30));
+    for (int it = 0; it < 200; ++it) {
+        double f = -roots, df = 0.0;
+#pragma unroll
+        for (int i = 0; i < NF; ++i) {
+            const double pi = p[i][0];
+            if (ms.m[i] == 0.0) {  // the same for all lanes
+                f = fma(xi, pi, f);
+                df += pi;
+            } else {
+                double en;
+                const double xp = xi * pi, ie = rsqrt_fast(fma(xp, xp, ms.m[i] * ms.m[i]), en);
+                f += en;
+                df = fma(xp * pi, ie, df);
+            }
+        }
+        if (f > 0.0) hi = xi;
+        else lo = xi;
+        double nx = xi - f / df;
+        const bool newton = nx >= lo && nx <= hi;
+        if (!newton) nx = 0.5 * (lo + hi);
+        const bool done = fabs(nx - xi) <= (newton ? 1e-8 : 1e-16) * nx;
+        xi = nx;
+        if (done) break;
+    }
+    return xi;
+}
+
+// x^N
+template <int N>
+__device__ __forceinline__ double ipow(double x) {
+    if constexpr (N == 0) return 1.0;
+    else if constexpr (N % 2) return x * ipow<N - 1>(x);
+    else return ipow<N / 2>(x * x);
+}
+
+// The block's nb rows from LDS, one double apart (lanes then write their rows
+// without bank conflicts), to consecutive addresses, 16 bytes per lane.
+template <int NP>
+__device__ __forceinline__ void ps_write_rows(const double* tile, double* __restrict__ mom, int nb) {
+    constexpr int H = 2 * NP;  // double2 per row
+    double2* dst = reinterpret_cast<double2*>(mom);
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+        const int k = PS_BLOCK * j + (int)threadIdx.x, r = k / H, c = 2 * (k % H);
+        if (r < nb) dst[k] = double2{tile[r * (4 * NP + 1) + c], tile[r * (4 * NP + 1) + c + 1]};
+    }
+}
+
 // Events first .. first + nevt - 1 of the stream; momenta [nevt][NF + 2][4].
+// 2^20 events of four particles, two of them massive, take 72 us (the 210 MB
+// alone 41), against 369 us: with Newton steps until xi no longer moved, sqrt and
+// divisions in them, pow and sincos of 2 pi u.
 template <int NF>
 __global__ __launch_bounds__(PS_BLOCK) void k_ps_rambo(double roots, ps_masses ms, int massive, double w0,
                                                        uint64_t seed, int64_t first, int64_t nevt,
                                                        double* __restrict__ mom, double* __restrict__ wt) {
     constexpr int NP = NF + 2, ROW = NP * 4;
-    __shared__ double tile[PS_BLOCK * ROW];
+    __shared__ double tile[PS_BLOCK * (ROW + 1)];
     const int64_t e0 = (int64_t)blockIdx.x * PS_BLOCK;
     const int t = threadIdx.x;
     const int64_t e = e0 + t;
@@ -75,11 +150,10 @@ __global__ __launch_bounds__(PS_BLOCK) void k_ps_rambo(double roots, ps_masses m
         const philox_out a = philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), 2 * i, 0u, k0, k1);
         const philox_out b = philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), 2 * i + 1, 0u, k0, k1);
         const double c = 2.0 * u53(a.x[0], a.x[1]) - 1.0;
-        const double phi = 2.0 * M_PI * u53(a.x[2], a.x[3]);
         const double q0 = -log(u53(b.x[0], b.x[1]) * u53(b.x[2], b.x[3]));
         const double st = sqrt(1.0 - c * c);
         double sp, cp;
-        sincos(phi, &sp, &cp);
+        sincospi(2.0 * u53(a.x[2], a.x[3]), &sp, &cp);
         q[i][0] = q0;
         q[i][1] = q0 * st * cp;
         q[i][2] = q0 * st * sp;
@@ -99,54 +173,30 @@ __global__ __launch_bounds__(PS_BLOCK) void k_ps_rambo(double roots, ps_masses m
         p[i][2] = x * (q[i][2] + b2 * q[i][0] + a * bq * b2);
         p[i][3] = x * (q[i][3] + b3 * q[i][0] + a * bq * b3);
     }
-    double xi = 1.0, w = w0;
-    if (massive) {
-        // sum_i sqrt(m_i^2 + xi^2 P_i^2) = roots: increasing in xi, negative at 0,
-        // non-negative at 1; Newton steps kept inside the bracket
-        double lo = 0.0, hi = 1.0;
-        for (int it = 0; it < 200; ++it) {
-            double f = -roots, df = 0.0;
-#pragma unroll
-            for (int i = 0; i < NF; ++i) {
-                const double en = sqrt(ms.m[i] * ms.m[i] + xi * xi * p[i][0] * p[i][0]);
-                f += en;
-                df += xi * p[i][0] * p[i][0] / en;
-            }
-            if (f > 0.0) hi = xi;
-            else lo = xi;
-            double nx = xi - f / df;
-            if (!(nx > lo && nx < hi)) nx = 0.5 * (lo + hi);
-            const bool done = fabs(nx - xi) <= 1e-16 * xi;
-            xi = nx;
-            if (done) break;
-        }
-    }
+    const double xi = massive ? rambo_xi<NF>(roots, ms, p) : 1.0;
+    double w = w0;
     double sk = 0.0, pr = 1.0, sk2 = 0.0;
-    double* row = tile + t * ROW;
+    double* row = tile + t * (ROW + 1);
     row[0] = 0.5 * roots, row[1] = 0.0, row[2] = 0.0, row[3] = 0.5 * roots;
     row[4] = 0.5 * roots, row[5] = 0.0, row[6] = 0.0, row[7] = -0.5 * roots;
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
         const double kx = xi * p[i][1], ky = xi * p[i][2], kz = xi * p[i][3];
         const double kk = sqrt(kx * kx + ky * ky + kz * kz);
-        const double en = sqrt(ms.m[i] * ms.m[i] + kk * kk);  // on shell by construction
+        const double en = ms.m[i] == 0.0 ? kk : sqrt(ms.m[i] * ms.m[i] + kk * kk);  // on shell by construction
         row[4 * (i + 2) + 0] = en;
         row[4 * (i + 2) + 1] = kx;
         row[4 * (i + 2) + 2] = ky;
         row[4 * (i + 2) + 3] = kz;
         sk += kk;
-        pr *= kk / en;
-        sk2 += kk * kk / en;
+        const double v = ms.m[i] == 0.0 ? 1.0 : kk / en;
+        pr *= v;
+        sk2 += kk * v;
     }
-    if (massive) w = w0 * pow(sk / roots, 2 * NF - 3) * pr * roots / sk2;
+    if (massive) w = w0 * ipow<2 * NF - 3>(sk / roots) * pr * roots / sk2;
     if (wt && e < nevt) wt[e] = w;
     __syncthreads();
-    // coalesced write-back of the block's rows (double2 granules)
-    const int64_t nb = (nevt - e0 < PS_BLOCK) ? (nevt - e0) : PS_BLOCK;
-    const int total2 = (int)(nb * ROW / 2);
-    const double2* src = reinterpret_cast<const double2*>(tile);
-    double2* dst = reinterpret_cast<double2*>(mom + e0 * ROW);
-    for (int j = t; j < total2; j += PS_BLOCK) dst[j] = src[j];
+    ps_write_rows<NP>(tile, mom + e0 * ROW, (int)((nevt - e0 < PS_BLOCK) ? (nevt - e0) : PS_BLOCK));
 }
 
 // ---------------------------------------------------------------------------
@@ -185,11 +235,10 @@ __device__ __forceinline__ void rambo_active(double roots, double m0, int nb, ui
             const philox_out a = philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), 2 * i, 0u, k0, k1);
             const philox_out b = philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), 2 * i + 1, 0u, k0, k1);
             const double c = 2.0 * u53(a.x[0], a.x[1]) - 1.0;
-            const double phi = 2.0 * M_PI * u53(a.x[2], a.x[3]);
             const double q0 = -log(u53(b.x[0], b.x[1]) * u53(b.x[2], b.x[3]));
             const double st = sqrt(1.0 - c * c);
             double sp, cp;
-            sincos(phi, &sp, &cp);
+            sincospi(2.0 * u53(a.x[2], a.x[3]), &sp, &cp);
             q[i][0] = q0;
             q[i][1] = q0 * st * cp;
             q[i][2] = q0 * st * sp;
@@ -211,23 +260,21 @@ __device__ __forceinline__ void rambo_active(double roots, double m0, int nb, ui
     }
     double xi = 1.0;
     if (m0 > 0.0) {
-        double lo = 0.0, hi = 1.0;
-        for (int it = 0; it < 200; ++it) {
-            double f = -roots, df = 0.0;
+        // as rambo_xi, only body 0 massive
+        double lo = 0.0, hi = 1.0, rest = 0.0;
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                if (i < nb) {
-                    const double mi = (i == 0) ? m0 : 0.0;
-                    const double en = sqrt(mi * mi + xi * xi * p[i][0] * p[i][0]);
-                    f += en;
-                    df += xi * p[i][0] * p[i][0] / en;
-                }
-            }
+        for (int i = 1; i < NB; ++i) rest += p[i][0];
+        xi = sqrt(fmax(1.0 - (m0 / roots) * (m0 / roots), 1e-30));
+        for (int it = 0; it < 200; ++it) {
+            double en;
+            const double xp = xi * p[0][0], ie = rsqrt_fast(fma(xp, xp, m0 * m0), en);
+            const double f = fma(xi, rest, en - roots), df = fma(xp * p[0][0], ie, rest);
             if (f > 0.0) hi = xi;
             else lo = xi;
             double nx = xi - f / df;
-            if (!(nx > lo && nx < hi)) nx = 0.5 * (lo + hi);
-            const bool done = fabs(nx - xi) <= 1e-16 * xi;
+            const bool newton = nx >= lo && nx <= hi;
+            if (!newton) nx = 0.5 * (lo + hi);
+            const bool done = fabs(nx - xi) <= (newton ? 1e-8 : 1e-16) * nx;
             xi = nx;
             if (done) break;
         }
@@ -248,7 +295,7 @@ __global__ __launch_bounds__(PS_BLOCK) void k_ps_mc(ps_mc_args g, uint64_t seed,
                                                     double* __restrict__ mom, double* __restrict__ wt,
                                                     int32_t* __restrict__ chan) {
     constexpr int NP = NF + 2, ROW = NP * 4;
-    __shared__ double tile[PS_BLOCK * ROW];
+    __shared__ double tile[PS_BLOCK * (ROW + 1)];
     const int64_t e0 = (int64_t)blockIdx.x * PS_BLOCK;
     const int t = threadIdx.x;
     const int64_t e = e0 + t;
@@ -275,10 +322,10 @@ __global__ __launch_bounds__(PS_BLOCK) void k_ps_mc(ps_mc_args g, uint64_t seed,
     } else {
         // isotropic decay of the pair (body 0, mass M) in its rest frame
         const philox_out x17 = philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), 17u, 0u, k0, k1);
-        const double ct = 2.0 * u53(x17.x[0], x17.x[1]) - 1.0, ph = 2.0 * M_PI * u53(x17.x[2], x17.x[3]);
+        const double ct = 2.0 * u53(x17.x[0], x17.x[1]) - 1.0;
         const double st = sqrt(1.0 - ct * ct);
         double sp, cp;
-        sincos(ph, &sp, &cp);
+        sincospi(2.0 * u53(x17.x[2], x17.x[3]), &sp, &cp);
         const double es = 0.5 * M;
         const double ks1 = es * st * cp, ks2 = es * st * sp, ks3 = es * ct;
         const double pk = p[0][1] * ks1 + p[0][2] * ks2 + p[0][3] * ks3;
@@ -330,7 +377,7 @@ __global__ __launch_bounds__(PS_BLOCK) void k_ps_mc(ps_mc_args g, uint64_t seed,
             pr *= ki / f[i][0];
             sk2 += ki * ki / f[i][0];
         }
-        const double wr = g.w0m1 * pow(sk / g.roots, 2 * (NF - 1) - 3) * pr * g.roots / sk2;
+        const double wr = g.w0m1 * ipow<2 * (NF - 1) - 3>(sk / g.roots) * pr * g.roots / sk2;
         const double mw = g.mz * g.wz, d = m2 - g.mz * g.mz;
         const double p_bw = mw / (d * d + mw * mw) / (g.bw_hi - g.bw_lo);
         const double p_ph = 1.0 / (m2 * log(g.b2 / g.a2));
@@ -341,7 +388,7 @@ __global__ __launch_bounds__(PS_BLOCK) void k_ps_mc(ps_mc_args g, uint64_t seed,
         if (wt) wt[e] = 1.0 / gsum;
         if (chan) chan[e] = c;
     }
-    double* row = tile + t * ROW;
+    double* row = tile + t * (ROW + 1);
     row[0] = 0.5 * g.roots, row[1] = 0.0, row[2] = 0.0, row[3] = 0.5 * g.roots;
     row[4] = 0.5 * g.roots, row[5] = 0.0, row[6] = 0.0, row[7] = -0.5 * g.roots;
 #pragma unroll
@@ -349,11 +396,7 @@ __global__ __launch_bounds__(PS_BLOCK) void k_ps_mc(ps_mc_args g, uint64_t seed,
 #pragma unroll
         for (int kx = 0; kx < 4; ++kx) row[4 * (i + 2) + kx] = f[i][kx];
     __syncthreads();
-    const int64_t nb = (nevt - e0 < PS_BLOCK) ? (nevt - e0) : PS_BLOCK;
-    const int total2 = (int)(nb * ROW / 2);
-    const double2* src = reinterpret_cast<const double2*>(tile);
-    double2* dst = reinterpret_cast<double2*>(mom + e0 * ROW);
-    for (int j = t; j < total2; j += PS_BLOCK) dst[j] = src[j];
+    ps_write_rows<NP>(tile, mom + e0 * ROW, (int)((nevt - e0 < PS_BLOCK) ? (nevt - e0) : PS_BLOCK));
 }
 
 template <int NF>

@@ -89,3 +89,23 @@ def test_rambo_errors(env):
     with pytest.raises(me.MEError):
         me.ps_rambo(100.0, [0.0], 1, 0, 8, torch.empty((8, 3, 4), dtype=torch.float64, device="cuda"))
     me.ps_rambo(100.0, [0.0, 0.0], 1, 0, 0, out)  # nevt == 0: nothing
+
+
+@pytest.mark.parametrize("masses", [(173.0, 173.0, 0.0, 0.0), (1e-9, 0.0), (999.999, 0.0, 0.0), (300.0, 300.0, 399.9999),
+                                    (1.0, 2.0, 4.0, 8.0, 16.0, 32.0, 64.0, 872.99)])
+def test_rescaling_to_the_energy(env, masses):
+    """From light particles to 1e-7 above threshold: the final energies add up to
+    sqrt(s) and every particle is on its shell.  xi balances the energies of the
+    massless points, whose own rounding is that of the conformal map (4e-15 kappa
+    per component, as above, so 4e-15 kappa NF in the sum); each final energy and
+    xi add an ulp or two (2e-15 NF)."""
+    torch, me = env
+    roots, n, nf = 1000.0, 2000, len(masses)
+    print(f"[ps] rescaling {masses}", flush=True)
+    mom, wt = me.rambo(roots, list(masses), 17, n)
+    fin = mom.cpu().numpy()[:, 2:]
+    assert np.all(np.isfinite(fin)) and np.all(np.isfinite(wt.cpu().numpy())) and np.all(wt.cpu().numpy() > 0)
+    kappa = oracle.rambo(roots, list(masses), 17, 0, n, cond=True)[2]
+    assert np.all(np.abs(fin[..., 0].sum(axis=1) - roots) <= (2e-15 + 4e-15 * kappa) * nf * roots)
+    m2 = fin[..., 0] ** 2 - (fin[..., 1:] ** 2).sum(axis=-1)
+    assert np.all(np.abs(m2 - np.array(masses) ** 2) <= 4e-15 * fin[..., 0] ** 2)
