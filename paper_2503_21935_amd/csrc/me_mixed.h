@@ -144,6 +144,56 @@ MEV float colour_sum_mfma(const cx<float>* J, const float* S, char* lds, int lan
     return q / (s * s);
 }
 
+// Float32 wavefunctions of the external particles for both helicities of one
+// event per lane, in LDS: of a gluon those of helicity +1 (at -1 the real parts
+// change sign), of t and tbar both.  They are made in float64 with roots and
+// divisions, a tenth of the kernel's instructions when done for every helicity.
+template <int NG>
+struct ext_store {
+    static constexpr int SPIN = 5 * NG;     // [helicity][ubar, v][8]
+    static constexpr int SIZE = SPIN + 32;  // floats per lane, 64 apart
+};
+template <class P>
+MEV void externals_store(gg_ext<float, P::ngluon>& x, float* E) {
+    constexpr int NG = P::ngluon;
+#pragma unroll
+    for (int up = 0; up < 2; ++up) {
+        gg_externals<P, float>(x, up ? (1 << P::npart) - 1 : 0);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float* s = E + (ext_store<NG>::SPIN + 16 * up + 2 * c) * 64;
+            s[0] = x.ubar3.s[c].r, s[64] = x.ubar3.s[c].i;
+            s[8 * 64] = x.v4.s[c].r, s[9 * 64] = x.v4.s[c].i;
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < NG; ++a) {
+        float* e = E + 5 * a * 64;
+        e[0] = x.eps[a].v[1].r, e[64] = x.eps[a].v[1].i, e[128] = x.eps[a].v[2].r, e[192] = x.eps[a].v[2].i;
+        e[256] = x.eps[a].v[3].r;
+    }
+}
+template <class P>
+MEV void externals_load(gg_ext<float, P::ngluon>& x, const float* E, int h) {
+    constexpr int NG = P::ngluon, NP = P::npart;
+#pragma unroll
+    for (int a = 0; a < NG; ++a) {
+        const float* e = E + 5 * a * 64;
+        const float s = float(helicity_of<NP>(h, a < 2 ? a : a + 2));
+        x.eps[a].v[0] = mk(0.f, 0.f);
+        x.eps[a].v[1] = mk(s * e[0], e[64]);
+        x.eps[a].v[2] = mk(s * e[128], e[192]);
+        x.eps[a].v[3] = mk(s * e[256], 0.f);
+    }
+    const float* u = E + (ext_store<NG>::SPIN + (helicity_of<NP>(h, 2) > 0 ? 16 : 0)) * 64;
+    const float* v = E + (ext_store<NG>::SPIN + (helicity_of<NP>(h, 3) > 0 ? 24 : 8)) * 64;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        x.ubar3.s[c] = mk(u[2 * c * 64], u[(2 * c + 1) * 64]);
+        x.v4.s[c] = mk(v[2 * c * 64], v[(2 * c + 1) * 64]);
+    }
+}
+
 // Mixed kernel: out = float32-form |M|^2 (as float64); events whose error
 // estimate exceeds tol are appended to flag_idx (wave-aggregated atomics on
 // *flag_count).  err_out / flag_out (optional) receive the estimate and the
@@ -166,11 +216,13 @@ __global__ __launch_bounds__(ME_BLOCK, ME_MIXED_WAVES) void k_me_gg_mixed(const 
     __shared__ double Qt[ME_MOM_ROW(NG + 2)];
     gg_ext<T, NG> x;
     gg_setup<P, T>(x, mom, ev, Qt, lane, prm);
+    __shared__ float Et[ext_store<NG>::SIZE * 64];
+    externals_store<P>(x, Et + lane);
     float acc = 0.f, dacc = 0.f;
 #pragma unroll 1
     for (int ih = 0; ih < nh; ++ih) {
         const int h = hels[ih];
-        gg_externals<P, T>(x, h);
+        externals_load<P>(x, Et + lane, h);
         cx<T> J[P::ncol];
         T S[P::ncol];
 #pragma unroll
