@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/mlp.h"
@@ -490,16 +491,18 @@ __global__ void k_to_bf16_t(const float* __restrict__ theta, int64_t o, int rows
 // LDS in a fixed order (the result does not depend on the grid) and the block
 // applies Adam to the tile's FP32 masters and refreshes their BF16 copies, so
 // every parameter is updated by the block that formed its gradient; where no
-// block has two tiles the masters and moments stay in its registers from step
-// to step.  Rounding points are those of the layered path.
-// A step of 4096 rows at depth 4 takes 47 us (68 before): 20 in phase 1, of
-// which 1 us per product is one CU's share of the weights through its L1, 15 in
-// phase 2 (half a megabyte of operands per block), the rest the two barriers and
-// the first reads behind each, which come from memory.  What the 21 us were: the
-// loss added in one chain of dependent loads by a block with an item of its own
-// (20), 256 LDS reads for 16 partial losses (2), operands left dirty for the
-// barrier to write back (3), moments read and written in every step (2); less
-// what two activation buffers and derivatives kept in registers gave.
+// block has two tiles the masters and moments stay in its LDS from step to
+// step.  Rounding points are those of the layered path.
+// A step of 4096 rows at depth 4 takes 41 us (68 before): 20 in phase 1, of which
+// 1 us per product is one CU's share of the weights through its L1 and 5 the
+// first reads after the barrier, which come from memory; 11 in phase 2 (half a
+// megabyte of operands per block); the rest the two barriers with their cache
+// write-back and invalidation.  What the 27 us were: the loss added in one chain of
+// dependent loads by a block with an item of its own (20), 256 LDS reads for 16
+// partial losses (2), operands left dirty for the barrier to write back (3),
+// moments read and written in every step (2), registers spilled to memory
+// that each barrier's invalidation makes cold, and loads under conditions that
+// make the counted waits wait for everything (6 together).
 // ---------------------------------------------------------------------------
 #define FT_R 16        // rows per phase-1 tile
 #define FT_S 4         // batch quarters of the weight-gradient sums, one per wave
@@ -533,20 +536,18 @@ struct ft_args {
     int nsteps;               // steps in this launch, batch st on rows idx[st M ..] (or st M ..)
 };
 
-__device__ __forceinline__ float silu_d(float z) {
-    const float s = sigmoidf_(z);
-    return s * (1.f + z * (1.f - s));
-}
-
 // B fragments of rows 64 wave + 16 t + 0..15 of the [256][K] matrix Wm kept in
 // fragment order (K / 32 MFMA k-steps).
 template <int K>
 __device__ __forceinline__ void ft_load_w(const bf16* __restrict__ Wm, int wave, int lane, bf16x8 (&b)[8][4]) {
+    unsigned off = 16u * (unsigned)lane;
+    asm volatile("" : "+v"(off));  // scalar base plus this: no vector addresses to keep (and spill) across the steps
+    const char* base = reinterpret_cast<const char*>(Wm) + (int64_t)wave * (4 * (K / 32) * 1024);
 #pragma unroll
     for (int ks = 0; ks < K / 32; ++ks)
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-            b[ks][t] = *reinterpret_cast<const bf16x8*>(Wm + ((int64_t)((4 * wave + t) * (K / 32) + ks) * 64 + lane) * 8);
+            b[ks][t] = *reinterpret_cast<const bf16x8*>(base + (t * (K / 32) + ks) * 1024 + off);
 }
 
 // acc[t] = (16-row LDS tile A, pitch MLPF_PITCH) x (the loaded rows)^T.
@@ -563,12 +564,11 @@ __device__ __forceinline__ void ft_mma(const bf16* A, const bf16x8 (&b)[8][4], i
 }
 
 // The weights of product k of a tile's chain after the first layer (k = 1 ..
-// 2 (depth - 1)): W_k forward for k < depth, then W_l^T backward for l =
-// depth - 1 .. 1; nullptr past the end.
-__device__ __forceinline__ const bf16* ft_chain_w(const bf16* const* wfr, const bf16* const* wtfr, int depth, int k) {
-    if (k <= depth - 1) return wfr[k];
-    if (k <= 2 * (depth - 1)) return wtfr[2 * depth - 1 - k];
-    return nullptr;
+// 2 (D - 1)): W_k forward for k < D, then W_l^T backward for l = D - 1 .. 1.
+template <int D, int K>
+__device__ __forceinline__ void ft_load_chain(const ft_args& a, int wave, int lane, bf16x8 (&b)[8][4]) {
+    if constexpr (K >= 1 && K <= D - 1) ft_load_w<MLPF_W>(a.wfr[K], wave, lane, b);
+    else if constexpr (K >= D && K <= 2 * (D - 1)) ft_load_w<MLPF_W>(a.wtfr[2 * D - 1 - K], wave, lane, b);
 }
 
 // Grid-wide barrier of a cooperative launch (every block resident).  Each
@@ -577,7 +577,7 @@ __device__ __forceinline__ const bf16* ft_chain_w(const bf16* const* wfr, const 
 // arrives on bar[0] and waits for the generation in bar[32] to move; the last
 // block to arrive resets the count and moves the generation.  One release
 // and one acquire per block, where a fence in every wave would write the L2
-// back once per wave.  Wave 1 does `meanwhile` during the wait.
+// back once per wave.  The other waves do `meanwhile` during the wait.
 template <class F>
 __device__ __forceinline__ void ft_grid_sync(unsigned* bar, F&& meanwhile) {
     __builtin_amdgcn_s_waitcnt(0);
@@ -594,7 +594,7 @@ __device__ __forceinline__ void ft_grid_sync(unsigned* bar, F&& meanwhile) {
                 __builtin_amdgcn_s_sleep(1);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    } else if ((threadIdx.x >> 6) == 1) {
+    } else if (threadIdx.x >= 64) {
         meanwhile();
     }
     __syncthreads();
@@ -628,8 +628,8 @@ __device__ __forceinline__ void ft_store_t(const bf16* S, int c, bf16* dst, int6
 
 // Adam on a parameter (FP32 master, moments) with gradient g.
 __device__ __forceinline__ void ft_adam(float g, float& m, float& v, float& th, float lr, float c1, float c2) {
-    m = 0.9f * m + 0.1f * g;
-    v = 0.999f * v + 0.001f * g * g;
+    m = fmaf(0.1f, g, 0.9f * m);  // explicit: which product is fused must not depend on the surroundings
+    v = fmaf(0.001f * g, g, 0.999f * v);
     th = th - lr * (m / c1) / (sqrtf(v / c2) + 1e-8f);
 }
 
@@ -647,37 +647,64 @@ __device__ __forceinline__ void ft_update(const ft_args& a, int64_t i, float g, 
     a.theta[i] = th;
 }
 
-// The 16 input rows (padded to MLP_KPAD features) and targets of the tile at
-// batch row m0 of step st: loaded into registers (two elements per thread),
-// then written to LDS, so that the loads of the next step's first tile can be
-// in flight across the end of the current step.
-struct ft_rows {
-    float xv[2], tv[2];
-};
+// f(0) .. f(N - 1) with constant arguments
+template <int N, int K = 0, class F>
+__device__ __forceinline__ void ft_each(F&& f) {
+    if constexpr (K < N) {
+        f(std::integral_constant<int, K>{});
+        ft_each<N, K + 1>(f);
+    }
+}
 
-__device__ __forceinline__ void ft_rows_load(const ft_args& a, int st, int64_t m0, int tid, ft_rows& g) {
-    static_assert(FT_R * MLP_KPAD == 2 * 256, "two elements per thread");
+// Sum of src[0 .. n): thread q of eight adjacent ones adds q, q + 8, ..., 32 loads
+// in flight, and the eight are combined by shuffles.
+__device__ __forceinline__ float ft_sum8(const float* __restrict__ src, int n, int q) {
+    float g = 0.f;
+    for (int i = q; i < n; i += 256) {
+        float v[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) v[u] = src[i + 8 * u < n ? i + 8 * u : i];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 32; ++u) g = i + 8 * u < n ? g + v[u] : g;
+    }
+    g += __shfl_xor(g, 1);
+    g += __shfl_xor(g, 2);
+    return g + __shfl_xor(g, 4);
+}
+
+// The 16 input rows (padded to MLP_KPAD features) and targets of the tile at
+// batch row m0 of step st into LDS, by N threads u = 0 .. N - 1.
+template <int N>
+__device__ __forceinline__ void ft_rows(const ft_args& a, int st, int64_t m0, int u, bf16* Hs, float* tgs) {
+    constexpr int E = FT_R * MLP_KPAD, Q = (E + N - 1) / N;
     const int32_t* idx = a.idx ? a.idx + (int64_t)st * a.M : nullptr;
     const float* x = a.idx ? a.x : a.x + (int64_t)st * a.M * a.n_in;
     const float* tg = a.idx ? a.t : a.t + (int64_t)st * a.M;
+    int64_t src[Q];
+    float xv[Q], tv[Q];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int e = tid + 256 * q, r = e / MLP_KPAD, k = e % MLP_KPAD;
-        const int64_t src = idx ? idx[m0 + r] : m0 + r;
-        g.xv[q] = k < a.n_in ? x[src * a.n_in + k] : 0.f;
-        g.tv[q] = k == 0 ? tg[src] : 0.f;
+    for (int q = 0; q < Q; ++q) {
+        const int e = u + N * q, r = (e < E ? e : u) / MLP_KPAD;
+        src[q] = idx ? idx[m0 + r] : m0 + r;
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int k = (u + N * q) % MLP_KPAD;
+        xv[q] = x[src[q] * a.n_in + (k < a.n_in ? k : 0)];
+        tv[q] = tg[src[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int e = u + N * q, r = e / MLP_KPAD, k = e % MLP_KPAD;
+        if (e < E) {
+            Hs[r * MLPF_PITCH + k] = (bf16)(k < a.n_in ? xv[q] : 0.f);
+            if (k == 0) tgs[r] = tv[q];
+        }
     }
 }
 
-__device__ __forceinline__ void ft_rows_store(const ft_rows& g, int tid, bf16* Hs, float* tgs) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int e = tid + 256 * q, r = e / MLP_KPAD, k = e % MLP_KPAD;
-        Hs[r * MLPF_PITCH + k] = (bf16)g.xv[q];
-        if (k == 0) tgs[r] = g.tv[q];
-    }
-}
-
+template <int D>
 __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
     constexpr int W = MLPF_W, P = MLPF_PITCH;
     static_assert(FT_R == 16 && W == 256, "one 16-row MFMA tile per phase-1 step, one thread per feature");
@@ -685,73 +712,64 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
     // needs one barrier (the first Hs is the tile's input)
     __shared__ __attribute__((aligned(16))) bf16 Hs[2][FT_R * P], Gs[2][FT_R * P];
     __shared__ float part[4096 + 128];                          // phase 2: [wave][32][32] partial tiles, [wave][32] of the biases
-    __shared__ float bs[FT_MAXDEPTH][W];                        // hidden biases of this step
+    __shared__ float dact[D][FT_R][W + 4];                      // derivatives of the activations (each lane's own)
+    __shared__ float bs[D][W];                                  // hidden biases of this step
     __shared__ float wos[W + 1];                                // output weights and bias
-    __shared__ float dys[FT_R], tgs[FT_R], sq[FT_R], corr[2];
+    __shared__ float dys[FT_R], tgs[FT_R], sq[FT_R], corr[3];
     __shared__ __attribute__((aligned(16))) float red[256];
+    __shared__ __attribute__((aligned(16))) bf16 wq[32 * 40];   // phase 2: the item's new weights, rows 80 bytes apart
+    // Moments and masters of the block's phase-2 item (four weights per thread; its
+    // biases).  Where no block has two items they stay here from the first step
+    // of the launch to the last.
+    __shared__ float held[12][256], heldb[3][32];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t M = a.M;
     const int nrt = (int)(M / FT_R);
     // B fragments: bw0 the first layer's (one k-step); the products after it
     // alternate between bwa (odd) and bwb (even), and the weights of product
     // k + 2 are loaded into a buffer as soon as product k has used it, so
-    // every load has a whole layer's work to arrive
+    // every load has a whole layer's work to arrive.  The depth is a constant:
+    // loads under a condition cannot be counted, and the first layer's
+    // would be waited for with all that were issued after them.
     bf16x8 bw0[8][4], bwa[8][4], bwb[8][4];
-    // Masters and moments of this thread's four weights of the block's phase-2
-    // item.  Where no block has two items they stay here from the first step
-    // of the launch to the last.
-    float mo[4], vo[4], th[4];
-    bool first_in_lds = false;   // the step's first tile is already in Hs / tgs
     for (int st = 0; st < a.nsteps; ++st) {
         // Offsets are formed in each step and phase: kept from step to step they
         // spill, and after a grid barrier a spilled value comes from memory.
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         int lane = tid & 63, li = lane & 15, lg = lane >> 4;
-        float* loss = a.loss ? a.loss + st : nullptr;
-        const float lr = a.lrs ? a.lrs[st] : a.lr;
         float loss_acc = 0.f;
-        float bv[FT_MAXDEPTH], wv = a.theta[a.wout_off + tid], wb = a.theta[a.bout_off];
+        float bv[D], wv = a.theta[a.wout_off + tid], wb = a.theta[a.bout_off];
 #pragma unroll
-        for (int l = 0; l < FT_MAXDEPTH; ++l) bv[l] = l < a.depth ? a.theta[a.L.b_off[l] + tid] : 0.f;
+        for (int l = 0; l < D; ++l) bv[l] = a.theta[a.L.b_off[l] + tid];
 
         // ---------------- phase 1: rows through forward and backward ----------------
+        if (st == 0 && (int)blockIdx.x < nrt) ft_rows<256>(a, st, (int64_t)blockIdx.x * FT_R, tid, Hs[0], tgs);
         for (int rt = blockIdx.x; rt < nrt; rt += gridDim.x) {
             const int64_t m0 = (int64_t)rt * FT_R;
-            const bf16* const* wfr = a.wfr;
-            const bf16* const* wtfr = a.wtfr;
-            ft_load_w<MLP_KPAD>(wfr[0], wave, lane, bw0);
-            if (const bf16* w1 = ft_chain_w(wfr, wtfr, a.depth, 1)) ft_load_w<W>(w1, wave, lane, bwa);
-            if (const bf16* w2 = ft_chain_w(wfr, wtfr, a.depth, 2)) ft_load_w<W>(w2, wave, lane, bwb);
-            if (rt == (int)blockIdx.x) {
+            ft_load_w<MLP_KPAD>(a.wfr[0], wave, lane, bw0);
+            ft_load_chain<D, 1>(a, wave, lane, bwa);
+            ft_load_chain<D, 2>(a, wave, lane, bwb);
+            // (for every tile: under a condition, all the loads above would be waited for)
 #pragma unroll
-                for (int l = 0; l < FT_MAXDEPTH; ++l) bs[l][tid] = bv[l];
-                wos[tid] = wv;
-                if (tid == 0) wos[W] = wb;
-            }
-            if (!(first_in_lds && rt == (int)blockIdx.x)) {
-                ft_rows g;
-                ft_rows_load(a, st, m0, tid, g);
-                ft_rows_store(g, tid, Hs[0], tgs);
-            }
+            for (int l = 0; l < D; ++l) bs[l][tid] = bv[l];
+            wos[tid] = wv;
+            wos[W] = wb;
             __syncthreads();
             if (tid < MLP_KPAD) ft_store_t(Hs[0], tid, a.XT, M, m0);
             // A lane's elements of a layer: columns 64 wave + 16 t + li of rows 4 lg + v,
-            // the same in every layer and in both directions, so the activations'
-            // derivatives stay in registers.
-            float dact[FT_MAXDEPTH][4][4];
-#pragma unroll
-            for (int l = 0; l < FT_MAXDEPTH; ++l) {
-                if (l >= a.depth) break;
+            // the same in every layer and in both directions.
+            ft_each<D>([&](auto LL) __attribute__((always_inline)) {
+                constexpr int l = LL;
                 f32x4 acc[4];
-                if (l == 0) {
+                if constexpr (l == 0) {
                     ft_mma<MLP_KPAD>(Hs[0], bw0, li, lg, acc);
-                } else if (l & 1) {  // product l
-                    ft_mma<W>(Hs[l & 1], bwa, li, lg, acc);
-                    if (const bf16* wn = ft_chain_w(wfr, wtfr, a.depth, l + 2)) ft_load_w<W>(wn, wave, lane, bwa);
+                } else if constexpr (l & 1) {  // product l
+                    ft_mma<W>(Hs[1], bwa, li, lg, acc);
+                    ft_load_chain<D, l + 2>(a, wave, lane, bwa);
                 } else {
-                    ft_mma<W>(Hs[l & 1], bwb, li, lg, acc);
-                    if (const bf16* wn = ft_chain_w(wfr, wtfr, a.depth, l + 2)) ft_load_w<W>(wn, wave, lane, bwb);
+                    ft_mma<W>(Hs[0], bwb, li, lg, acc);
+                    ft_load_chain<D, l + 2>(a, wave, lane, bwb);
                 }
                 bf16* out = Hs[(l + 1) & 1];
 #pragma unroll
@@ -764,14 +782,14 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
                         const float z = acc[t][v] + bc;
                         const float s = sigmoidf_(z);
                         h[v] = (bf16)(z * s);
-                        dact[l][t][v] = s * (1.f + z * (1.f - s));
+                        dact[l][4 * lg + v][c] = s * (1.f + z * (1.f - s));
                         out[(4 * lg + v) * P + c] = h[v];
                     }
-                    if (l + 1 < a.depth) ft_store4(h, 4 * wave + t, li, lg, a.HT[l], M, m0);
+                    if constexpr (l + 1 < D) ft_store4(h, 4 * wave + t, li, lg, a.HT[l], M, m0);
                 }
                 __syncthreads();
-            }
-            const bf16* hl = Hs[a.depth & 1];
+            });
+            const bf16* hl = Hs[D & 1];
             // output layer, residual, loss (16 threads per row)
             {
                 const int r = tid >> 4, q16 = tid & 15;
@@ -806,35 +824,29 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
             }
             // dZ of the last hidden layer
 #pragma unroll
-            for (int l = 0; l < FT_MAXDEPTH; ++l) {
-                if (l != a.depth - 1) continue;
+            for (int t = 0; t < 4; ++t) {
+                const int c = 64 * wave + 16 * t + li;
+                const float woc = wos[c];
+                bf16x4 g;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int c = 64 * wave + 16 * t + li;
-                    const float woc = wos[c];
-                    bf16x4 g;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        g[v] = (bf16)(dys[4 * lg + v] * woc * dact[l][t][v]);
-                        Gs[0][(4 * lg + v) * P + c] = g[v];
-                    }
-                    ft_store4(g, 4 * wave + t, li, lg, a.DZT[l], M, m0);
+                for (int v = 0; v < 4; ++v) {
+                    g[v] = (bf16)(dys[4 * lg + v] * woc * dact[D - 1][4 * lg + v][c]);
+                    Gs[0][(4 * lg + v) * P + c] = g[v];
                 }
+                ft_store4(g, 4 * wave + t, li, lg, a.DZT[D - 1], M, m0);
             }
             __syncthreads();
             // backward through the hidden layers: dZ_{l-1} = (dZ_l W_l) silu'(Z_{l-1})
-            // (product 2 depth - 1 - l: bwa when l is even)
-#pragma unroll
-            for (int l = FT_MAXDEPTH - 1; l >= 1; --l) {
-                if (l >= a.depth) continue;
+            // (product 2 D - 1 - l: bwa when l is even)
+            ft_each<D - 1>([&](auto II) __attribute__((always_inline)) {
+                constexpr int l = D - 1 - II, k = 2 * D - 1 - l, in = II & 1;
                 f32x4 acc[4];
-                const int k = 2 * a.depth - 1 - l, in = (a.depth - 1 - l) & 1;
-                if ((l & 1) == 0) {
+                if constexpr ((l & 1) == 0) {
                     ft_mma<W>(Gs[in], bwa, li, lg, acc);
-                    if (const bf16* wn = ft_chain_w(wfr, wtfr, a.depth, k + 2)) ft_load_w<W>(wn, wave, lane, bwa);
+                    ft_load_chain<D, k + 2>(a, wave, lane, bwa);
                 } else {
                     ft_mma<W>(Gs[in], bwb, li, lg, acc);
-                    if (const bf16* wn = ft_chain_w(wfr, wtfr, a.depth, k + 2)) ft_load_w<W>(wn, wave, lane, bwb);
+                    ft_load_chain<D, k + 2>(a, wave, lane, bwb);
                 }
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
@@ -842,13 +854,15 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
                     bf16x4 g;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        g[v] = (bf16)(acc[t][v] * dact[l - 1][t][v]);
+                        g[v] = (bf16)(acc[t][v] * dact[l - 1][4 * lg + v][c]);
                         Gs[1 - in][(4 * lg + v) * P + c] = g[v];
                     }
                     ft_store4(g, 4 * wave + t, li, lg, a.DZT[l - 1], M, m0);
                 }
                 __syncthreads();
-            }
+            });
+            const int next = rt + (int)gridDim.x;
+            if (next < nrt) ft_rows<256>(a, st, (int64_t)next * FT_R, tid, Hs[0], tgs);
         }
         if ((tid & 15) == 0) sq[tid >> 4] = loss_acc;  // the threads that hold any
         __syncthreads();
@@ -858,23 +872,25 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
             for (int i = 0; i < FT_R; ++i) s += sq[i];
             a.lossp[blockIdx.x] = s;
         }
-        ft_grid_sync(a.bar, [&]() {
-            const float k = (float)(a.step0 + st + 1);
-            const float c1 = a.lrs ? 1.f - powf(0.9f, k) : a.c1, c2 = a.lrs ? 1.f - powf(0.999f, k) : a.c2;
-            if (lane == 0) corr[0] = c1, corr[1] = c2;
+        // during the wait: the update's constants, and the next step's first tile
+        const bool pre = st + 1 < a.nsteps && (int)blockIdx.x < nrt;
+        ft_grid_sync(a.bar, [&]() __attribute__((always_inline)) {
+            if (wave == 1) {
+                const float k = (float)(a.step0 + st + 1);
+                const float c1 = a.lrs ? 1.f - powf(0.9f, k) : a.c1, c2 = a.lrs ? 1.f - powf(0.999f, k) : a.c2;
+                const float lr = a.lrs ? a.lrs[st] : a.lr;
+                if (lane == 0) corr[0] = c1, corr[1] = c2, corr[2] = lr;
+            }
+            if (pre) ft_rows<192>(a, st + 1, (int64_t)blockIdx.x * FT_R, tid - 64, Hs[0], tgs);
         });
-        const float c1 = corr[0], c2 = corr[1];
+
+        // ---------------- phase 2: weight gradients and the update ----------------
+        const float c1 = corr[0], c2 = corr[1], lr = corr[2];
         tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         lane = tid & 63, li = lane & 15, lg = lane >> 4;
-
-        // ---------------- phase 2: weight gradients and the update ----------------
-        // the next step's first tile, loaded across this phase and the barrier
-        ft_rows nxt;
-        const bool pre = st + 1 < a.nsteps && (int)blockIdx.x < nrt;
-        if (pre) ft_rows_load(a, st + 1, (int64_t)blockIdx.x * FT_R, tid, nxt);
         // the loss, by the last block (which seldom has an item), added in block order
-        if (blockIdx.x == gridDim.x - 1 && loss) {
+        if (blockIdx.x == gridDim.x - 1 && a.loss) {
             float s = 0.f;
             for (int o = 0; o < (int)gridDim.x; o += 256) {
                 __syncthreads();
@@ -888,57 +904,39 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
                     }
                 }
             }
-            if (tid == 0) loss[0] = s / (float)M;
+            if (tid == 0) a.loss[st] = s / (float)M;
         }
         // items: per layer l, 8 x (padded fan-in / 32) tiles of 32 x 32 of dW_l
         // (n-tile major), then eight output-layer items
-        int nw = 0;
-        for (int l = 0; l < a.depth; ++l) nw += 8 * (((l == 0) ? MLP_KPAD : W) / 32);
-        const int nitems = nw + 8;
+        constexpr int nw = 8 + 64 * (D - 1), nitems = nw + 8;
         // Items that share operand rows are neighbours in this order; blocks go
         // round-robin over the 8 XCDs, so slot v of XCD x takes item x q + v:
         // each XCD's L2 then fetches about an eighth of the operands instead
         // of nearly all of them.
-        const int q8 = (nitems + 7) / 8;
-        const bool hold = 8 * q8 <= (int)gridDim.x, last = st + 1 == a.nsteps;
+        constexpr int q8 = (nitems + 7) / 8;
+        const bool hold = 8 * q8 <= (int)gridDim.x, last = st + 1 == a.nsteps, fresh = !hold || st == 0;
         for (int vb = blockIdx.x; vb < 8 * q8; vb += gridDim.x) {
             const int it = (vb % 8) * q8 + vb / 8;
             if (it >= nitems) continue;
             if (it >= nw) {
                 // output layer, columns 32 oq .. 32 oq + 31 (the last item also takes
-                // the bias): eight threads per column add the per-tile partials in a
-                // fixed interleave, combine them by shuffles and update
+                // the bias, in wave 0's first lanes' second sum): eight threads per
+                // column add the per-tile partials in a fixed interleave, combine them
+                // by shuffles and update
                 const int oq = it - nw;
                 const int c = 32 * oq + (tid >> 3), q = tid & 7;
-                const float* src = a.opart + (int64_t)c * nrt;
-                float g = 0.f;
-#pragma unroll 32
-                for (int i = q; i < nrt; i += 8) g += src[i];
-                g += __shfl_xor(g, 1);
-                g += __shfl_xor(g, 2);
-                g += __shfl_xor(g, 4);
+                const float g = ft_sum8(a.opart + (int64_t)c * nrt, nrt, q);
                 if (q == 0) ft_update(a, a.wout_off + c, g, lr, c1, c2);
                 if (oq == 7 && wave == 0) {
-                    const float* sb = a.opart + (int64_t)W * nrt;
-                    float d = 0.f;
-#pragma unroll 32
-                    for (int i = lane & 7; i < nrt; i += 8) d += sb[i];
-                    d += __shfl_xor(d, 1);
-                    d += __shfl_xor(d, 2);
-                    d += __shfl_xor(d, 4);
+                    const float d = ft_sum8(a.opart + (int64_t)W * nrt, nrt, q);
                     if (lane == 0) ft_update(a, a.bout_off, d, lr, c1, c2);
                 }
                 continue;
             }
-            int l = 0, j = it;
-            for (; l < a.depth; ++l) {
-                const int nl = 8 * (((l == 0) ? MLP_KPAD : W) / 32);
-                if (j < nl) break;
-                j -= nl;
-            }
-            const int kt = ((l == 0) ? MLP_KPAD : W) / 32;
+            const int l = it < 8 ? 0 : 1 + (it - 8) / 64, j = it < 8 ? it : (it - 8) % 64;
+            const int kt = l == 0 ? 1 : 8;
             const int nb = j / kt, kb = j % kt;
-            const int fi = a.L.fan_in[l], ld = (l == 0) ? MLP_KPAD : fi;
+            const int fi = l == 0 ? a.n_in : W, ld = l == 0 ? MLP_KPAD : W;
             // operands in fragment order: the fragment of 16-row tile f at batch
             // step m / 32 starts at (f (M / 32) + m / 32) 512
             const bf16* A = a.DZT[l];                       // dZ_l^T [n][m]
@@ -947,9 +945,10 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
             const bf16* Br[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                Ar[i] = A + (int64_t)(2 * nb + i) * (M >> 5) * 512 + lane * 8;
-                Br[i] = B + (int64_t)(2 * kb + i) * (M >> 5) * 512 + lane * 8;
+                Ar[i] = A + (int64_t)(2 * nb + i) * (M >> 5) * 512;
+                Br[i] = B + (int64_t)(2 * kb + i) * (M >> 5) * 512;
             }
+            const int lane8 = lane * 8;
             f32x4 acc[2][2];
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -976,8 +975,8 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
                 for (int u = 0; u < U; ++u)
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
-                        av[u][i] = *reinterpret_cast<const bf16x8*>(Ar[i] + 16 * (m + 32 * u));
-                        bv[u][i] = *reinterpret_cast<const bf16x8*>(Br[i] + 16 * (m + 32 * u));
+                        av[u][i] = *reinterpret_cast<const bf16x8*>(Ar[i] + 16 * (m + 32 * u) + lane8);
+                        bv[u][i] = *reinterpret_cast<const bf16x8*>(Br[i] + 16 * (m + 32 * u) + lane8);
                     }
 #pragma unroll
                 for (int u = 0; u < U; ++u) mstep(av[u], bv[u]);
@@ -986,8 +985,8 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
                 bf16x8 av[2], bv[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    av[i] = *reinterpret_cast<const bf16x8*>(Ar[i] + 16 * m);
-                    bv[i] = *reinterpret_cast<const bf16x8*>(Br[i] + 16 * m);
+                    av[i] = *reinterpret_cast<const bf16x8*>(Ar[i] + 16 * m + lane8);
+                    bv[i] = *reinterpret_cast<const bf16x8*>(Br[i] + 16 * m + lane8);
                 }
                 mstep(av, bv);
             }
@@ -1004,55 +1003,88 @@ __global__ __launch_bounds__(256, 1) void k_mlp_train_fused(ft_args a) {
                 bsum[i] += __shfl_xor(bsum[i], 32);
                 if (lg == 0) part[4096 + wave * 32 + 16 * i + li] = bsum[i];
             }
+            // four of the tile's 1024 weights per thread, 8 rows apart: element tid + 256 r
+            const int n0 = tid >> 5, kk = 32 * kb + (tid & 31);
+            const int64_t i0 = a.L.w_off[l] + (int64_t)(32 * nb + n0) * fi + kk, ib = a.L.b_off[l] + 32 * nb + tid;
+            const bool mine = kk < fi, bias = kb == 0 && tid < 32;
+            if (fresh && !a.grad_out) {
+                float x[12];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int64_t i = mine ? i0 + (int64_t)(8 * r) * fi : a.L.w_off[l];
+                    x[r] = a.m[i], x[4 + r] = a.v[i], x[8 + r] = a.theta[i];
+                }
+#pragma unroll
+                for (int r = 0; r < 12; ++r) held[r][tid] = x[r];
+                if (bias) heldb[0][tid] = a.m[ib], heldb[1][tid] = a.v[ib], heldb[2][tid] = a.theta[ib];
+            }
             __syncthreads();
-            // the four quarters added in wave order, then four of the tile's 1024
-            // weights per thread (every load first)
+            // the four quarters added in wave order
             float g[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int e = tid + 256 * r, n = e >> 5, k = e & 31;
-                g[r] = ((part[n * 32 + k] + part[(32 + n) * 32 + k]) + part[(64 + n) * 32 + k]) + part[(96 + n) * 32 + k];
-                const int64_t i = a.L.w_off[l] + (int64_t)(32 * nb + n) * fi + 32 * kb + k;
-                if ((!hold || st == 0) && 32 * kb + k < fi && !a.grad_out) {
-                    mo[r] = a.m[i];
-                    vo[r] = a.v[i];
-                    th[r] = a.theta[i];
-                }
+                const int e = tid + 256 * r;
+                g[r] = ((part[e] + part[1024 + e]) + part[2048 + e]) + part[3072 + e];
             }
+            if (a.grad_out) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int e = tid + 256 * r, n = e >> 5, k = e & 31;
-                const int rr = 32 * nb + n, kk = 32 * kb + k;
-                if (kk >= fi) continue;
-                const int64_t i = a.L.w_off[l] + (int64_t)rr * fi + kk;
-                if (a.grad_out) {
-                    a.grad_out[i] = g[r];
-                    continue;
-                }
-                ft_adam(g[r], mo[r], vo[r], th[r], lr, c1, c2);
-                if (!hold || last) {
-                    a.m[i] = mo[r];
-                    a.v[i] = vo[r];
-                    a.theta[i] = th[r];
-                }
-                // the fragment-order copies feed the next step; the row-major
-                // ones only other kernels, so they are written by the last step
-                const bf16 wq = (bf16)th[r];
-                a.wfr[l][frag_off(rr, kk, ld)] = wq;
-                if (last) a.wbf[l][rr * ld + kk] = wq;
-                if (l > 0) {
-                    a.wtfr[l][frag_off(kk, rr, W)] = wq;
-                    if (last) a.wbft[l][kk * W + rr] = wq;
+                for (int r = 0; r < 4; ++r)
+                    if (mine) a.grad_out[i0 + (int64_t)(8 * r) * fi] = g[r];
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float mo = held[r][tid], vo = held[4 + r][tid], th = held[8 + r][tid];
+                    ft_adam(g[r], mo, vo, th, lr, c1, c2);
+                    held[r][tid] = mo, held[4 + r][tid] = vo, held[8 + r][tid] = th;
+                    wq[(n0 + 8 * r) * 40 + (tid & 31)] = mine ? (bf16)th : (bf16)0.f;
                 }
             }
-            if (kb == 0 && tid < 32) {
+            if (bias) {
                 const float gb = ((part[4096 + tid] + part[4096 + 32 + tid]) + part[4096 + 64 + tid]) + part[4096 + 96 + tid];
-                ft_update(a, a.L.b_off[l] + 32 * nb + tid, gb, lr, c1, c2);
+                if (a.grad_out) {
+                    a.grad_out[ib] = gb;
+                } else {
+                    float mo = heldb[0][tid], vo = heldb[1][tid], th = heldb[2][tid];
+                    ft_adam(gb, mo, vo, th, lr, c1, c2);
+                    heldb[0][tid] = mo, heldb[1][tid] = vo, heldb[2][tid] = th;
+                    a.theta[ib] = th;
+                    if (!hold || last) a.m[ib] = mo, a.v[ib] = vo;
+                }
             }
-            __syncthreads();  // part is rewritten by the next item
+            __syncthreads();  // wq is complete; part is rewritten by the next item
+            if (!a.grad_out) {
+                // The fragment-order copies feed the next step: lane f of fragment (n, k)
+                // holds columns 8 (f / 16) .. + 7 of row f % 16, one 16-byte store per
+                // thread, the first half of the block W, the second W^T.
+                const int half = tid >> 7, t16 = (tid >> 6) & 1;
+                if (half == 0) {
+                    const bf16x8 v = *reinterpret_cast<const bf16x8*>(wq + (16 * t16 + li) * 40 + 8 * lg);
+                    *reinterpret_cast<bf16x8*>(a.wfr[l] + ((int64_t)((2 * nb + t16) * (ld >> 5) + kb) * 64 + lane) * 8) = v;
+                } else if (l > 0) {
+                    bf16x8 v;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) v[q] = wq[(8 * lg + q) * 40 + 16 * t16 + li];
+                    *reinterpret_cast<bf16x8*>(a.wtfr[l] + ((int64_t)((2 * kb + t16) * (W >> 5) + nb) * 64 + lane) * 8) = v;
+                }
+                if (!hold || last) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int64_t i = i0 + (int64_t)(8 * r) * fi;
+                        if (mine) a.m[i] = held[r][tid], a.v[i] = held[4 + r][tid], a.theta[i] = held[8 + r][tid];
+                    }
+                }
+                // the row-major copies feed only other kernels
+                if (last) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int rr = 32 * nb + n0 + 8 * r;
+                        const bf16 v = wq[(n0 + 8 * r) * 40 + (tid & 31)];
+                        if (mine) a.wbf[l][rr * ld + kk] = v;
+                        if (mine && l > 0) a.wbft[l][kk * W + rr] = v;
+                    }
+                }
+            }
         }
-        if (pre) ft_rows_store(nxt, tid, Hs[0], tgs);
-        first_in_lds = pre;
         if (st + 1 < a.nsteps) ft_grid_sync(a.bar, []() {});  // the next step reads the updated weights
     }
 }
@@ -1073,6 +1105,12 @@ __global__ void k_features(const double* __restrict__ mom, int64_t n, int npart,
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
+
+static void (*ft_kernel(int depth))(ft_args) {
+    static_assert(FT_MAXDEPTH == 4, "one kernel per depth");
+    return depth == 1 ? k_mlp_train_fused<1> : depth == 2 ? k_mlp_train_fused<2>
+         : depth == 3 ? k_mlp_train_fused<3> : k_mlp_train_fused<4>;
+}
 
 struct me_mlp {
     int n_in, width, depth;
@@ -1357,7 +1395,7 @@ int mlp_create(int n_in, int width, int depth, uint64_t seed, me_mlp** out) {
             return me_fail(ME_EDEVICE, "mlp_create: device allocation");
         int dev = 0, cus = 0, per = 0;
         if (bad(hipGetDevice(&dev)) || bad(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) ||
-            bad(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_mlp_train_fused, 256, 0)))
+            bad(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, ft_kernel(depth), 256, 0)))
             return me_fail(ME_EDEVICE, "mlp_create: occupancy query");
         p->fgrid = cus * per;
         if (p->fgrid < 1) p->fused = false;
@@ -1530,7 +1568,7 @@ static int fused_step(me_mlp* p, const float* x, const float* t, const int32_t* 
         a.c1 = a.c2 = 1.f;
     }
     void* args[] = {&a};
-    HCHK(hipLaunchCooperativeKernel((const void*)k_mlp_train_fused, dim3((unsigned)p->fgrid), dim3(256), args, 0, s));
+    HCHK(hipLaunchCooperativeKernel((const void*)ft_kernel(p->depth), dim3((unsigned)p->fgrid), dim3(256), args, 0, s));
     return ME_OK;
 }
 
