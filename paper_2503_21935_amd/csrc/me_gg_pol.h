@@ -269,7 +269,7 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
 #pragma unroll 1
     for (int s4 = 0; s4 < 2; ++s4) {
         int l4 = l;
-        if constexpr (MC) asm volatile("" : "+v"(l4));
+        asm volatile("" : "+v"(l4));
         // rows from p4: R(c), and W(b) R(c) + W(bc) v as r(c) slash(b) + r0 slash W(bc)
         const row r0 = ld8(D + N0 + 16 + 8 * s4);
         row r1[3], r2[3][2], rw[3];
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
         each<3>([&](auto C) __attribute__((always_inline)) {
             each<2>([&](auto H) __attribute__((always_inline)) {  // b: the H-th gluon other than C
                 constexpr int b = H < C ? H : H + 1, p = b + C - 1;
-                const row t = slash(r1[C], MC ? ld4(D + EPS + 8 * b + 4 * bit(l4, b)) : eps[b]);
+                const row t = slash(r1[C], ld4(D + EPS + 8 * b + 4 * bit(l4, b)));
                 const double sg = b < C ? 1.0 : -1.0;
                 if constexpr (MC)
                     r2[C][H] = t;

@@ -301,6 +301,7 @@ __global__ __launch_bounds__(64, 2) void k_me_qew_pol(const double* __restrict__
                         cut(T[k], l1, r2);
                         cut(T[k], l2, R1[C]);
                         cut(T[k], l3, R0);
+                        settle(T[k].t);
                     }
                 }
             });
