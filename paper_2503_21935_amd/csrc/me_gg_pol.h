@@ -11,14 +11,38 @@
 // polarisations and the four spin pairs.
 //   J_abc = L(a) [W(b) R(c) + W(bc) v] + ubar W(ab) R(c) + ubar W(abc) v.
 //
-// Both are bound by VALU issue (2,900 vector instructions per wave of 64 events
-// and 2,600 per wave of eight).  Against one helicity per pass over the diagram program
-// (k_me_gg): 2^20 events of g g -> t tbar take 110 us against 521 us, 2^18
+// Both are bound by VALU issue (2,600 vector instructions per wave of 64 events
+// and of eight).  Against one helicity per pass over the diagram program
+// (k_me_gg): 2^20 events of g g -> t tbar take 92 us against 521 us, 2^18
 // events of g g -> t tbar g 0.30 ms against 2.7 ms; with the weights of the
-// events' channels 2^19 events of g g -> t tbar 74 us against 316 us, 2^17 events
+// events' channels 2^19 events of g g -> t tbar 65 us against 316 us, 2^17 events
 // of g g -> t tbar g 0.24 ms against 0.55 ms (k_me_gg_mc).
 #pragma once
 #include "me_qew_pol.h"
+
+namespace g2 {
+
+using namespace wv;
+
+// f (gamma.e) for a polarisation vector: no time component, e2 none along z.
+template <bool E2>
+MEV row slash_e(const row& f, const vec& e) {
+    const c2 c{e.v[1], e.v[2]}, d{e.v[1], -e.v[2]};
+    if constexpr (E2) return {{f.s[3] * c, f.s[2] * d, f.s[1] * -c, f.s[0] * -d}};
+    const double z = e.v[3];
+    return {{axpy(z, f.s[2], f.s[3] * c), axpy(-z, f.s[3], f.s[2] * d), axpy(-z, f.s[0], f.s[1] * -c),
+             axpy(z, f.s[1], f.s[0] * -d)}};
+}
+// f gamma_mu R for mu = 1, 2, 3, R held as the row r, dotted with e1 and e2
+MEV void currents_e(const row& f, const row& r, const vec& e1, const vec& e2, c2& d1, c2& d2) {
+    const c2 u = cfma(f.s[2], r.s[0], f.s[0] * r.s[2]), v = cfma(f.s[3], r.s[1], f.s[1] * r.s[3]);
+    const c2 x = u - v, y = times_mi(u + v);
+    const c2 z = cfma(f.s[3], r.s[0], cfma(f.s[2], r.s[1], cfma(f.s[1], r.s[2], f.s[0] * r.s[3])));
+    d1 = axpy(-e1.v[3], z, axpy(e1.v[2], y, rmul(e1.v[1], x)));
+    d2 = axpy(e2.v[2], y, rmul(e2.v[1], x));
+}
+
+}  // namespace g2
 
 // idx, count and spins as for k_me_gg4_wave.  With IDS (the channel numbers of
 // the diagrams) also the single-diagram weight of each event's channel, as k_me_gg4_chan.
@@ -28,7 +52,7 @@ __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__
                                                       const int* __restrict__ idx, const int* __restrict__ count,
                                                       const int* __restrict__ chan = nullptr,
                                                       double* __restrict__ alpha = nullptr) {
-    using namespace wv;
+    using namespace g2;
     static_assert(P::ngluon == 2 && P::ncol == 2, "two gluons");
     int64_t ev = (int64_t)blockIdx.x * 64 + threadIdx.x;
     if (count) {
@@ -78,14 +102,16 @@ __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__
             w[PP] = mul(iq, t);
         });
     }
-    // Spin by spin: the rows L of all sixteen at once, and those of the other end,
-    // do not fit in registers (2^20 events took 126 us); slashing the latter anew costs less (110 us).
+    // Spin by spin: the rows L of all sixteen at once do not fit in registers (2^20
+    // events took 126 us).  The other end enters through the current of L with it,
+    // which both polarisations of the second gluon share (92 us; 110 with the
+    // end's rows slashed by each of them).
     double acc = 0.0;
     each<2>([&](auto S3) __attribute__((always_inline)) {
         settle(n4[0].s), settle(n4[1].s);  // what is formed from them is not kept for the other spin
         row L[2][2];  // L(a) up to the sign, by gluon and polarisation
         each<4>([&](auto I) __attribute__((always_inline)) {
-            L[I / 2][I % 2] = scale(f[I / 2], slash_m(slash(n3[S3], e[I / 2][I % 2]), K[I / 2], m));
+            L[I / 2][I % 2] = scale(f[I / 2], slash_m(slash_e<I % 2>(n3[S3], e[I / 2][I % 2]), K[I / 2], m));
         });
         each<2>([&](auto S4) __attribute__((always_inline)) {
             c2 t[4], J01[4], J10[4];  // by polarisations
@@ -94,18 +120,15 @@ __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__
                 each<4>([&](auto PP) __attribute__((always_inline)) { t[PP] = cdot(V, w[PP]); });
                 settle(t);
             }
-            each<2>([&](auto B) __attribute__((always_inline)) {
-                const row x = slash(n4[S4], e[1][B]), y = slash(n4[S4], e[0][B]);
-                each<2>([&](auto A) __attribute__((always_inline)) {
-                    J01[A + 2 * B] = wedge(L[0][A], x, c2{0.0, 0.0});
-                    J10[B + 2 * A] = wedge(L[1][A], y, c2{0.0, 0.0});
-                });
+            each<2>([&](auto A) __attribute__((always_inline)) {
+                currents_e(L[0][A], n4[S4], e[1][0], e[1][1], J01[A], J01[A + 2]);
+                currents_e(L[1][A], n4[S4], e[0][0], e[0][1], J10[2 * A], J10[1 + 2 * A]);
             });
             settle(J01), settle(J10);
             double part = 0.0;
             each<4>([&](auto PP) __attribute__((always_inline)) {
                 if constexpr (MC) found(IDS::tree[0], t[PP]), found(IDS::order[0], J01[PP]), found(IDS::order[1], J10[PP]);
-                c2 J[2] = {J01[PP] + t[PP], J10[PP] - t[PP]};
+                c2 J[2] = {J01[PP] - t[PP], J10[PP] + t[PP]};  // (both with the sign of L)
                 part += P::colour_blocks(J);
             });
             acc += ((spins >> (S3 + 2 * S4)) & 1) ? part : 0.0;
