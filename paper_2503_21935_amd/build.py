@@ -79,7 +79,7 @@ static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, c
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_QEW, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, nullptr, 8.0,
-    0.0, nullptr, nullptr, 0, nullptr, launch_sum, nullptr}};
+    0.0, nullptr, nullptr, 0, nullptr, launch_sum, nullptr, false}};
 #endif
 """
 
@@ -107,7 +107,8 @@ static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, c
 extern const me_process_desc me_desc_{name} = {{
     "{name}", {kind}, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, {mixed_ptr}, {cest},
-    {colerr}, {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}, {chan_ptr}}};
+    {colerr}, {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}, {chan_ptr},
+    {mixed_part}}};
 #endif
 """
 
@@ -266,7 +267,7 @@ static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, c
 // translation units of their own
 hipError_t me_launch_mixed_{name}(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                   const me_params& prm, float tol, float cest, int* flag_count, int* flag_idx,
-                                  float* err_out, unsigned char* flag_out, hipStream_t s);
+                                  float* err_out, unsigned char* flag_out, float2* part, hipStream_t s);
 hipError_t me_launch_f64_cm_{name}(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                    const me_params& prm, double* qhel, int lg, hipStream_t s);
 hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, unsigned spins, const me_params& prm,
@@ -274,7 +275,7 @@ hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, un
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_GG, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, me_launch_mixed_{name}, {cest},
-    {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}, nullptr}};
+    {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}, nullptr, false}};
 #endif
 """
 
@@ -297,7 +298,7 @@ _TU_COOP_MIXED = """// Generated translation unit: mixed-precision kernel of {na
 
 hipError_t me_launch_mixed_{name}(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                   const me_params& prm, float tol, float cest, int* flag_count, int* flag_idx,
-                                  float* err_out, unsigned char* flag_out, hipStream_t s) {{
+                                  float* err_out, unsigned char* flag_out, float2*, hipStream_t s) {{
     if (flag_count) hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, s, flag_count);
     const dim3 grid((unsigned)((nevt + ME_TILE - 1) / ME_TILE));
     hipLaunchKernelGGL((k_me_gg_coop_mixed<{proc}>), grid, dim3(ME_TILE * {proc}::waves), 0, s, mom, nevt, out,
@@ -309,11 +310,16 @@ hipError_t me_launch_mixed_{name}(const double* mom, int64_t nevt, double* out, 
 _MIXED = """
 static hipError_t launch_mixed(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                const me_params& prm, float tol, float cest, int* flag_count, int* flag_idx,
-                               float* err_out, unsigned char* flag_out, hipStream_t s) {{
+                               float* err_out, unsigned char* flag_out, float2* part, hipStream_t s) {{
     if (flag_count) hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, s, flag_count);
-    const dim3 grid((unsigned)((nevt + ME_BLOCK - 1) / ME_BLOCK));
-    hipLaunchKernelGGL((k_me_gg_mixed<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, tol,
-                       cest, flag_count, flag_idx, err_out, flag_out);
+    const unsigned tiles = (unsigned)((nevt + ME_BLOCK - 1) / ME_BLOCK);
+    const int per = part ? mixed_per_block(nevt, nh) : nh;
+    if (per >= nh) part = nullptr;
+    hipLaunchKernelGGL((k_me_gg_mixed<{proc}>), dim3(tiles, part ? (unsigned)((nh + per - 1) / per) : 1u), dim3(ME_BLOCK),
+                       0, s, mom, nevt, out, hels, nh, prm, tol, cest, flag_count, flag_idx, err_out, flag_out, part, per);
+    if (part)
+        hipLaunchKernelGGL((k_mixed_sum<{proc}>), dim3(tiles), dim3(64), 0, s, part, nevt, nh, tol, cest, out, flag_count,
+                           flag_idx, err_out, flag_out);
     return hipGetLastError();
 }}
 """
@@ -394,7 +400,8 @@ def generate_sources(processes):
             tus.append(path_w)
         _write(path, _TU.format(name=name, include=inc, kernel=kernel, proc=proc, kind=kind, mixed=mixed,
                                 mixed_ptr=mixed_ptr, cest=MIXED_CEST.get(name, 8.0), colerr=colerr, cm=cm,
-                                cm_ptr=cm_ptr, mc_ptr=mc_ptr, mc_n=mc_n, mc_desc=mc_desc, sum_ptr=sum_ptr, chan_ptr=chan_ptr))
+                                cm_ptr=cm_ptr, mc_ptr=mc_ptr, mc_n=mc_n, mc_desc=mc_desc, sum_ptr=sum_ptr, chan_ptr=chan_ptr,
+                                mixed_part="false" if mixed_ptr == "nullptr" else "true"))
         tus.append(path)
     decls = "\n".join(f"extern const me_process_desc me_desc_{n};" for n in processes)
     ptrs = ", ".join(f"&me_desc_{n}" for n in processes)

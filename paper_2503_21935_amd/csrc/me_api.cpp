@@ -28,6 +28,12 @@ static int fail(int code, const std::string& msg) { return me_fail(code, msg); }
 
 // Grow the flagged-event index list to hold nevt entries (synchronises the
 // device when it has to reallocate).
+// With the index list, room for the helicities' values of as many events, at most
+// ME_PART_MAX bytes of it (2^18 events of 64 helicities; beyond, a few percent in
+// a last turn of blocks are not worth it).  Both grow in the same calls, so a
+// call that needed no allocation before needs none for these; without them
+// (no memory, or more events) the mixed form works all the same.
+#define ME_PART_MAX ((size_t)128 << 20)
 static int ensure_scratch(me_ctx* c, int64_t nevt) {
     if (!c->d_count) HIP_CHECK(hipMalloc(&c->d_count, sizeof(int)));
     if (nevt > c->idx_cap) {
@@ -35,9 +41,22 @@ static int ensure_scratch(me_ctx* c, int64_t nevt) {
             HIP_CHECK(hipDeviceSynchronize());
             HIP_CHECK(hipFree(c->d_idx));
             c->d_idx = nullptr;
+            c->idx_cap = 0;
         }
         HIP_CHECK(hipMalloc(&c->d_idx, nevt * sizeof(int)));
         c->idx_cap = nevt;
+        const size_t want = std::min((size_t)nevt * c->nhel_good, ME_PART_MAX / sizeof(float2));
+        if (c->proc->mixed_part && want > c->part_cap) {
+            if (c->d_part) HIP_CHECK(hipFree(c->d_part));  // the device is idle: synchronised above
+            c->d_part = nullptr;
+            c->part_cap = 0;
+            if (hipMalloc(&c->d_part, want * sizeof(float2)) == hipSuccess) {
+                c->part_cap = want;
+            } else {
+                c->d_part = nullptr;
+                (void)hipGetLastError();
+            }
+        }
     }
     return ME_OK;
 }
@@ -254,6 +273,8 @@ int me_init(const char* process, const double* couplings, int n_couplings, const
     c->d_count = nullptr;
     c->d_idx = nullptr;
     c->idx_cap = 0;
+    c->d_part = nullptr;
+    c->part_cap = 0;
     c->uw_x = nullptr;
     c->uw_y = nullptr;
     c->uw_s = nullptr;
@@ -294,7 +315,8 @@ int me_eval(me_ctx* c, const double* momenta, int64_t nevt, double* out_me2, voi
         int rc = ensure_scratch(c, nevt);
         if (rc != ME_OK) return rc;
         HIP_CHECK(c->proc->launch_mixed(momenta, nevt, out_me2, c->d_good, c->nhel_good, c->prm, (float)c->tol,
-                                        (float)c->proc->mixed_cest, c->d_count, c->d_idx, nullptr, nullptr, s));
+                                        (float)c->proc->mixed_cest, c->d_count, c->d_idx, nullptr, nullptr,
+                                        (size_t)nevt * c->nhel_good <= c->part_cap ? c->d_part : nullptr, s));
         // float64 rerun of the flagged events, in place, on the same stream
         HIP_CHECK(me_launch_idx(c, momenta, nevt, out_me2, c->d_idx, c->d_count, s));
         return ME_OK;
@@ -346,7 +368,7 @@ int me_eval_mixed_noalloc(me_ctx* c, const double* momenta, int64_t nevt, double
     int* d_idx = base + ME_SCRATCH_HEAD;
     // the mixed launch clears the counter with a kernel before it appends
     HIP_CHECK(c->proc->launch_mixed(momenta, nevt, out_me2, c->d_good, c->nhel_good, c->prm, (float)c->tol,
-                                    (float)c->proc->mixed_cest, d_count, d_idx, nullptr, nullptr, s));
+                                    (float)c->proc->mixed_cest, d_count, d_idx, nullptr, nullptr, nullptr, s));
     HIP_CHECK(me_launch_idx(c, momenta, nevt, out_me2, d_idx, d_count, s));
     return ME_OK;
 }
@@ -369,7 +391,7 @@ int me_eval_mixed_diag(me_ctx* c, const double* momenta, int64_t nevt, double* o
     if (nevt > 0x7fffffffLL) return fail(ME_EINVAL, "nevt above 2^31 - 1");
     HIP_CHECK(c->proc->launch_mixed(momenta, nevt, out_me2, c->d_good, c->nhel_good, c->prm, (float)c->tol,
                                     (float)c->proc->mixed_cest, nullptr, nullptr, out_err, out_flag,
-                                    (hipStream_t)stream));
+                                    nullptr, (hipStream_t)stream));
     return ME_OK;
 }
 
@@ -465,7 +487,7 @@ int me_good_helicities(const me_ctx* c, int* out, int* count) {
 int me_free(me_ctx* c) {
     if (!c) return ME_OK;
     hipError_t e = hipSuccess;
-    void* bufs[] = {c->d_good, c->d_all, c->d_count, c->d_idx, c->uw_x, c->uw_y, c->uw_s, c->uw_me2, c->uw_idx1};
+    void* bufs[] = {c->d_good, c->d_all, c->d_count, c->d_idx, c->d_part, c->uw_x, c->uw_y, c->uw_s, c->uw_me2, c->uw_idx1};
     for (void* b : bufs)
         if (b) {
             hipError_t r = hipFree(b);

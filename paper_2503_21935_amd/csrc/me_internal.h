@@ -32,6 +32,8 @@ struct me_ctx {
     int* d_count;
     int* d_idx;
     int64_t idx_cap;
+    float2* d_part;  // values per helicity and event (part of launch_mixed)
+    size_t part_cap;  // of them
     // scratch of two-stage unweighting
     float* uw_x;
     float* uw_y;

@@ -18,11 +18,12 @@ typedef hipError_t (*me_launch_idx_fn)(const double* mom, int64_t nevt, double* 
                                        hipStream_t stream);
 
 // Mixed-precision form: float32 amplitudes, float16 hi/lo MFMA colour sum,
-// per-event error estimate; flagged events appended to flag_idx.
+// per-event error estimate; flagged events appended to flag_idx.  part: room for
+// two floats per helicity and event, for blocks with a few helicities each, or null.
 typedef hipError_t (*me_launch_mixed_fn)(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                          const me_params& prm, float tol, float cest, int* flag_count,
                                          int* flag_idx, float* err_out, unsigned char* flag_out,
-                                         hipStream_t stream);
+                                         float2* part, hipStream_t stream);
 
 // Multi-channel form: |M|^2 and the single-diagram weight of each event's channel.
 typedef hipError_t (*me_launch_mc_fn)(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
@@ -69,6 +70,7 @@ struct me_process_desc {
     const char* const* chan_desc;     // their descriptors
     me_launch_sum_fn launch_sum;      // spin sum with one event per wave (nullptr: none)
     me_launch_chan_fn launch_chan;    // multi-channel form with shared wavefunctions (nullptr: none)
+    bool mixed_part;                  // launch_mixed makes use of `part`
 };
 
 const me_process_desc* me_find_process(const char* name);

@@ -197,60 +197,11 @@ MEV void externals_load(gg_ext<float, P::ngluon>& x, const float* E, int h) {
 // Mixed kernel: out = float32-form |M|^2 (as float64); events whose error
 // estimate exceeds tol are appended to flag_idx (wave-aggregated atomics on
 // *flag_count).  err_out / flag_out (optional) receive the estimate and the
-// decision per event.
+// decision per event.  From the sums over helicities of one event per lane:
 template <class P>
-__global__ __launch_bounds__(ME_BLOCK, ME_MIXED_WAVES) void k_me_gg_mixed(const double* __restrict__ mom, int64_t nevt,
-                                                          double* __restrict__ out, const int* __restrict__ hels,
-                                                          int nh, me_params prm, float tol, float cest,
-                                                          int* __restrict__ flag_count, int* __restrict__ flag_idx,
-                                                          float* __restrict__ err_out,
-                                                          unsigned char* __restrict__ flag_out) {
-    static_assert(ME_BLOCK == 64, "one wave per block");
-    __shared__ __attribute__((aligned(16))) char lds[mfma_colour<P::ncol>::LDS_BYTES];
-    const int lane = threadIdx.x;
-    int64_t ev = (int64_t)blockIdx.x * ME_BLOCK + lane;
-    const bool valid = ev < nevt;
-    if (!valid) ev = nevt - 1;  // every lane takes part in the wave-wide colour GEMM
-    using T = float;
-    constexpr int NG = P::ngluon;
-    __shared__ double Qt[ME_MOM_ROW(NG + 2)];
-    gg_ext<T, NG> x;
-    gg_setup<P, T>(x, mom, ev, Qt, lane, prm);
-    __shared__ float Et[ext_store<NG>::SIZE * 64];
-    externals_store<P>(x, Et + lane);
-    float acc = 0.f, dacc = 0.f;
-#pragma unroll 1
-    for (int ih = 0; ih < nh; ++ih) {
-        const int h = hels[ih];
-        externals_load<P>(x, Et + lane, h);
-        cx<T> J[P::ncol];
-        T S[P::ncol];
-#pragma unroll
-        for (int k = 0; k < P::ncol; ++k) {
-            J[k] = mk(T(0), T(0));
-            S[k] = T(0);
-        }
-        P::template amps_f32<T, true>(x, J, S);
-        float jn2 = 0.f, sn2 = 0.f;
-#pragma unroll
-        for (int k = 0; k < P::ncol; ++k) {
-            jn2 = fmaf(J[k].r, J[k].r, fmaf(J[k].i, J[k].i, jn2));
-            sn2 = fmaf(S[k], S[k], sn2);
-        }
-        constexpr float u32 = 5.9604645e-8f;  // 2^-24
-        if constexpr (mfma_colour<P::ncol>::enabled) {
-            // amplitude rounding: |dJ_k| ~ c u32 S_k, so |dQ| <= 2 c u32 sum_k S_k |Z_k|;
-            // colour GEMM: float16 hi+lo carries J to 2^-22 per element, float32
-            // accumulation adds ~sqrt(K) u32 |J|^T |N| |J|
-            float zs, zj;
-            acc += colour_sum_mfma<P>(J, S, lds, lane, zs, zj);
-            dacc += 2.f * cest * u32 * zs + 2.f * 2.3841858e-7f * zj +
-                    sqrtf(float(P::ncol)) * u32 * float(P::abs_lambda_max) * jn2;
-        } else {
-            acc += P::template colour_sum<T>(J);
-            dacc += 2.f * cest * u32 * float(P::abs_lambda_max) * sqrtf(jn2 * sn2);
-        }
-    }
+MEV void mixed_result(int64_t ev, bool valid, int lane, float acc, float dacc, float tol, double* __restrict__ out,
+                      int* __restrict__ flag_count, int* __restrict__ flag_idx, float* __restrict__ err_out,
+                      unsigned char* __restrict__ flag_out) {
     const double me2 = double(acc) * (1.0 / (256.0 * P::identical * P::lcd));
     const float est = dacc / acc;
     const bool flag = valid && !(est <= tol);  // NaN estimates are flagged too
@@ -273,6 +224,116 @@ __global__ __launch_bounds__(ME_BLOCK, ME_MIXED_WAVES) void k_me_gg_mixed(const 
             }
         }
     }
+}
+
+// What a helicity's second value is multiplied with as it enters dacc (exact
+// where it is 1).
+template <class P>
+MEV float mixed_weight(float cest) {
+    constexpr float u32 = 5.9604645e-8f;  // 2^-24
+    return mfma_colour<P::ncol>::enabled ? 1.f : 2.f * cest * u32 * float(P::abs_lambda_max);
+}
+
+// With part, block (x, y) leaves the two values of its `per` helicities in
+// part[ih][event], and k_mixed_sum adds them in the list's order, as one lane does
+// here: the same float32 sums.
+template <class P>
+__global__ __launch_bounds__(ME_BLOCK, ME_MIXED_WAVES) void k_me_gg_mixed(const double* __restrict__ mom, int64_t nevt,
+                                                          double* __restrict__ out, const int* __restrict__ hels,
+                                                          int nh, me_params prm, float tol, float cest,
+                                                          int* __restrict__ flag_count, int* __restrict__ flag_idx,
+                                                          float* __restrict__ err_out,
+                                                          unsigned char* __restrict__ flag_out,
+                                                          float2* __restrict__ part, int per) {
+    static_assert(ME_BLOCK == 64, "one wave per block");
+    __shared__ __attribute__((aligned(16))) char lds[mfma_colour<P::ncol>::LDS_BYTES];
+    const int lane = threadIdx.x;
+    int64_t ev = (int64_t)blockIdx.x * ME_BLOCK + lane;
+    const bool valid = ev < nevt;
+    if (!valid) ev = nevt - 1;  // every lane takes part in the wave-wide colour GEMM
+    using T = float;
+    constexpr int NG = P::ngluon;
+    __shared__ double Qt[ME_MOM_ROW(NG + 2)];
+    gg_ext<T, NG> x;
+    gg_setup<P, T>(x, mom, ev, Qt, lane, prm);
+    __shared__ float Et[ext_store<NG>::SIZE * 64];
+    externals_store<P>(x, Et + lane);
+    float acc = 0.f, dacc = 0.f;
+    const int first = part ? (int)blockIdx.y * per : 0, end = part ? (first + per < nh ? first + per : nh) : nh;
+#pragma unroll 1
+    for (int ih = first; ih < end; ++ih) {
+        const int h = hels[ih];
+        externals_load<P>(x, Et + lane, h);
+        cx<T> J[P::ncol];
+        T S[P::ncol];
+#pragma unroll
+        for (int k = 0; k < P::ncol; ++k) {
+            J[k] = mk(T(0), T(0));
+            S[k] = T(0);
+        }
+        P::template amps_f32<T, true>(x, J, S);
+        float jn2 = 0.f, sn2 = 0.f;
+#pragma unroll
+        for (int k = 0; k < P::ncol; ++k) {
+            jn2 = fmaf(J[k].r, J[k].r, fmaf(J[k].i, J[k].i, jn2));
+            sn2 = fmaf(S[k], S[k], sn2);
+        }
+        constexpr float u32 = 5.9604645e-8f;  // 2^-24
+        float q, d;
+        if constexpr (mfma_colour<P::ncol>::enabled) {
+            // amplitude rounding: |dJ_k| ~ c u32 S_k, so |dQ| <= 2 c u32 sum_k S_k |Z_k|;
+            // colour GEMM: float16 hi+lo carries J to 2^-22 per element, float32
+            // accumulation adds ~sqrt(K) u32 |J|^T |N| |J|
+            float zs, zj;
+            q = colour_sum_mfma<P>(J, S, lds, lane, zs, zj);
+            d = 2.f * cest * u32 * zs + 2.f * 2.3841858e-7f * zj +
+                sqrtf(float(P::ncol)) * u32 * float(P::abs_lambda_max) * jn2;
+        } else {
+            q = P::template colour_sum<T>(J);
+            d = sqrtf(jn2 * sn2);
+        }
+        if (part) {
+            if (valid) part[(int64_t)ih * nevt + ev] = float2{q, d};
+        } else {
+            acc += q;
+            dacc = fmaf(mixed_weight<P>(cest), d, dacc);
+        }
+    }
+    if (!part) mixed_result<P>(ev, valid, lane, acc, dacc, tol, out, flag_count, flag_idx, err_out, flag_out);
+}
+
+template <class P>
+__global__ __launch_bounds__(64) void k_mixed_sum(const float2* __restrict__ part, int64_t nevt, int nh, float tol,
+                                                  float cest, double* __restrict__ out, int* __restrict__ flag_count,
+                                                  int* __restrict__ flag_idx, float* __restrict__ err_out,
+                                                  unsigned char* __restrict__ flag_out) {
+    int64_t ev = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const bool valid = ev < nevt;
+    if (!valid) ev = nevt - 1;
+    float acc = 0.f, dacc = 0.f;
+#pragma unroll 16
+    for (int ih = 0; ih < nh; ++ih) {
+        const float2 v = part[(int64_t)ih * nevt + ev];
+        acc += v.x;
+        dacc = fmaf(mixed_weight<P>(cest), v.y, dacc);
+    }
+    mixed_result<P>(ev, valid, threadIdx.x, acc, dacc, tol, out, flag_count, flag_idx, err_out, flag_out);
+}
+
+// Helicities per block where their values are added by a kernel of their own
+// (nh: not done).  One wave takes 45 us per helicity of g g -> t tbar g g and the
+// chip holds 1024 of these waves, so a call of up to 65,536 events took the 2.9 ms
+// of 64 helicities in turn (64 events now 72 us, 16,384 0.81 ms, with the
+// rerun), and one of a few more than a multiple of it a whole turn more (70,000
+// events 3.3 ms against 5.8).  Where the last turn is not nearly full the list is
+// parted until there are 8 turns of blocks, whose setup is a tenth of a
+// helicity's work; where it is full that costs 2 % (131,072 events 6.0 ms against 5.9).
+static inline int mixed_per_block(int64_t nevt, int nh) {
+    const int64_t tiles = (nevt + ME_BLOCK - 1) / ME_BLOCK, turns = (tiles + 1023) / 1024;
+    int per = nh;
+    if (10 * 1024 * turns <= 11 * tiles) return per;
+    while (per > 1 && tiles * ((nh + per - 1) / per) < 8 * 1024) per = (per + 1) / 2;
+    return per;
 }
 
 static __global__ void k_zero_int(int* p) {

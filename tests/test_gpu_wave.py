@@ -126,3 +126,24 @@ def test_channel_weights_with_helicities_dropped(env):
         total = total + m.eval_multichannel(mom, torch.full((300,), c, dtype=torch.int32, device="cuda"))[1]
     np.testing.assert_allclose(total.cpu().numpy(), 1.0, rtol=1e-12)
     m.close()
+
+
+@pytest.mark.parametrize("proc,n", [("gg_tt", 1), ("gg_ttg", 1000), ("gg_ttgg", 1), ("gg_ttgg", 65), ("gg_ttgg", 4097),
+                                    ("gg_ttgg", 66000)])
+def test_mixed_form_with_its_helicities_parted(env, proc, n):
+    """The parted form adds the same float32 values in the same order as one lane
+    does: unflagged events bit for bit as the diagnostic call, which never parts
+    them, gives, and the same number flagged."""
+    torch, me = env
+    print(f"[wave] parted {proc} n={n}", flush=True)
+    base = process_points(proc, min(n, 3000), 65, precise=False)
+    mom = torch.from_numpy(np.tile(base, (-(-n // len(base)), 1, 1))[:n].copy()).cuda()
+    m = me.MatrixElement(proc)
+    m.set_precision(me.ME_MIXED, 1e-5)
+    raw, _, flag = m.eval_mixed_diag(mom)
+    got = m.eval(mom)
+    assert m.fallback_count() == int(flag.sum())
+    keep = flag == 0
+    assert torch.equal(got[keep], raw[keep])
+    assert torch.equal(m.eval(mom), got)
+    m.close()
