@@ -47,28 +47,54 @@ def timed(fn, steps, stream):
     return e0.elapsed_time(e1) / steps * 1e-3, wall
 
 
+# the float64 kernel of each process and the sources that make it up
+_COMMON = ("me_vertex.h", "me_process.h", "me_kernels.h", "me_launch.h")
+KERNELS = {
+    "ee_mumu": ("k_me_ee<proc_ee_mumu>", ()),
+    "gg_tt": ("k_me_gg2_pol<proc_gg_tt>", ("me_wave.h", "me_qew_pol.h", "me_gg_pol.h", "gen/proc_gg_tt.h")),
+    "gg_ttg": ("k_me_gg3_pol<proc_gg_ttg>", ("me_wave.h", "me_qew_pol.h", "me_gg_pol.h", "gen/proc_gg_ttg.h")),
+    "gg_ttgg": ("k_me_gg4_wave<proc_gg_ttgg>", ("me_wave.h", "gen/proc_gg_ttgg.h")),
+    "gg_ttggg": ("k_me_gg5_wave<proc_gg_ttggg>", ("me_wave.h", "me_wave5.h", "gen/proc_gg_ttggg.h",
+                                                  "gen/proc_gg_ttggg_wave.h")),
+}
+
+
+def kernel_of(process):
+    return KERNELS.get(process, (f"k_me_qew_pol<proc_{process}>",
+                                 ("me_wave.h", "me_qew.h", "me_qew_pol.h", f"gen/proc_{process}.h")))
+
+
 def kernel_sources_digest(process):
     """Digest of the sources that make up the float64 kernel of `process`."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2503_21935_amd", "csrc")
-    for f in ("me_vertex.h", "me_process.h", "me_kernels.h", "me_launch.h", "me_lds.h", "me_coop.h", "me_qew.h",
-              os.path.join("gen", f"proc_{process}.h")):
+    for f in _COMMON + kernel_of(process)[1]:
         p = os.path.join(csrc, f)
         if os.path.exists(p):
             h.update(open(p, "rb").read())
     return h.hexdigest()[:16]
 
 
-def traffic_from_profile(process, kernel):
-    """HBM bytes per launch from the committed counter summary, or None when the
-    kernel's sources changed after the counters were taken."""
+def counters(process):
+    """The committed counter summary of the process's float64 kernel, or None when
+    its sources changed after the counters were taken."""
     path = os.path.join(ROOT, "profiles", "counters.json")
-    if not os.path.exists(path):
-        return None
-    rec = json.load(open(path)).get(kernel)
-    if not rec or rec.get("sources") != kernel_sources_digest(process):
-        return None
-    return rec["fetch_kib"] * rec["fetch_factor"] * 1024 + rec["write_kib"] * rec["write_factor"] * 1024
+    rec = json.load(open(path)).get(kernel_of(process)[0]) if os.path.exists(path) else None
+    return rec if rec and rec.get("sources") == kernel_sources_digest(process) else None
+
+
+def roofline(process, nevt, k_s):
+    """Counted HBM bytes per launch and executed float64 operations per event (from
+    the counters: the kernels share wavefunctions between spins, so the
+    operation count of one program per helicity says nothing about them), and
+    the rate that makes at k_s seconds per launch; None without counters."""
+    rec = counters(process)
+    if not rec:
+        return {"traffic": None, "executed_flops_per_event": None, "achieved": None, "frac": None}
+    ops = rec["fp64_flops_per_event"]
+    achieved = ops * nevt / k_s / 1e12
+    return {"traffic": rec["fetch_kib"] * rec["fetch_factor"] * 1024 + rec["write_kib"] * rec["write_factor"] * 1024,
+            "executed_flops_per_event": ops, "achieved": achieved, "frac": achieved / PEAK["fp64"]}
 
 
 def bench_fp64(m, mom, out, args, stream):
@@ -108,21 +134,18 @@ def bench_process(me, proc, nevt, seed, steps, stream, check=8, tol=None):
                  "fallback_fraction": nfb / nevt, "max_rel_err_vs_oracle": float(np.abs(mres[idx] / ref - 1).max())}
         m.set_precision(me.ME_FP64, tol)
     m.close()
-    achieved = info["flops_per_event"] * nevt / k_s / 1e12
-    kernel = {"gg_ttggg": f"k_me_gg_coop<proc_{proc}>", "ee_mumu": "k_me_ee<proc_ee_mumu>"}.get(
-        proc, f"k_me_qew<proc_{proc}>" if proc.startswith("gux_") else f"k_me_gg<proc_{proc}>")
-    return {"workload": f"{proc}, {nevt} RAMBO points seed {seed}", "MEs_per_s": nevt / wall, "kernel": kernel,
-            "traffic": traffic_from_profile(proc, kernel),
-            "kernel_ms": k_s * 1e3, "flops_per_event": info["flops_per_event"],
-            "achieved_tflops": achieved, "frac_of_fp64_peak": achieved / PEAK["fp64"],
+    roof = roofline(proc, nevt, k_s)
+    return {"workload": f"{proc}, {nevt} RAMBO points seed {seed}", "MEs_per_s": nevt / wall,
+            "kernel": kernel_of(proc)[0], "traffic": roof["traffic"], "kernel_ms": k_s * 1e3,
+            "flops_per_event_one_helicity_at_a_time": info["flops_per_event"],
+            "executed_flops_per_event": roof["executed_flops_per_event"],
+            "achieved_tflops": roof["achieved"], "frac_of_fp64_peak": roof["frac"],
             "max_rel_dev_vs_oracle": float(rel.max()), "checked_events": check, "mixed": mixed}
 
 
 def nevt_sweep(me, proc, seed, lanes_list, logs, stream):
     """MEs/s of the float64 kernel against the number of events per launch, for
-    the automatic lane count (0: enough lanes per event to put 2^16 lanes in
-    flight), one lane per event and helicity-parallel launches (2^k lanes per
-    event)."""
+    settings of the lanes per event (0: automatic; only e+ e- -> mu+ mu- has others)."""
     import torch
 
     from inputs import process_points
@@ -287,7 +310,7 @@ def bench_multichannel(me, stream, mom, proc, steps):
     ref = np.array([sums[j, col[gd[c]]] / sums[j].sum() for j, c in enumerate(ch)])
     dev = float(np.max(np.abs(alpha[idx].cpu().numpy() / ref - 1)))
     m.close()
-    return {"process": proc, "nevt": n, "channels": nchan, "kernel": f"k_me_gg_mc<proc_{proc}_mc>",
+    return {"process": proc, "nevt": n, "channels": nchan, "kernel": f"k_me_gg4_chan<chan_ids_{proc}>",
             "MEs_per_s": n / k_s, "kernel_ms": k_s * 1e3, "max_rel_dev_alpha_vs_oracle": dev, "checked_events": len(idx)}
 
 
@@ -607,7 +630,7 @@ def main():
                     help="gg_ttggg: also time the float64 kernel of g g -> t tbar g g g (2^18 points, seed 3); "
                          "dy3j: g ubar -> tau+ tau- g g ubar, the DY+3j subprocess (2^20 points, seed 4); "
                          "configs: e+e- -> mu+mu- (16384 points, seed 0) and g g -> t tbar (2^20, seed 1); "
-                         "sweep: events per launch 2^10..2^20 at 1, 4, 16, 64 lanes per event; "
+                         "sweep: events per launch 2^10..2^20; "
                          "ps: the GPU phase-space sampler on the benchmark's workload; "
                          "psmc: multi-channel phase space for the DY+3j subprocess, and its variance against flat; "
                          "colour: float64 kernels with the colour sum on the VALU and on the matrix cores; "
@@ -661,10 +684,7 @@ def main():
     res = out.cpu().numpy()
     assert np.all(np.isfinite(res)), "non-finite results"
     value = args.nevt / wall
-    flops_evt = info["flops_per_event"]
-    achieved = flops_evt * args.nevt / k_s / 1e12
-    kernel = f"k_me_gg<proc_{args.process}>"
-    traffic = traffic_from_profile(args.process, kernel)
+    roof = roofline(args.process, args.nevt, k_s)
     log(f"fp64: {value:.3e} MEs/s, kernel {k_s * 1e3:.2f} ms")
 
     line = {
@@ -683,10 +703,11 @@ def main():
         "config": {"workload": f"{args.process} |M|^2, {args.nevt} RAMBO points seed {args.seed}, "
                                f"{info['nhel_good']} helicities, {info['ndiag']} diagrams, "
                                f"{info['ncol']}x{info['ncol']} colour matrix",
-                   "nevt": args.nevt, "parallelism": "single GPU, one event per lane"},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK["fp64"], "unit": "TFLOP/s",
-                     "frac": achieved / PEAK["fp64"], "traffic": traffic,
-                     "kernel": kernel, "flops_per_event": flops_evt, "kernel_ms": k_s * 1e3},
+                   "nevt": args.nevt, "parallelism": "single GPU, one event per wave"},
+        "roofline": {"bound": "alu", "achieved": roof["achieved"], "peak": PEAK["fp64"], "unit": "TFLOP/s",
+                     "frac": roof["frac"], "traffic": roof["traffic"], "kernel": kernel_of(args.process)[0],
+                     "executed_flops_per_event": roof["executed_flops_per_event"],
+                     "flops_per_event_one_helicity_at_a_time": info["flops_per_event"], "kernel_ms": k_s * 1e3},
         "forms": {"fp64": {"MEs_per_s": value, "ms_per_step": wall * 1e3}},
     }
     if "mixed" in forms:
@@ -727,7 +748,7 @@ def main():
         line["phase_space_multichannel"] = bench_ps_multichannel(me, stream, 1 << 20, 20)
         log(f"multi-channel phase space: {line['phase_space_multichannel']}")
     if "sweep" in forms:
-        line["nevt_sweep"] = nevt_sweep(me, args.process, args.seed, [0, 1, 4, 16, 64], list(range(10, 21, 2)), stream)
+        line["nevt_sweep"] = nevt_sweep(me, args.process, args.seed, [0], list(range(10, 21, 2)), stream)
 
     if not args.no_cpu:
         import oracle

@@ -214,8 +214,10 @@ int me_eval_helicities(me_ctx *ctx, const double *momenta, int64_t nevt, double 
  * me_info -- static properties of the context's process (diagrams, colour
  * flows, helicities: the sizes behind the paper's Sec. 3 cost discussion).
  * Any output pointer may be NULL.  flops_per_event: the algorithmic
- * floating-point operation count of one event over the good helicities
- * (diagram program + colour sum; FMA counted as two operations).
+ * floating-point operation count of one event over the good helicities taken
+ * one at a time (diagram program + colour sum; FMA counted as two operations).
+ * The spin-summed float64 kernels share wavefunctions between helicities and
+ * execute a fraction of it.
  */
 int me_info(const me_ctx *ctx, int *npart, int *ndiag, int *ncol, int *nhel, int *nhel_good,
             double *flops_per_event);
@@ -245,7 +247,8 @@ int me_info(const me_ctx *ctx, int *npart, int *ndiag, int *ncol, int *nhel, int
  *   divided by the same sum over all channel diagrams (colour factors
  *   stripped so that every colour-flow coefficient has unit modulus); 0 when
  *   chan is outside 0 .. nchan - 1.  The evaluation is float64 with one
- *   amplitude per Feynman diagram (no merged currents).  Errors: ME_EINVAL,
+ *   amplitude per Feynman diagram (no merged currents); where the helicity
+ *   filter dropped helicities (a massless top) the sums leave them out.  Errors: ME_EINVAL,
  *   ME_ESTATE (no multi-channel form), ME_EDEVICE.
  */
 int me_channels(const me_ctx *ctx, int *nchan);
@@ -259,11 +262,11 @@ int me_eval_multichannel(me_ctx *ctx, const double *momenta, const int32_t *chan
  * wavefunctions, currents, amplitudes, accumulation into J) with every
  * wavefunction computed once; colour_per_hel, the colour sum J^dag N J in the
  * symmetric form the float64 kernels evaluate; executed_per_hel, the diagram
- * part as the float64 kernel executes it (wavefunctions recomputed under its
- * register budget included, all waves of a workgroup kernel together).  FMA
- * counts as two operations.  These are the algorithmic counts of the
- * roofline accounting (the paper's Sec. 3 splits the cost the same way:
- * Feynman-diagram code and the colour-matrix quadratic form).
+ * part as the kernels that evaluate single helicities (me_eval_helicities,
+ * the filter) execute it, wavefunctions recomputed under their register budget
+ * included, all waves of a workgroup kernel together.  FMA counts as two
+ * operations.  (The paper's Sec. 3 splits the cost the same way: Feynman-diagram
+ * code and the colour-matrix quadratic form.)
  */
 int me_flops(const me_ctx *ctx, double *amp_per_hel, double *colour_per_hel, double *executed_per_hel);
 

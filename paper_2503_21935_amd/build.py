@@ -60,25 +60,16 @@ static hipError_t launch_sum(const double* mom, int64_t nevt, double* out, unsig
 }}
 
 static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
-                             const me_params& prm, double* qhel, int lg, hipStream_t s) {{
-    const dim3 grid((unsigned)(((nevt << lg) + ME_BLOCK - 1) / ME_BLOCK));
-    hipLaunchKernelGGL((k_me_qew<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel,
-                       nullptr, nullptr, lg);
-    return hipGetLastError();
-}}
-
-static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
-                                 const me_params& prm, const int* idx, const int* count, hipStream_t s) {{
+                             const me_params& prm, double* qhel, int, hipStream_t s) {{
     const dim3 grid((unsigned)((nevt + ME_BLOCK - 1) / ME_BLOCK));
-    hipLaunchKernelGGL((k_me_qew<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm,
-                       nullptr, idx, count, 0);
+    hipLaunchKernelGGL((k_me_qew<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel);
     return hipGetLastError();
 }}
 
 #ifndef __HIP_DEVICE_COMPILE__  // the table entry holds host function pointers
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_QEW, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
-    {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, nullptr, 8.0,
+    {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, nullptr, nullptr, 8.0,
     0.0, nullptr, nullptr, 0, nullptr, launch_sum, nullptr, false}};
 #endif
 """
@@ -87,10 +78,28 @@ _TU = """// Generated translation unit: kernels of {name}.
 #include "me_mixed.h"
 {include}
 
-static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
+{f64}{mixed}{cm}
+#ifndef __HIP_DEVICE_COMPILE__  // the table entry holds host function pointers
+extern const me_process_desc me_desc_{name} = {{
+    "{name}", {kind}, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
+    {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, {idx_ptr}, {mixed_ptr}, {cest},
+    {colerr}, {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}, {chan_ptr},
+    {mixed_part}}};
+#endif
+"""
+
+_F64_GG = """static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
+                             const me_params& prm, double* qhel, int, hipStream_t s) {{
+    const dim3 grid((unsigned)((nevt + ME_BLOCK - 1) / ME_BLOCK));
+    hipLaunchKernelGGL((k_me_gg<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel);
+    return hipGetLastError();
+}}
+"""
+
+_F64_EE = """static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                              const me_params& prm, double* qhel, int lg, hipStream_t s) {{
     const dim3 grid((unsigned)(((nevt << lg) + ME_BLOCK - 1) / ME_BLOCK));
-    hipLaunchKernelGGL(({kernel}<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm,
+    hipLaunchKernelGGL((k_me_ee<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm,
                        qhel, nullptr, nullptr, lg);
     return hipGetLastError();
 }}
@@ -98,18 +107,10 @@ static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const
 static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                  const me_params& prm, const int* idx, const int* count, hipStream_t s) {{
     const dim3 grid((unsigned)((nevt + ME_BLOCK - 1) / ME_BLOCK));
-    hipLaunchKernelGGL(({kernel}<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm,
+    hipLaunchKernelGGL((k_me_ee<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm,
                        nullptr, idx, count, 0);
     return hipGetLastError();
 }}
-{mixed}{cm}
-#ifndef __HIP_DEVICE_COMPILE__  // the table entry holds host function pointers
-extern const me_process_desc me_desc_{name} = {{
-    "{name}", {kind}, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
-    {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, {mixed_ptr}, {cest},
-    {colerr}, {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}, {chan_ptr},
-    {mixed_part}}};
-#endif
 """
 
 _MC_DECL = """
@@ -234,10 +235,9 @@ def _chan_tu(name):
 
 _CM = """
 static hipError_t launch_f64_cm(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
-                                const me_params& prm, double* qhel, int lg, hipStream_t s) {{
-    const dim3 grid((unsigned)(((nevt << lg) + ME_BLOCK - 1) / ME_BLOCK));
-    hipLaunchKernelGGL((k_me_gg_cm<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel,
-                       nullptr, nullptr, lg);
+                                const me_params& prm, double* qhel, int, hipStream_t s) {{
+    const dim3 grid((unsigned)((nevt + ME_BLOCK - 1) / ME_BLOCK));
+    hipLaunchKernelGGL((k_me_gg_cm<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel);
     return hipGetLastError();
 }}
 """
@@ -250,15 +250,7 @@ static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const
                              const me_params& prm, double* qhel, int lg, hipStream_t s) {{
     const dim3 grid((unsigned)(((nevt << lg) + ME_TILE - 1) / ME_TILE));
     hipLaunchKernelGGL((k_me_gg_coop<{proc}>), grid, dim3(ME_TILE * {proc}::waves), 0, s, mom, nevt, out, hels,
-                       nh, prm, qhel, nullptr, nullptr, lg);
-    return hipGetLastError();
-}}
-
-static hipError_t launch_f64_idx(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
-                                 const me_params& prm, const int* idx, const int* count, hipStream_t s) {{
-    const dim3 grid((unsigned)((nevt + ME_TILE - 1) / ME_TILE));
-    hipLaunchKernelGGL((k_me_gg_coop<{proc}>), grid, dim3(ME_TILE * {proc}::waves), 0, s, mom, nevt, out, hels,
-                       nh, prm, nullptr, idx, count, 0);
+                       nh, prm, qhel, lg);
     return hipGetLastError();
 }}
 
@@ -274,7 +266,7 @@ hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, un
                                 const int* idx, const int* count, bool mfma, hipStream_t s);
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_GG, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
-    {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, launch_f64_idx, me_launch_mixed_{name}, {cest},
+    {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, nullptr, me_launch_mixed_{name}, {cest},
     {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}, nullptr, false}};
 #endif
 """
@@ -287,7 +279,7 @@ hipError_t me_launch_f64_cm_{name}(const double* mom, int64_t nevt, double* out,
                                    const me_params& prm, double* qhel, int lg, hipStream_t s) {{
     const dim3 grid((unsigned)(((nevt << lg) + ME_TILE - 1) / ME_TILE));
     hipLaunchKernelGGL((k_me_gg_coop<{proc}, true>), grid, dim3(ME_TILE * {proc}::waves), 0, s, mom, nevt, out,
-                       hels, nh, prm, qhel, nullptr, nullptr, lg);
+                       hels, nh, prm, qhel, lg);
     return hipGetLastError();
 }}
 """
@@ -358,10 +350,10 @@ def generate_sources(processes):
             tus.append(path)
             continue
         if name == "ee_mumu":
-            inc, kernel, proc, kind = "", "k_me_ee", "proc_ee_mumu", "ME_KIND_EE"
+            inc, proc, kind = "", "proc_ee_mumu", "ME_KIND_EE"
             mixed, mixed_ptr, colerr = "", "nullptr", "0.0"
         else:
-            inc, kernel, proc, kind = f'#include "gen/proc_{name}.h"', "k_me_gg", f"proc_{name}", "ME_KIND_GG"
+            inc, proc, kind = f'#include "gen/proc_{name}.h"', f"proc_{name}", "ME_KIND_GG"
             mixed, mixed_ptr, colerr = _MIXED.format(proc=proc), "launch_mixed", f"{proc}::colour_err_f16"
         path = os.path.join(GEN, f"tu_{name}.hip")
         if name in COOP:
@@ -398,7 +390,9 @@ def generate_sources(processes):
             path_w = os.path.join(GEN, f"tu_{name}_wave.hip")
             _write(path_w, _wave_tu(name))
             tus.append(path_w)
-        _write(path, _TU.format(name=name, include=inc, kernel=kernel, proc=proc, kind=kind, mixed=mixed,
+        f64 = (_F64_EE if name == "ee_mumu" else _F64_GG).format(proc=proc)
+        idx_ptr = "launch_f64_idx" if name == "ee_mumu" else "nullptr"
+        _write(path, _TU.format(name=name, include=inc, f64=f64, idx_ptr=idx_ptr, proc=proc, kind=kind, mixed=mixed,
                                 mixed_ptr=mixed_ptr, cest=MIXED_CEST.get(name, 8.0), colerr=colerr, cm=cm,
                                 cm_ptr=cm_ptr, mc_ptr=mc_ptr, mc_n=mc_n, mc_desc=mc_desc, sum_ptr=sum_ptr, chan_ptr=chan_ptr,
                                 mixed_part="false" if mixed_ptr == "nullptr" else "true"))

@@ -216,14 +216,13 @@ static hipError_t launch_sum(const me_ctx* c, const double* momenta, int64_t nev
                                s);
 }
 
-// The float64 form of me_eval: the spin-summed kernel where the process has
-// one (it uses a whole wave per event at any count of events, so the lane
-// setting does not enter), else the context's colour form and lane count.
+// The float64 form of me_eval: the spin-summed kernel where the process has one
+// (the lane setting does not enter), else the context's lane count.
 static hipError_t launch_f64_form(const me_ctx* c, const double* momenta, int64_t nevt, double* out,
                                   hipStream_t s) {
     if (c->proc->launch_sum) return launch_sum(c, momenta, nevt, out, c->spins, s);
     const int lg = c->hel_lg >= 0 ? c->hel_lg : auto_lanes_lg(nevt, c->nhel_good);
-    return f64_launcher(c)(momenta, nevt, out, c->d_good, c->nhel_good, c->prm, nullptr, lg, s);
+    return c->proc->launch_f64(momenta, nevt, out, c->d_good, c->nhel_good, c->prm, nullptr, lg, s);
 }
 
 hipError_t me_launch_idx(const me_ctx* c, const double* mom, int64_t nevt, double* out, const int* idx,

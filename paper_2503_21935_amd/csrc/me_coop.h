@@ -53,7 +53,9 @@ MEV double coop_colour(int wave, const double* Jl) {
 }
 
 // Arguments as for k_me_gg; launched with blocks of 64 * P::waves threads,
-// one block per 64 / 2^lg events (or entries of idx).  With lg > 0 the 2^lg
+// one block per 64 / 2^lg events (the callers ask for lg = 0; with the helicity
+// the same for all lanes the program gets branches and takes three times as long to
+// compile).  With lg > 0 the 2^lg
 // lanes of an event take every 2^lg-th helicity of the list (the same count
 // of passes for every lane, so the barriers stay uniform; a lane past the end
 // of the list repeats its last helicity and discards the result).
@@ -63,7 +65,7 @@ MEV double coop_colour(int wave, const double* Jl) {
 template <class P, bool CM = false>
 __global__ __launch_bounds__(ME_TILE * P::waves, 1) void k_me_gg_coop(
     const double* __restrict__ mom, int64_t nevt, double* __restrict__ out, const int* __restrict__ hels, int nh,
-    me_params prm, double* __restrict__ qhel, const int* __restrict__ idx, const int* __restrict__ count, int lg) {
+    me_params prm, double* __restrict__ qhel, int lg) {
     constexpr int NP = P::npart, NG = P::ngluon;
     __shared__ double Jt[P::ncol * 2 * ME_TILE];
     __shared__ double Qt[(NG + 2) * 4 * ME_TILE];
@@ -71,13 +73,9 @@ __global__ __launch_bounds__(ME_TILE * P::waves, 1) void k_me_gg_coop(
     const int lane = threadIdx.x % ME_TILE;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / ME_TILE);
     const int grp = lane & ((1 << lg) - 1);
-    const int64_t n = count ? (int64_t)*count : nevt;
-    const int64_t first = (int64_t)blockIdx.x * (ME_TILE >> lg);
-    if (first >= n) return;  // whole block: no barrier is left waiting
-    int64_t i = first + (lane >> lg);
-    const bool valid = i < n;
-    if (!valid) i = n - 1;  // idle lanes repeat an event so that every wave runs the full program
-    const int64_t ev = count ? (int64_t)idx[i] : i;
+    int64_t ev = (int64_t)blockIdx.x * (ME_TILE >> lg) + (lane >> lg);
+    const bool valid = ev < nevt;
+    if (!valid) ev = nevt - 1;  // idle lanes repeat an event so that every wave runs the full program
     if (wave == 0) {  // the tile's momenta: gluons in incoming-flow sign, then p3, p4
         const double2* pe = reinterpret_cast<const double2*>(mom + ev * (NP * 4));
 #pragma unroll

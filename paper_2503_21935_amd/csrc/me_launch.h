@@ -8,11 +8,13 @@
 
 #define ME_BLOCK 64
 
-// lg: 2^lg lanes per event, each summing every 2^lg-th helicity (0 <= lg <= 6).
+// lg: 2^lg lanes per event, each summing every 2^lg-th helicity (0 <= lg <= 6), for
+// e+ e- -> mu+ mu-; the others are called for single helicities and have one lane.
 typedef hipError_t (*me_launch_fn)(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                    const me_params& prm, double* qhel, int lg, hipStream_t stream);
 
-// Indexed variant: evaluate events idx[0..*count) only (count on the device).
+// Indexed variant: evaluate events idx[0..*count) only (count on the device);
+// where there is no launch_sum.
 typedef hipError_t (*me_launch_idx_fn)(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                        const me_params& prm, const int* idx, const int* count,
                                        hipStream_t stream);

@@ -2,7 +2,7 @@
 // processes (a massless quark line with gluons and one photon/Z insertion
 // decaying to a lepton pair; g ubar -> tau+ tau- g g ubar is the DY+3j
 // subprocess of the paper's Sec. 3).  One event per lane, helicities looped
-// (or spread over 2^lg lanes), as the gluon-process kernel: externals, the
+// as the gluon-process kernel: externals, the
 // generated diagram program into the colour-flow amplitudes J, the colour sum.
 #pragma once
 #include "me_kernels.h"
@@ -88,21 +88,13 @@ MEV void qew_externals(qew_ext<double, P::ngluon>& x, int h, const me_params& pr
     }
 }
 
-// qhel, idx, count and lg as for k_me_gg.
+// qhel as for k_me_gg.
 template <class P>
 __global__ __launch_bounds__(ME_BLOCK) void k_me_qew(const double* __restrict__ mom, int64_t nevt,
                                                      double* __restrict__ out, const int* __restrict__ hels,
-                                                     int nh, me_params prm, double* __restrict__ qhel,
-                                                     const int* __restrict__ idx, const int* __restrict__ count,
-                                                     int lg) {
-    const int grp = threadIdx.x & ((1 << lg) - 1);
-    int64_t ev = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> lg;
-    if (count) {
-        if (ev >= *count) return;
-        ev = idx[ev];
-    } else if (ev >= nevt) {
-        return;
-    }
+                                                     int nh, me_params prm, double* __restrict__ qhel) {
+    const int64_t ev = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (ev >= nevt) return;
     using T = double;
     constexpr int NG = P::ngluon;
     static_assert(ME_BLOCK == 64, "one wave per block");
@@ -111,8 +103,9 @@ __global__ __launch_bounds__(ME_BLOCK) void k_me_qew(const double* __restrict__ 
     qew_setup<P>(x, mom, ev, Qt, threadIdx.x, prm);
     T acc = T(0);
 #pragma unroll 1
-    for (int ih = grp; ih < nh; ih += 1 << lg) {
-        const int h = hels[ih];
+    for (int ih = 0; ih < nh; ++ih) {
+        int h = hels[ih];
+        asm volatile("" : "+v"(h));  // per-lane copy: selects instead of branches in the externals
         qew_externals<P>(x, h, prm);
         cx<T> J[P::ncol];
 #pragma unroll
@@ -122,6 +115,5 @@ __global__ __launch_bounds__(ME_BLOCK) void k_me_qew(const double* __restrict__ 
         if (qhel) qhel[ev * P::nhel + h] = double(q) / P::lcd;
         acc += q;
     }
-    const double tot = group_sum(double(acc), lg);
-    if (grp == 0) out[ev] = tot * (1.0 / (P::avg * P::lcd));
+    out[ev] = double(acc) * (1.0 / (P::avg * P::lcd));
 }

@@ -16,7 +16,9 @@ from .qew import QEWEmitter
 GG_PROCESSES = {"gg_tt": 2, "gg_ttg": 3, "gg_ttgg": 4, "gg_ttggg": 5}
 # Maximum number of wavefunctions kept alive at once by the emitted program
 # (more are recomputed).  The momenta live in LDS, so the register budget
-# goes to wavefunctions and J.  Chosen per process by compiling and timing:
+# goes to wavefunctions and J.  Chosen per process by compiling and timing a sum over
+# all helicities with these programs (me_eval's spin sums no longer run them: they
+# serve single helicities, the helicity filter and, in float32, the mixed form):
 # g g -> t tbar g g with every operand opaque ran fastest at 14 (49.5 ms per
 # 2^20 events against 50.5 ms at 12, which has no private memory at all, and
 # 44 bytes of it per lane at 14), with the polarisation-only copies at 13; g g -> t tbar g g g (workgroup program, J in LDS, window of 16)
