@@ -188,7 +188,7 @@ def bench_phase_space(me, stream, n, host_s):
                          "frac": nbytes / k_s / 1e9 / 8000.0, "bytes_per_point": 200,
                          "note": "the output bytes against HBM; the kernel is bound by its float64 arithmetic "
                                  "(Philox, logarithms, square roots, the massive rescaling), counted in "
-                                 "profiles/ps_rambo_2p20.md"},
+                                 "profiles/kernels.md"},
             "host_numpy_rambo_s_same_size": host_s}
 
 
@@ -250,7 +250,7 @@ def bench_ps_multichannel(me, stream, n, steps):
             "roofline": {"bound": "hbm", "achieved": nbytes / k_s / 1e9, "peak": 8000.0, "unit": "GB/s",
                          "frac": nbytes / k_s / 1e9 / 8000.0, "bytes_per_point": nbytes // n,
                          "note": "the output bytes against HBM; the kernel is bound by its float64 "
-                                 "transcendental functions, counted in profiles/ps_multichannel_dy3j_2p20.md"},
+                                 "transcendental functions, those of the flat sampler are counted in profiles/kernels.md"},
             "flat": fl, "multichannel": mc,
             "variance_gain": (fl["rel_std_error"] / mc["rel_std_error"]) ** 2,
             "estimates_differ_by_sigma": float(abs(fl["estimate"] - mc["estimate"]) / np.hypot(
