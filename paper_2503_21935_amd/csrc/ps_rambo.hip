@@ -33,19 +33,23 @@ struct philox_out {
     uint32_t x[4];
 };
 
+// a ^ b ^ c in one instruction
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+
 // Philox4x32-10: ten rounds of two 32 x 32 -> 64 bit products and a word
 // exchange, the key advanced by the golden-ratio Weyl increments between rounds.
 __device__ __forceinline__ philox_out philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                                     uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-        const uint32_t lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
-        const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;  // one instruction each
+        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0), n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
         c0 = n0;
-        c1 = lo1;
+        c1 = (uint32_t)p1;
         c2 = n2;
-        c3 = lo0;
+        c3 = (uint32_t)p0;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -130,9 +134,10 @@ __device__ __forceinline__ void ps_write_rows(const double* tile, double* __rest
 }
 
 // Events first .. first + nevt - 1 of the stream; momenta [nevt][NF + 2][4].
-// 2^20 events of four particles, two of them massive, take 72 us (the 210 MB
+// 2^20 events of four particles, two of them massive, take 68 us (the 210 MB
 // alone 41), against 369 us: with Newton steps until xi no longer moved, sqrt and
-// divisions in them, pow and sincos of 2 pi u.
+// divisions in them, pow and sincos of 2 pi u, and two multiplications and xors for
+// each of Philox's products and sums (72 us).
 template <int NF>
 __global__ __launch_bounds__(PS_BLOCK) void k_ps_rambo(double roots, ps_masses ms, int massive, double w0,
                                                        uint64_t seed, int64_t first, int64_t nevt,
