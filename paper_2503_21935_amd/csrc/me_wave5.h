@@ -19,12 +19,16 @@
 // Klein four-group and the reversal split the 120 x 120 form into eight blocks.
 // 159 kB of LDS: one workgroup per CU, three waves per SIMD.
 //
-// Measured: 2^15 events in 3.74 ms (8.8e6 per second) where the kernel with one
+// Measured: 2^15 events in 3.50 ms (9.4e6 per second) where the kernel with one
 // event per lane and a diagram program split over four waves (k_me_gg_coop)
-// takes 37 ms, 64 events in 40 us against 280 us.  An event takes a CU about 70,000
+// takes 37 ms, 64 events in 33 us against 280 us.  An event takes a CU about 65,000
 // cycles: 38,000 vector instructions, the VALU active half the time; the rest
 // is barriers between some twenty stages and the latency of LDS and tables
-// that three waves per SIMD leave open.
+// that three waves per SIMD leave open.  168 registers per lane are what three
+// waves leave; what was kept from phase to phase (lane indices, 64-bit table
+// addresses, the second unit's sums while the next event is prepared) spilled
+// 136 bytes per lane, now 100: 50,021 events write 1.0 GB of it instead of 2.7
+// and take 5.33 ms instead of 5.56.
 #pragma once
 #include "gen/proc_gg_ttggg_wave.h"
 #include "me_wave.h"
@@ -58,8 +62,10 @@ MEV void arrived(words<Q>& w) {
 template <int Q>
 MEV words<Q> ld_words(const int4* __restrict__ tab, int n, int node) {
     words<Q> w;
+    const unsigned off = 16u * (unsigned)node;  // scalar base plus this: no 64-bit addresses to keep
 #pragma unroll
-    for (int k = 0; k < Q; ++k) w.q[k] = tab[k * n + node];
+    for (int k = 0; k < Q; ++k)
+        w.q[k] = *reinterpret_cast<const int4*>(reinterpret_cast<const char*>(tab + k * n) + off);
     return w;
 }
 
@@ -147,8 +153,16 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
     static_assert(P::ngluon == 5 && P::ncol == 120, "five gluons");
     constexpr int NP = 7;
     __shared__ double2 T[w5::S_END];
-    const int tid0 = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Lane and thread index, made anew in every phase: kept, they and what is
+    // formed from them spill.
+    int lane, tid;
+    auto here = [&]() __attribute__((always_inline)) {
+        lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(lane));
+        tid = 64 * wave + lane;
+    };
+    here();
     const int64_t n = count ? (int64_t)*count : nevt;
     const double m = prm.mt;
     double* const D = reinterpret_cast<double*>(T);
@@ -160,19 +174,20 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
     // waves 8, 9 and 10 prepare the next event: lane l holds component l of (gluons in incoming flow, p3, p4)
     const bool ahead = wave >= 8 && wave < 11;
     double q28 = 0.0;
-    auto fetch = [&](int64_t i) __attribute__((always_inline)) {
-        const int l = tid0 & 63, slot = l >> 2;
+    auto fetch = [&](int64_t i, int l) __attribute__((always_inline)) {
+        const int slot = l >> 2;
         if (ahead && l < 28 && i < n) {
             const int part = slot < 2 ? slot : slot < 5 ? slot + 2 : slot - 3;
-            const double v = mom[(count ? (int64_t)idx[i] : i) * (NP * 4) + 4 * part + (l & 3)];
-            q28 = (slot >= 2 && slot < 5) ? -v : v;
+            q28 = mom[(count ? (int64_t)idx[i] : i) * (NP * 4) + 4 * part + (l & 3)];
         }
     };
-    fetch(blockIdx.x);
-    if (ahead) prepare0(T, NEXT, wave - 8, q28, tid0 & 63, prm);
+    auto incoming = [&](int l) __attribute__((always_inline)) {  // with the sign of the incoming flow
+        return (l >> 2) >= 2 && (l >> 2) < 5 ? -q28 : q28;
+    };
+    fetch(blockIdx.x, lane);
+    if (ahead) prepare0(T, NEXT, wave - 8, incoming(lane), lane, prm);
     __syncthreads();
-    if (ahead && wave < 10) prepare1(T, NEXT, wave - 8, tid0 & 63, prm);
-    fetch((int64_t)blockIdx.x + gridDim.x);
+    if (ahead && wave < 10) prepare1(T, NEXT, wave - 8, lane, prm);
     // the waves' shares of the colour sum of event i, added up once every wave has passed a barrier
     double* const part = D + 2 * (w5::S_END - 8);
     auto finish = [&](int64_t i, int lane) __attribute__((always_inline)) {
@@ -181,9 +196,7 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
     };
     int64_t done = -1;
     for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
-        int tid = tid0;
-        asm volatile("" : "+v"(tid));  // addresses and tables are not kept across the events
-        const int lane = tid & 63;
+        here();
         static_assert(N_N2 == 320 && N_W3 == 240, "five waves and the next four");
         words<2> w23;
         if (wave < 5) {
@@ -193,11 +206,13 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
             w23 = ld_words<2>(tab_W3, N_W3, k);
         }
         __syncthreads();
+        here();
         if (wave == 11 && done >= 0) finish(done, lane);
         if (tid < w5::S_SMALL) T[tid] = T[w5::S_WINDOW + tid];
         auto w4 = ld_words<2>(tab_W4, N_W4, tid < N_W4 ? tid : N_W4 - 1);
         arrived(w23);
         __syncthreads();
+        here();
         // ---- two-gluon rows and triple currents ----
         if (wave < 5) {
             const auto& w = w23;
@@ -221,6 +236,7 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
         auto w4s = ld_words<1>(tab_W4S, N_W4S, tid < N_W4S ? tid : N_W4S - 1);
         auto w5d = ld_words<3>(tab_W5, N_W5, tid);
         __syncthreads();
+        here();
         // ---- four-gluon currents: those that begin with the first gluon, then the rest ----
         if (tid < N_W4) {
             const auto& w = w4;
@@ -246,6 +262,7 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
         arrived(w4s);
         arrived(w5d);
         __syncthreads();
+        here();
         if (tid < N_W4S) {
             const auto& w = w4s;
             const vec x = add(add(ld_vec(T, w.template at<0>(), 16), ld_vec(T, w.template at<1>(), 16)),
@@ -254,6 +271,7 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
             st_vec(T, w.template at<4>(), 16, x);
         }
         __syncthreads();
+        here();
         // ---- five-gluon currents, without their propagator ----
         auto w5a = ld_words<1>(tab_W5A, N_W5A, tid);
         auto w5b = ld_words<1>(tab_W5B, N_W5B, tid < N_W5B ? tid : N_W5B - 1);
@@ -284,11 +302,12 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
             st_vec(T, w.template at<19>(), 32, x);
         }
         // entries of this wave's orderings at configuration `lane`, per slot and stage
-        const int4* const cfg[2] = {tab_cfg + unit[0] * CFG_UNIT + lane, tab_cfg + unit[1] * CFG_UNIT + lane};
-        words<Q_TREE> tree[2] = {ld_words<Q_TREE>(cfg[0] + AT_TREE, 64, 0), ld_words<Q_TREE>(cfg[1] + AT_TREE, 64, 0)};
+        const int4* const cfg[2] = {tab_cfg + unit[0] * CFG_UNIT, tab_cfg + unit[1] * CFG_UNIT};
+        words<Q_TREE> tree[2] = {ld_words<Q_TREE>(cfg[0] + AT_TREE, 64, lane), ld_words<Q_TREE>(cfg[1] + AT_TREE, 64, lane)};
         arrived(w5a);
         arrived(w5b);
         __syncthreads();
+        here();
         {
             const vec x = add(add(ld_vec(T, w5a.template at<0>(), 32), ld_vec(T, w5a.template at<1>(), 32)),
                               add(ld_vec(T, w5a.template at<2>(), 32), ld_vec(T, w5a.template at<3>(), 32)));
@@ -308,9 +327,15 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
         arrived(tree[0]);
         arrived(tree[1]);
         __syncthreads();
+        here();
 
         // ---- J of 24 (or 12) orderings at configuration `lane` ----
         c2 J[2][12];
+        // The waves that prepare the next event have one unit: the second is not live while they do.
+        auto one_unit = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < 12; ++k) J[1][k] = c2{0.0, 0.0};
+        };
         each<12>([&](auto K) __attribute__((always_inline)) { J[0][K] = J[1][K] = c2{0.0, 0.0}; });
         each<2>([&](auto S) __attribute__((always_inline)) {  // ubar W(abcde) v
             if (S == 1 && !both) return;
@@ -322,8 +347,9 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
         });
         arrived(wc);
         __syncthreads();
+        here();
         // currents of the line with one gluon on each side, and with one at an end
-        words<Q_ENDS> ends = ld_words<Q_ENDS>(cfg[0] + AT_ENDS, 64, 0);
+        words<Q_ENDS> ends = ld_words<Q_ENDS>(cfg[0] + AT_ENDS, 64, lane);
         if (wave < 7) {
             // component strides: end rows 2, one-gluon rows 4
             const int sf = wave == 6 ? 2 : 4, sr = wave == 5 ? 2 : 4;
@@ -331,14 +357,14 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
             st_row(T, wc.template at<2>(), wave < 5 ? 16 : 8, V);
         }
         static_assert(N_N3 > THREADS && N_N3 <= 2 * THREADS && N_X3 == N_N3, "one or two per thread");
-        const int tid2 = tid + THREADS < N_N3 ? tid + THREADS : N_N3 - 1;
-        const bool second = tid + THREADS < N_N3;
+        auto tid2 = [&]() __attribute__((always_inline)) { return tid + THREADS < N_N3 ? tid + THREADS : N_N3 - 1; };
         arrived(ends);
         __syncthreads();
+        here();
         words<1> wn[2];
         each<2>([&](auto S) __attribute__((always_inline)) {
             if (S == 1 && !both) return;
-            words<Q_MID> mid = ld_words<Q_MID>(cfg[S] + AT_MID, 64, 0);
+            words<Q_MID> mid = ld_words<Q_MID>(cfg[S] + AT_MID, 64, lane);
             each<2>([&](auto O) __attribute__((always_inline)) {  // L(a) W(bcde) v
                 const row V = ld_row(T, ends.template at<O>(), 8);
                 each<6>([&](auto K) __attribute__((always_inline)) {
@@ -357,7 +383,7 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
                 });
                 settle(J[S]);
             });
-            if (S == 0 && both) ends = ld_words<Q_ENDS>(cfg[1] + AT_ENDS, 64, 0);
+            if (S == 0 && both) ends = ld_words<Q_ENDS>(cfg[1] + AT_ENDS, 64, lane);
             each<6>([&](auto OZ) __attribute__((always_inline)) {  // L(a) W(bcd) R(e)
                 constexpr int O = OZ / 3, Z = OZ % 3;
                 const row V = ld_row(T, mid.template at<3 * O + Z>(), 16);
@@ -369,11 +395,13 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
                 settle(J[S]);
             });
         });
+        fetch(i + gridDim.x, lane);  // used a phase later
         wn[0] = ld_words<1>(tab_N3, N_N3, tid);
-        wn[1] = ld_words<1>(tab_N3, N_N3, tid2);
+        wn[1] = ld_words<1>(tab_N3, N_N3, tid2());
         __syncthreads();
+        here();
         // three-gluon rows from p4 without the propagator at the cut
-        words<1> rows[2] = {ld_words<1>(cfg[0] + AT_ROWS, 64, 0), ld_words<1>(cfg[1] + AT_ROWS, 64, 0)};
+        words<1> rows[2] = {ld_words<1>(cfg[0] + AT_ROWS, 64, lane), ld_words<1>(cfg[1] + AT_ROWS, 64, lane)};
         {
             auto node = [&](const words<1>& w) __attribute__((always_inline)) {
                 row f = slash(ld_row(T, w.template at<0>(), 8), ld_vec(T, w.template at<1>(), 2));
@@ -382,13 +410,17 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
                 st_row(T, w.template at<6>(), 16, f);
             };
             node(wn[0]);
-            if (second) node(wn[1]);
+            if (tid + THREADS < N_N3) node(wn[1]);
         }
         arrived(rows[0]);
         arrived(rows[1]);
         __syncthreads();
-        words<1> wx[2] = {ld_words<1>(tab_X3, N_X3, tid), ld_words<1>(tab_X3, N_X3, tid2)};
-        if (ahead) prepare0(T, NEXT, wave - 8, q28, lane, prm);
+        here();
+        words<1> wx[2] = {ld_words<1>(tab_X3, N_X3, tid), ld_words<1>(tab_X3, N_X3, tid2())};
+        if (ahead) {
+            prepare0(T, NEXT, wave - 8, incoming(lane), lane, prm);
+            one_unit();
+        }
         each<2>([&](auto S) __attribute__((always_inline)) {  // L(ab) [...]
             if (S == 1 && !both) return;
             const auto& w = rows[S];
@@ -403,8 +435,9 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
         arrived(wx[0]);
         arrived(wx[1]);
         __syncthreads();
+        here();
         // [L(a) W(bc) + ubar W(abc)] R(de)
-        words<Q_TWO> two[2] = {ld_words<Q_TWO>(cfg[0] + AT_TWO, 64, 0), ld_words<Q_TWO>(cfg[1] + AT_TWO, 64, 0)};
+        words<Q_TWO> two[2] = {ld_words<Q_TWO>(cfg[0] + AT_TWO, 64, lane), ld_words<Q_TWO>(cfg[1] + AT_TWO, 64, lane)};
         {
             auto node = [&](const words<1>& w) __attribute__((always_inline)) {
                 row f = slash(ld_row(T, w.template at<0>(), 4), ld_vec(T, w.template at<1>(), 4));
@@ -412,12 +445,16 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
                 st_row(T, w.template at<4>(), 16, f);
             };
             node(wx[0]);
-            if (second) node(wx[1]);
+            if (tid + THREADS < N_N3) node(wx[1]);
         }
         arrived(two[0]);
         arrived(two[1]);
         __syncthreads();
-        if (ahead && wave < 10) prepare1(T, NEXT, wave - 8, lane, prm);
+        here();
+        if (ahead && wave < 10) {
+            prepare1(T, NEXT, wave - 8, lane, prm);
+            one_unit();
+        }
         each<2>([&](auto S) __attribute__((always_inline)) {
             if (S == 1 && !both) return;
             const auto& w = two[S];
@@ -432,8 +469,8 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
                 });
             });
         });
-        fetch(i + 2 * (int64_t)gridDim.x);
         __syncthreads();
+        here();
         // ---- colour sum ----
         double q = 0.0;
         double* const DJ = D + 2 * w5::S_J;
@@ -485,5 +522,5 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
         done = i;
     }
     __syncthreads();
-    if (wave == 11 && done >= 0) finish(done, tid0 & 63);
+    if (wave == 11 && done >= 0) finish(done, lane);
 }
