@@ -417,9 +417,13 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
         __syncthreads();
         here();
         words<1> wx[2] = {ld_words<1>(tab_X3, N_X3, tid), ld_words<1>(tab_X3, N_X3, tid2())};
+        // A chain of divisions and roots on few lanes: the wave issues it first, or the others wait for
+        // it at the barrier (50,021 events 5.31 -> 5.25 ms; any other wave or phase so raised is slower).
         if (ahead) {
+            __builtin_amdgcn_s_setprio(2);
             prepare0(T, NEXT, wave - 8, incoming(lane), lane, prm);
             one_unit();
+            __builtin_amdgcn_s_setprio(0);
         }
         each<2>([&](auto S) __attribute__((always_inline)) {  // L(ab) [...]
             if (S == 1 && !both) return;
@@ -452,8 +456,10 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
         __syncthreads();
         here();
         if (ahead && wave < 10) {
+            __builtin_amdgcn_s_setprio(2);
             prepare1(T, NEXT, wave - 8, lane, prm);
             one_unit();
+            __builtin_amdgcn_s_setprio(0);
         }
         each<2>([&](auto S) __attribute__((always_inline)) {
             if (S == 1 && !both) return;
