@@ -499,6 +499,10 @@ __global__ __launch_bounds__(64, CM ? 1 : 2) void k_me_gg4_wave(const double* __
     for (int64_t base = (int64_t)blockIdx.x * eb; base < n; base += (int64_t)gridDim.x * eb) {
         const int ne = (eb == 2 && base + 1 < n) ? 2 : 1;
         __syncthreads();  // the previous event's reads are done
+        // Issue priority falls from the setup (long chains) over J (operands from LDS) to the colour sum
+        // (registers only), so that of two waves on a SIMD the one that has to wait most asks first:
+        // 2^20 events 6.46 -> 6.35 ms, 2^14 108 -> 105.6 us.  Raised for the setup alone: 6.45 ms.
+        __builtin_amdgcn_s_setprio(2);
         gg4_setup(T, mom, base, ne, idx, count, prm, lane);
 #pragma unroll 1
         for (int j = 0; j < ne; ++j) {
@@ -562,6 +566,7 @@ __global__ __launch_bounds__(64, CM ? 1 : 2) void k_me_gg4_wave(const double* __
             if (ln < 32) four(w4[1]);
             __syncthreads();
 
+            __builtin_amdgcn_s_setprio(1);
             // ---- J of configuration `lane` ----
             c2 J[24];
             {  // all four gluons in one tree
@@ -672,6 +677,7 @@ __global__ __launch_bounds__(64, CM ? 1 : 2) void k_me_gg4_wave(const double* __
             each<6, 4>(split);
             settle(J);
             each<6, 4>(middle);
+            __builtin_amdgcn_s_setprio(0);
             double q;
             if constexpr (CM) {
                 __shared__ double Jt[P::ncol * 2 * 64];
@@ -696,6 +702,7 @@ __global__ __launch_bounds__(64, CM ? 1 : 2) void k_me_gg4_wave(const double* __
                 const int64_t i = base + j;
                 out[count ? (int64_t)idx[i] : i] = tot * (1.0 / (256.0 * P::identical * P::lcd));
             }
+            __builtin_amdgcn_s_setprio(2);
         }
     }
 }
