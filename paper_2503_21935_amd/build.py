@@ -53,9 +53,10 @@ _TU_QEW = """// Generated translation unit: kernels of {name} (quark line + lept
 
 static hipError_t launch_sum(const double* mom, int64_t nevt, double* out, unsigned, const me_params& prm,
                              const int* idx, const int* count, bool, hipStream_t s) {{
-    const int64_t per = 64 >> {proc}::ngluon;  // events per wave
-    const dim3 grid((unsigned)((nevt + per - 1) / per));
-    hipLaunchKernelGGL((k_me_qew_pol<{proc}>), grid, dim3(64), 0, s, mom, nevt, out, prm, idx, count);
+    me_each_launch(nevt, 64 >> {proc}::ngluon, 64, [&](int64_t first, unsigned blocks) {{
+        hipLaunchKernelGGL((k_me_qew_pol<{proc}>), dim3(blocks), dim3(64), 0, s, mom, nevt, out, prm, idx, count,
+                           first);
+    }});
     return hipGetLastError();
 }}
 
@@ -164,9 +165,10 @@ _LAUNCH_GROUP = """    const dim3 grid((unsigned)(nevt < ME_GROUP_BLOCKS ? nevt 
 """
 # several events per wave
 _LAUNCH_LANES = """    (void)mfma;
-    const dim3 grid((unsigned)((nevt + {per} - 1) / {per}));
-    hipLaunchKernelGGL(({kernel}<proc_{name}>), grid, dim3(64), 0, s, mom, nevt, out, spins, prm, idx, count, nullptr,
-                       nullptr);
+    me_each_launch(nevt, {per}, 64, [&](int64_t first, unsigned blocks) {{
+        hipLaunchKernelGGL(({kernel}<proc_{name}>), dim3(blocks), dim3(64), 0, s, mom, nevt, out, spins, prm, idx,
+                           count, first, nullptr, nullptr);
+    }});
 """
 
 
@@ -220,9 +222,10 @@ _LAUNCH_CHAN_WAVE = """    const hipError_t e = me_launch_sum_{name}(mom, nevt, 
     hipLaunchKernelGGL((k_me_gg4_chan<chan_ids_{name}>), grid, dim3(64), 0, s, mom, nevt, chan, alpha, prm, eb);
 """
 # with |M|^2 in one kernel
-_LAUNCH_CHAN_LANES = """    const dim3 grid((unsigned)((nevt + {per} - 1) / {per}));
-    hipLaunchKernelGGL(({kernel}<proc_{name}, chan_ids_{name}>), grid, dim3(64), 0, s, mom, nevt, out, 0xfu, prm,
-                       nullptr, nullptr, chan, alpha);
+_LAUNCH_CHAN_LANES = """    me_each_launch(nevt, {per}, 64, [&](int64_t first, unsigned blocks) {{
+        hipLaunchKernelGGL(({kernel}<proc_{name}, chan_ids_{name}>), dim3(blocks), dim3(64), 0, s, mom, nevt, out, 0xfu,
+                           prm, nullptr, nullptr, first, chan, alpha);
+    }});
 """
 
 

@@ -44,17 +44,19 @@ MEV void currents_e(const row& f, const row& r, const vec& e1, const vec& e2, c2
 
 }  // namespace g2
 
-// idx, count and spins as for k_me_gg4_wave.  With IDS (the channel numbers of
+// idx, count and spins as for k_me_gg4_wave; first0: the launch's first event (or
+// entry of idx).  With IDS (the channel numbers of
 // the diagrams) also the single-diagram weight of each event's channel, as k_me_gg4_chan.
 template <class P, class IDS = void>
 __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__ mom, int64_t nevt,
                                                       double* __restrict__ out, unsigned spins, me_params prm,
                                                       const int* __restrict__ idx, const int* __restrict__ count,
+                                                      int64_t first0,
                                                       const int* __restrict__ chan = nullptr,
                                                       double* __restrict__ alpha = nullptr) {
     using namespace g2;
     static_assert(P::ngluon == 2 && P::ncol == 2, "two gluons");
-    int64_t ev = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    int64_t ev = first0 + (int64_t)blockIdx.x * 64 + threadIdx.x;
     if (count) {
         if (ev >= *count) return;
         ev = idx[ev];
@@ -173,6 +175,7 @@ template <class P, class IDS = void>
 __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__ mom, int64_t nevt,
                                                       double* __restrict__ out, unsigned spins, me_params prm,
                                                       const int* __restrict__ idx, const int* __restrict__ count,
+                                                      int64_t first0,
                                                       const int* __restrict__ chan = nullptr,
                                                       double* __restrict__ alpha = nullptr) {
     using namespace g3;
@@ -181,7 +184,7 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
     const int lane = threadIdx.x, l = lane & 7, e = lane >> 3;
     const double m = prm.mt;
     const int64_t n = count ? (int64_t)*count : nevt;
-    const int64_t first = (int64_t)blockIdx.x * 8;
+    const int64_t first = first0 + (int64_t)blockIdx.x * 8;
     if (first >= n) return;
     int64_t i = first + e;
     const bool valid = i < n;

@@ -4,6 +4,7 @@
 
 #include <cstdint>
 
+#include "me_host.h"
 #include "me_process.h"
 
 #define ME_BLOCK 64

@@ -113,18 +113,19 @@ MEV bool from_row(int S, bool with_e) {
 
 }  // namespace qp
 
-// idx and count as for k_me_gg.
+// idx and count as for k_me_ee; first0: the launch's first event (or entry of idx).
 template <class P>
 __global__ __launch_bounds__(64, 2) void k_me_qew_pol(const double* __restrict__ mom, int64_t nevt,
                                                       double* __restrict__ out, me_params prm,
-                                                      const int* __restrict__ idx, const int* __restrict__ count) {
+                                                      const int* __restrict__ idx, const int* __restrict__ count,
+                                                      int64_t first0) {
     using namespace qp;
     constexpr int NG = P::ngluon, G = 1 << NG, FULL = G - 1;
     using Y = layout<NG>;
     __shared__ double2 mem[(64 >> NG) * (Y::STRIDE / 2)];
     const int lane = threadIdx.x, l = lane & (G - 1), e = lane >> NG;
     const int64_t n = count ? (int64_t)*count : nevt;
-    const int64_t first = (int64_t)blockIdx.x * (64 >> NG);
+    const int64_t first = first0 + (int64_t)blockIdx.x * (64 >> NG);
     if (first >= n) return;
     int64_t i = first + e;
     const bool valid = i < n;

@@ -1672,8 +1672,10 @@ int me_features(const double* momenta, int64_t n, int npart, float* x, void* str
     if (n < 0 || npart < 2 || npart > 8) return me_fail(ME_EINVAL, "me_features: bad size");
     if (n == 0) return ME_OK;
     if (!momenta || !x) return me_fail(ME_EINVAL, "me_features: null buffer");
-    hipLaunchKernelGGL(k_features, dim3((unsigned)((n + FEAT_EV - 1) / FEAT_EV)), dim3(256), 0, (hipStream_t)stream, momenta, n,
-                       npart, x);
+    me_each_launch(n, FEAT_EV, 256, [&](int64_t first, unsigned blocks) {
+        hipLaunchKernelGGL(k_features, dim3(blocks), dim3(256), 0, (hipStream_t)stream, momenta + first * 4 * npart,
+                           n - first, npart, x + first * 4 * npart);
+    });
     HCHK(hipGetLastError());
     return ME_OK;
 }
