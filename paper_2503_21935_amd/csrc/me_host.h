@@ -1,6 +1,8 @@
 // me_host.h -- host-side rules that need no device.
 #pragma once
+#include <cstddef>
 #include <cstdint>
+#include <initializer_list>
 
 // HIP takes launches of fewer than 2^32 threads, which at several threads per event is
 // less than a call may hold (2^29 events at 8 lanes each, momenta of 86 GB and more).
@@ -13,4 +15,34 @@ static inline void me_each_launch(int64_t nevt, int per, int threads, F&& f) {
         const int64_t blocks = (nevt - first + per - 1) / per;
         f(first, (unsigned)(blocks < most ? blocks : most));
     }
+}
+
+// Buffers that grow together: their pointers and new sizes in bytes, `cap` the number of
+// elements they hold.  Frees the old ones and allocates new ones for n elements.  After
+// a failure cap is 0 and every pointer is null or a live buffer, so that the next
+// call grows them again and none is used or freed after its release.
+struct me_buffer {
+    void** p;
+    size_t bytes;
+};
+template <class Alloc, class Free>
+static inline auto me_regrow(int64_t n, int64_t& cap, std::initializer_list<me_buffer> bufs, Alloc&& alloc,
+                             Free&& release) -> decltype(release((void*)nullptr)) {
+    typedef decltype(release((void*)nullptr)) status;
+    cap = 0;
+    for (const me_buffer& b : bufs) {
+        void* old = *b.p;
+        *b.p = nullptr;
+        const status e = old ? release(old) : status(0);
+        if (e != status(0)) return e;
+    }
+    for (const me_buffer& b : bufs) {
+        const status e = alloc(b.p, b.bytes);
+        if (e != status(0)) {
+            *b.p = nullptr;
+            return e;
+        }
+    }
+    cap = n;
+    return status(0);
 }

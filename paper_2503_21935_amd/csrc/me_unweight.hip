@@ -87,14 +87,15 @@ __global__ void k_uw_stage2(const int* __restrict__ idx1, const double* __restri
 static int ensure_uw(me_ctx* c, int64_t n) {
     if (n <= c->uw_cap) return ME_OK;
     HCHK(hipDeviceSynchronize());
-    void* bufs[] = {c->uw_y, c->uw_s, c->uw_me2, c->uw_idx1};
-    for (void* b : bufs)
-        if (b) HCHK(hipFree(b));
-    HCHK(hipMalloc(&c->uw_y, n * sizeof(float)));
-    HCHK(hipMalloc(&c->uw_s, n * sizeof(double)));
-    HCHK(hipMalloc(&c->uw_me2, n * sizeof(double)));
-    HCHK(hipMalloc(&c->uw_idx1, n * sizeof(int)));
-    c->uw_cap = n;
+    const size_t k = (size_t)n;
+    const hipError_t e = me_regrow(n, c->uw_cap,
+                                   {{(void**)&c->uw_y, k * sizeof(float)}, {(void**)&c->uw_s, k * sizeof(double)},
+                                    {(void**)&c->uw_me2, k * sizeof(double)}, {(void**)&c->uw_idx1, k * sizeof(int)}},
+                                   [](void** p, size_t bytes) { return hipMalloc(p, bytes); }, hipFree);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();  // not the error of a later call
+        return me_fail(ME_EDEVICE, std::string("unweight_two_stage: scratch: ") + hipGetErrorString(e));
+    }
     return ME_OK;
 }
 
