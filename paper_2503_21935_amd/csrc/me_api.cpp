@@ -274,12 +274,11 @@ int me_init(const char* process, const double* couplings, int n_couplings, const
     c->idx_cap = 0;
     c->d_part = nullptr;
     c->part_cap = 0;
-    c->uw_x = nullptr;
     c->uw_y = nullptr;
     c->uw_s = nullptr;
     c->uw_me2 = nullptr;
     c->uw_idx1 = nullptr;
-    c->uw_cap = c->uw_xcap = 0;
+    c->uw_cap = 0;
     hipError_t e = hipGetDevice(&c->device);
     if (e != hipSuccess) {
         delete c;
@@ -486,7 +485,7 @@ int me_good_helicities(const me_ctx* c, int* out, int* count) {
 int me_free(me_ctx* c) {
     if (!c) return ME_OK;
     hipError_t e = hipSuccess;
-    void* bufs[] = {c->d_good, c->d_all, c->d_count, c->d_idx, c->d_part, c->uw_x, c->uw_y, c->uw_s, c->uw_me2, c->uw_idx1};
+    void* bufs[] = {c->d_good, c->d_all, c->d_count, c->d_idx, c->d_part, c->uw_y, c->uw_s, c->uw_me2, c->uw_idx1};
     for (void* b : bufs)
         if (b) {
             hipError_t r = hipFree(b);

@@ -35,12 +35,11 @@ struct me_ctx {
     float2* d_part;  // values per helicity and event (part of launch_mixed)
     size_t part_cap;  // of them
     // scratch of two-stage unweighting
-    float* uw_x;
     float* uw_y;
     double* uw_s;
     double* uw_me2;
     int* uw_idx1;
-    int64_t uw_cap, uw_xcap;
+    int64_t uw_cap;
 };
 
 // Float64 |M|^2 of the events idx[0..*count) (both on the device).
@@ -48,6 +47,6 @@ hipError_t me_launch_idx(const me_ctx* c, const double* mom, int64_t nevt, doubl
                          const int* count, hipStream_t s);
 
 struct me_mlp;
-// The network on the features of the momenta in one kernel; false: it has no such form.
-bool mlp_forward_momenta(me_mlp* p, const double* momenta, int64_t n, float* y, hipStream_t s);
+// mlp_forward on the features of the momenta.
+int mlp_forward_momenta(me_mlp* p, const double* momenta, int64_t n, float* y, hipStream_t s);
 int mlp_n_in(const me_mlp* p);

@@ -99,18 +99,6 @@ static int ensure_uw(me_ctx* c, int64_t n) {
     return ME_OK;
 }
 
-// Features, for networks that do not form them themselves.
-static int ensure_uw_x(me_ctx* c, int64_t n, int n_in) {
-    if (n <= c->uw_xcap) return ME_OK;
-    HCHK(hipDeviceSynchronize());
-    if (c->uw_x) HCHK(hipFree(c->uw_x));
-    c->uw_x = nullptr;
-    c->uw_xcap = 0;
-    HCHK(hipMalloc(&c->uw_x, n * n_in * sizeof(float)));
-    c->uw_xcap = n;
-    return ME_OK;
-}
-
 extern "C" int unweight_two_stage(me_ctx* c, me_mlp* mlp, const double* momenta, const double* w_ps, int64_t n,
                                   const double* uniforms, double y_mu, double y_sigma, double s_max, double r_max,
                                   int32_t* out_idx, double* out_w, int32_t* out_count, void* stream) {
@@ -129,14 +117,8 @@ extern "C" int unweight_two_stage(me_ctx* c, me_mlp* mlp, const double* momenta,
     if (mlp_n_in(mlp) != 4 * npart) return me_fail(ME_EINVAL, "unweight_two_stage: network inputs != 4 npart");
     int rc = ensure_uw(c, n);
     if (rc != ME_OK) return rc;
-    if (!mlp_forward_momenta(mlp, momenta, n, c->uw_y, s)) {
-        rc = ensure_uw_x(c, n, 4 * npart);
-        if (rc != ME_OK) return rc;
-        rc = me_features(momenta, n, npart, c->uw_x, s);
-        if (rc != ME_OK) return rc;
-        rc = mlp_forward(mlp, c->uw_x, n, c->uw_y, s);
-        if (rc != ME_OK) return rc;
-    }
+    rc = mlp_forward_momenta(mlp, momenta, n, c->uw_y, s);
+    if (rc != ME_OK) return rc;
     const dim3 grid((unsigned)((n + UW_BLOCK - 1) / UW_BLOCK));
     hipLaunchKernelGGL(k_uw_stage1, grid, dim3(UW_BLOCK), 0, s, c->uw_y, w_ps, uniforms, n, y_mu, y_sigma, s_max, c->uw_s,
                        c->uw_idx1, out_count);

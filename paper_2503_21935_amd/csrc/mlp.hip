@@ -1102,6 +1102,22 @@ __global__ void k_features(const double* __restrict__ mom, int64_t n, int npart,
     for (int e = threadIdx.x; e < ne * nc; e += 256) x[first * nc + e] = (float)(mom[first * nc + e] * inv[e / nc]);
 }
 
+// Rows of bf16(features), zero-padded to 32, from momenta: what k_features and
+// k_prep_input make in two passes.
+__global__ void k_prep_momenta(const double* __restrict__ mom, int64_t n, int n_in, bf16* __restrict__ X) {
+    __shared__ double inv[FEAT_EV];
+    const int64_t first = (int64_t)blockIdx.x * FEAT_EV;
+    const int ne = (int)(n - first < FEAT_EV ? n - first : FEAT_EV);
+    if ((int)threadIdx.x < ne) inv[threadIdx.x] = inv_sqrt_shat(mom + (first + threadIdx.x) * n_in);
+    __syncthreads();
+    for (int e = threadIdx.x; e < ne * MLP_KPAD; e += 256) {
+        const int r = e / MLP_KPAD, k = e % MLP_KPAD;
+        float f = k < n_in ? (float)(mom[(first + r) * n_in + k] * inv[r]) : 0.f;
+        asm volatile("" : "+v"(f));  // rounded to FP32 first, as k_features stores it
+        X[(first + r) * MLP_KPAD + k] = (bf16)f;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
@@ -1464,6 +1480,22 @@ static bool infer_fused(const me_mlp* p, const float* x, const double* mom, int6
     return true;
 }
 
+// The layered inference in chunks; prep(o, m) fills the input rows of samples o .. o + m - 1.
+extern "C++" template <class Prep>
+static int forward_layers(me_mlp* p, int64_t n, float* y, hipStream_t s, Prep&& prep) {
+    const int64_t chunk = 1 << 16;
+    int rc = ensure_acts(p, std::min<int64_t>(n, chunk));
+    if (rc != ME_OK) return rc;
+    for (int64_t o = 0; o < n; o += chunk) {
+        const int64_t m = std::min<int64_t>(chunk, n - o);
+        prep(o, m);
+        forward(p, m, false, s);
+        HCHK(hipMemcpyAsync(y + o, p->y, m * sizeof(float), hipMemcpyDeviceToDevice, s));
+    }
+    HCHK(hipGetLastError());
+    return ME_OK;
+}
+
 int mlp_forward(me_mlp* p, const float* x, int64_t n, float* y, void* stream) {
     if (!p || n < 0) return me_fail(ME_EINVAL, "mlp_forward: null or negative n");
     if (n == 0) return ME_OK;
@@ -1473,18 +1505,10 @@ int mlp_forward(me_mlp* p, const float* x, int64_t n, float* y, void* stream) {
         HCHK(hipGetLastError());
         return ME_OK;
     }
-    const int64_t chunk = 1 << 16;
-    int rc = ensure_acts(p, std::min<int64_t>(n, chunk));
-    if (rc != ME_OK) return rc;
-    for (int64_t o = 0; o < n; o += chunk) {
-        const int64_t m = std::min<int64_t>(chunk, n - o);
-        hipLaunchKernelGGL(k_prep_input, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, x + o * p->n_in,
-                           nullptr, m, p->n_in, p->X);
-        forward(p, m, false, s);
-        HCHK(hipMemcpyAsync(y + o, p->y, m * sizeof(float), hipMemcpyDeviceToDevice, s));
-    }
-    HCHK(hipGetLastError());
-    return ME_OK;
+    return forward_layers(p, n, y, s, [&](int64_t o, int64_t m) {
+        hipLaunchKernelGGL(k_prep_input, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, x + o * p->n_in, nullptr, m,
+                           p->n_in, p->X);
+    });
 }
 
 // Batch buffers of the fused step (grow on the first call with a larger batch;
@@ -1682,8 +1706,15 @@ int me_features(const double* momenta, int64_t n, int npart, float* x, void* str
 
 }  // extern "C"
 
-// helper for the unweighting driver in me_unweight.hip
-bool mlp_forward_momenta(me_mlp* p, const double* momenta, int64_t n, float* y, hipStream_t s) {
-    return infer_fused(p, nullptr, momenta, n, y, s);
+// helpers for the unweighting driver in me_unweight.hip
+int mlp_forward_momenta(me_mlp* p, const double* momenta, int64_t n, float* y, hipStream_t s) {
+    if (infer_fused(p, nullptr, momenta, n, y, s)) {
+        HCHK(hipGetLastError());
+        return ME_OK;
+    }
+    return forward_layers(p, n, y, s, [&](int64_t o, int64_t m) {
+        hipLaunchKernelGGL(k_prep_momenta, dim3((unsigned)((m + FEAT_EV - 1) / FEAT_EV)), dim3(256), 0, s,
+                           momenta + o * p->n_in, m, p->n_in, p->X);
+    });
 }
 int mlp_n_in(const me_mlp* p) { return p->n_in; }
