@@ -71,7 +71,7 @@ static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_QEW, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, nullptr, nullptr, 8.0,
-    0.0, nullptr, nullptr, 0, nullptr, launch_sum, nullptr, false}};
+    nullptr, nullptr, 0, nullptr, launch_sum, nullptr, false}};
 #endif
 """
 
@@ -84,7 +84,7 @@ _TU = """// Generated translation unit: kernels of {name}.
 extern const me_process_desc me_desc_{name} = {{
     "{name}", {kind}, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, {idx_ptr}, {mixed_ptr}, {cest},
-    {colerr}, {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}, {chan_ptr},
+    {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}, {chan_ptr},
     {mixed_part}}};
 #endif
 """
@@ -270,7 +270,7 @@ hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, un
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_GG, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, nullptr, me_launch_mixed_{name}, {cest},
-    {proc}::colour_err_f16, me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}, nullptr, false}};
+    me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}, nullptr, false}};
 #endif
 """
 
@@ -354,10 +354,10 @@ def generate_sources(processes):
             continue
         if name == "ee_mumu":
             inc, proc, kind = "", "proc_ee_mumu", "ME_KIND_EE"
-            mixed, mixed_ptr, colerr = "", "nullptr", "0.0"
+            mixed, mixed_ptr = "", "nullptr"
         else:
             inc, proc, kind = f'#include "gen/proc_{name}.h"', f"proc_{name}", "ME_KIND_GG"
-            mixed, mixed_ptr, colerr = _MIXED.format(proc=proc), "launch_mixed", f"{proc}::colour_err_f16"
+            mixed, mixed_ptr = _MIXED.format(proc=proc), "launch_mixed"
         path = os.path.join(GEN, f"tu_{name}.hip")
         if name in COOP:
             _write(path, _TU_COOP.format(name=name, include=inc, proc=proc, cest=MIXED_CEST.get(name, 8.0)))
@@ -396,7 +396,7 @@ def generate_sources(processes):
         f64 = (_F64_EE if name == "ee_mumu" else _F64_GG).format(proc=proc)
         idx_ptr = "launch_f64_idx" if name == "ee_mumu" else "nullptr"
         _write(path, _TU.format(name=name, include=inc, f64=f64, idx_ptr=idx_ptr, proc=proc, kind=kind, mixed=mixed,
-                                mixed_ptr=mixed_ptr, cest=MIXED_CEST.get(name, 8.0), colerr=colerr, cm=cm,
+                                mixed_ptr=mixed_ptr, cest=MIXED_CEST.get(name, 8.0), cm=cm,
                                 cm_ptr=cm_ptr, mc_ptr=mc_ptr, mc_n=mc_n, mc_desc=mc_desc, sum_ptr=sum_ptr, chan_ptr=chan_ptr,
                                 mixed_part="false" if mixed_ptr == "nullptr" else "true"))
         tus.append(path)

@@ -66,7 +66,6 @@ struct me_process_desc {
     me_launch_idx_fn launch_f64_idx;
     me_launch_mixed_fn launch_mixed;  // nullptr: the process has no mixed form
     double mixed_cest;                // calibration of the amplitude error estimate
-    double colour_err;                // a-priori error of the float16 hi/lo colour sum
     me_launch_fn launch_f64_cm;       // float64 with the colour sum on the matrix cores (nullptr: none)
     me_launch_mc_fn launch_mc;        // multi-channel form (nullptr: none)
     int nchan;                        // its channels

@@ -102,9 +102,8 @@ MEV two ld2(const double* p) {
 
 // Whether the line momentum after subset S is taken from the row end (p3 - Q_S)
 // rather than the column end (Q_rest - p4): the form with fewer beam momenta.
-// The insertion belongs to S (with_e) or to the rest.
 template <class P>
-MEV bool from_row(int S, bool with_e) {
+MEV bool from_row(int S) {
     int in = P::row_in, out = P::col_in;
 #pragma unroll
     for (int a = 0; a < P::ngluon; ++a) (((S >> a) & 1) ? in : out) += P::gluon_in[a];
@@ -157,7 +156,7 @@ __global__ __launch_bounds__(64, 2) void k_me_qew_pol(const double* __restrict__
         const int kind = k / FULL, S = k % FULL + 1;
         // the line momentum after U from the row end, or U's momentum
         const int U = kind == 1 ? FULL & ~S : S;
-        const bool row = kind == 2 || from_row<P>(U, kind == 1);
+        const bool row = kind == 2 || from_row<P>(U);
         vec K{{0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
         for (int a = 0; a < NG; ++a) {

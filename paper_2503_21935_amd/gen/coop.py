@@ -470,10 +470,8 @@ class GGCoopEmitter(GGEmitter):
         Nm = np.array(self.num, dtype=float)
         ev = np.linalg.eigvalsh(Nm)
         abs_lmax = float(np.linalg.eigvalsh(np.abs(Nm)).max())
-        col_err = float(2 * 2.0 ** -22 * ev.max() / ev.min() + math.sqrt(nc) * 2.0 ** -24 * abs_lmax / ev.min())
         h.append(f"    static constexpr double abs_lambda_max = {abs_lmax!r};  // largest eigenvalue of |N|")
         h.append(f"    static constexpr double lambda_min = {float(ev.min())!r};  // smallest eigenvalue of N")
-        h.append(f"    static constexpr double colour_err_f16 = {col_err!r};")
         h.append("};")
         h.append("")
         # B fragments of v_mfma_f32_16x16x32_f16 for N (exact in float16): for K step ks

@@ -789,13 +789,8 @@ class GGEmitter:
         N = np.array(self.num, dtype=float)
         ev = np.linalg.eigvalsh(N)
         abs_lmax = float(np.linalg.eigvalsh(np.abs(N)).max())
-        # a-priori relative error of J^dag N J when J is carried as float16 hi + lo
-        # (2^-22 per element) and the products accumulate in float32:
-        #   2 * 2^-22 * cond(N) + sqrt(ncol) * 2^-24 * lambda_max(|N|) / lambda_min(N)
-        col_err = float(2 * 2.0 ** -22 * ev.max() / ev.min() + math.sqrt(nc) * 2.0 ** -24 * abs_lmax / ev.min())
         h.append(f"    static constexpr double abs_lambda_max = {abs_lmax!r};  // largest eigenvalue of |N|")
         h.append(f"    static constexpr double lambda_min = {float(ev.min())!r};  // smallest eigenvalue of N")
-        h.append(f"    static constexpr double colour_err_f16 = {col_err!r};")
         h.append("};")
         h.append("")
         h.append(f"// colour-matrix numerators for device-side lookup, row-major [{nc}][{nc}]")
