@@ -88,7 +88,7 @@ int me_init(const char *process, const double *couplings, int n_couplings, const
  * nevt == 0 launches nothing.  Errors: ME_EINVAL (null pointer, nevt < 0),
  * ME_EDEVICE (launch failure).
  * Reproducibility: results are deterministic, the same input gives the same
- * bits (me_eval_helicities of "gg_ttggg" is the exception for out_qhel: its
+ * bits (me_eval_helicities of "gg_ttggg" is the exception: its
  * kernel adds the contributions of four waves into shared colour-flow
  * amplitudes with atomic float64 adds and agrees from run to run to rounding).
  */
@@ -127,8 +127,8 @@ int me_set_precision(me_ctx *ctx, int mode, double rel_tol);
  * power of two with nevt * lanes >= 65536, at most 64 and at most the number
  * of helicities kept (one lane per event from 65536 events up).  The result
  * equals the one-lane result up to the order of the helicity sum.  Applies to
- * the float64 form of me_eval only (the mixed form, its float64 rerun,
- * me_eval_helicities and unweighting keep one lane per event).  Only
+ * the float64 form of me_eval only (not to the mixed form, its float64 rerun,
+ * me_eval_helicities and unweighting).  Only
  * "ee_mumu" is evaluated that way: the other processes always spread an event
  * over the lanes that suit them, and there the setting is accepted and every
  * setting gives the same result.  Errors:
@@ -203,9 +203,9 @@ int me_eval_mixed_noalloc(me_ctx *ctx, const double *momenta, int64_t nevt, doub
  *           J_h^dag C J_h (before averaging) for every helicity combination
  *           h in 0..nhel-1 (particle i has helicity + when bit (npart-1-i)
  *           of h is set), including those the filter dropped.
- * out_me2:  as in me_eval, but summed over all helicities (no filter).  Where
- *           me_eval sums over real polarisation vectors (every process but "ee_mumu") it is
- *           that sum, equal to the sum of out_qhel up to rounding.
+ * out_me2:  as in me_eval, but summed over all helicities (no filter): the sum of
+ *           out_qhel or, where a call with one lane per event would leave half of the
+ *           chip idle, as me_eval forms it; the two are equal up to rounding.
  */
 int me_eval_helicities(me_ctx *ctx, const double *momenta, int64_t nevt, double *out_me2, double *out_qhel,
                        void *stream);

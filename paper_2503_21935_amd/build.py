@@ -61,9 +61,9 @@ static hipError_t launch_sum(const double* mom, int64_t nevt, double* out, unsig
 }}
 
 static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
-                             const me_params& prm, double* qhel, int, hipStream_t s) {{
-    const dim3 grid((unsigned)((nevt + ME_BLOCK - 1) / ME_BLOCK));
-    hipLaunchKernelGGL((k_me_qew<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel);
+                             const me_params& prm, double* qhel, int lg, hipStream_t s) {{
+    const dim3 grid((unsigned)(((nevt << lg) + ME_BLOCK - 1) / ME_BLOCK));
+    hipLaunchKernelGGL((k_me_qew<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel, lg);
     return hipGetLastError();
 }}
 
@@ -71,7 +71,7 @@ static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_QEW, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, nullptr, nullptr, 8.0,
-    nullptr, nullptr, 0, nullptr, launch_sum, nullptr, false}};
+    nullptr, nullptr, 0, nullptr, launch_sum, nullptr, false, 65536}};
 #endif
 """
 
@@ -85,14 +85,14 @@ extern const me_process_desc me_desc_{name} = {{
     "{name}", {kind}, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, {idx_ptr}, {mixed_ptr}, {cest},
     {cm_ptr}, {mc_ptr}, {mc_n}, {mc_desc}, {sum_ptr}, {chan_ptr},
-    {mixed_part}}};
+    {mixed_part}, {hel_turn}}};
 #endif
 """
 
 _F64_GG = """static hipError_t launch_f64(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
-                             const me_params& prm, double* qhel, int, hipStream_t s) {{
-    const dim3 grid((unsigned)((nevt + ME_BLOCK - 1) / ME_BLOCK));
-    hipLaunchKernelGGL((k_me_gg<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel);
+                             const me_params& prm, double* qhel, int lg, hipStream_t s) {{
+    const dim3 grid((unsigned)(((nevt << lg) + ME_BLOCK - 1) / ME_BLOCK));
+    hipLaunchKernelGGL((k_me_gg<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel, lg);
     return hipGetLastError();
 }}
 """
@@ -238,9 +238,9 @@ def _chan_tu(name):
 
 _CM = """
 static hipError_t launch_f64_cm(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
-                                const me_params& prm, double* qhel, int, hipStream_t s) {{
-    const dim3 grid((unsigned)((nevt + ME_BLOCK - 1) / ME_BLOCK));
-    hipLaunchKernelGGL((k_me_gg_cm<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel);
+                                const me_params& prm, double* qhel, int lg, hipStream_t s) {{
+    const dim3 grid((unsigned)(((nevt << lg) + ME_BLOCK - 1) / ME_BLOCK));
+    hipLaunchKernelGGL((k_me_gg_cm<{proc}>), grid, dim3(ME_BLOCK), 0, s, mom, nevt, out, hels, nh, prm, qhel, lg);
     return hipGetLastError();
 }}
 """
@@ -270,7 +270,7 @@ hipError_t me_launch_sum_{name}(const double* mom, int64_t nevt, double* out, un
 extern const me_process_desc me_desc_{name} = {{
     "{name}", ME_KIND_GG, {proc}::npart, {proc}::ndiag, {proc}::ncol, {proc}::nhel,
     {proc}::flops_amp, {proc}::flops_colour, {proc}::flops_executed, launch_f64, nullptr, me_launch_mixed_{name}, {cest},
-    me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}, nullptr, false}};
+    me_launch_f64_cm_{name}, nullptr, 0, nullptr, me_launch_sum_{name}, nullptr, false, 16384}};
 #endif
 """
 
@@ -398,7 +398,8 @@ def generate_sources(processes):
         _write(path, _TU.format(name=name, include=inc, f64=f64, idx_ptr=idx_ptr, proc=proc, kind=kind, mixed=mixed,
                                 mixed_ptr=mixed_ptr, cest=MIXED_CEST.get(name, 8.0), cm=cm,
                                 cm_ptr=cm_ptr, mc_ptr=mc_ptr, mc_n=mc_n, mc_desc=mc_desc, sum_ptr=sum_ptr, chan_ptr=chan_ptr,
-                                mixed_part="false" if mixed_ptr == "nullptr" else "true"))
+                                mixed_part="false" if mixed_ptr == "nullptr" else "true",
+                                hel_turn=0 if name == "ee_mumu" else 65536))
         tus.append(path)
     decls = "\n".join(f"extern const me_process_desc me_desc_{n};" for n in processes)
     ptrs = ", ".join(f"&me_desc_{n}" for n in processes)

@@ -53,9 +53,7 @@ MEV double coop_colour(int wave, const double* Jl) {
 }
 
 // Arguments as for k_me_gg; launched with blocks of 64 * P::waves threads,
-// one block per 64 / 2^lg events (the callers ask for lg = 0; with the helicity
-// the same for all lanes the program gets branches and takes three times as long to
-// compile).  With lg > 0 the 2^lg
+// one block per 64 / 2^lg events.  With lg > 0 the 2^lg
 // lanes of an event take every 2^lg-th helicity of the list (the same count
 // of passes for every lane, so the barriers stay uniform; a lane past the end
 // of the list repeats its last helicity and discards the result).

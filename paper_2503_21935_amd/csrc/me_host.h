@@ -17,6 +17,17 @@ static inline void me_each_launch(int64_t nevt, int per, int threads, F&& f) {
     }
 }
 
+// Lanes per event (2^k) of a call that asks for single helicities: as many as keep it
+// within `turn` lanes, one turn of the chip (at most 64, at most one per helicity).  Such
+// a call takes the time of one lane's helicities, however few its events are (64 events of
+// g g -> t tbar g g 2.8 ms at one lane each, 0.06 at 64).  A call of half a turn or more
+// gains nothing: the VALU is busy with one wave per SIMD.
+static inline int me_turn_lanes_lg(int64_t nevt, int nhel, int64_t turn) {
+    int lg = 0;
+    while (lg < 6 && nevt <= (turn >> (lg + 1)) && (2 << lg) <= nhel) ++lg;
+    return lg;
+}
+
 // Buffers that grow together: their pointers and new sizes in bytes, `cap` the number of
 // elements they hold.  Frees the old ones and allocates new ones for n elements.  After
 // a failure cap is 0 and every pointer is null or a live buffer, so that the next

@@ -94,11 +94,17 @@ MEV double group_sum(double v, int lg) {
 
 // qhel (optional): per-helicity J^dag C J, [nevt][P::nhel], for the helicity
 // filter and for tests; entries of helicities not in the list are untouched.
+// lg: helicity parallelism, 2^lg lanes per event (0 <= lg <= 6): lane
+// g = lane % 2^lg of an event takes the helicities ih = g, g + 2^lg, ... of
+// the list, and the group's partial sums are added across its lanes at the
+// end, so a block of 64 lanes holds 64 / 2^lg events (the paper's
+// helicity-level parallelism, Sec. 2: fewer events in flight fill the GPU).
 template <class P>
 __global__ __launch_bounds__(ME_BLOCK) void k_me_gg(const double* __restrict__ mom, int64_t nevt,
                                                     double* __restrict__ out, const int* __restrict__ hels,
-                                                    int nh, me_params prm, double* __restrict__ qhel) {
-    const int64_t ev = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                                    int nh, me_params prm, double* __restrict__ qhel, int lg) {
+    const int grp = threadIdx.x & ((1 << lg) - 1);
+    const int64_t ev = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> lg;
     if (ev >= nevt) return;
     using T = double;
     constexpr int NG = P::ngluon;
@@ -108,9 +114,8 @@ __global__ __launch_bounds__(ME_BLOCK) void k_me_gg(const double* __restrict__ m
     gg_setup<P, T>(x, mom, ev, Qt, threadIdx.x, prm);
     T acc = T(0);
 #pragma unroll 1
-    for (int ih = 0; ih < nh; ++ih) {
-        int h = hels[ih];
-        asm volatile("" : "+v"(h));  // per-lane copy: selects instead of branches in the externals
+    for (int ih = grp; ih < nh; ih += 1 << lg) {
+        const int h = hels[ih];
         // The momenta are read from LDS where they are used: the
         // helicity-independent subexpressions are recomputed per helicity
         // instead of being hoisted out of the loop into registers.
@@ -123,20 +128,24 @@ __global__ __launch_bounds__(ME_BLOCK) void k_me_gg(const double* __restrict__ m
         if (qhel) qhel[ev * P::nhel + h] = double(q) / P::lcd;
         acc += q;
     }
-    out[ev] = double(acc) * (1.0 / (256.0 * P::identical * P::lcd));
+    // the lanes of one event are all valid or all returned above
+    const double tot = group_sum(double(acc), lg);
+    if (grp == 0) out[ev] = tot * (1.0 / (256.0 * P::identical * P::lcd));
 }
 
 // The same evaluation with the colour sum on the matrix cores: after each
 // helicity's program the wave stages its 64 lanes' J in LDS as
 // [flow][re, im][lane] and the four 16-lane column blocks go through
 // colour_mfma16 (float64 MFMA GEMM, me_colour_mfma.h).  The MFMA needs all 64
-// lanes, so lanes past the end repeat the last event (no store).
+// lanes, so lanes past the end repeat the last event (no store) and every
+// lane makes the same number of helicity passes.
 template <class P>
 __global__ __launch_bounds__(ME_BLOCK) void k_me_gg_cm(const double* __restrict__ mom, int64_t nevt,
                                                        double* __restrict__ out, const int* __restrict__ hels,
-                                                       int nh, me_params prm, double* __restrict__ qhel) {
+                                                       int nh, me_params prm, double* __restrict__ qhel, int lg) {
     const int lane = threadIdx.x;
-    int64_t ev = (int64_t)blockIdx.x * ME_BLOCK + lane;
+    const int grp = lane & ((1 << lg) - 1);
+    int64_t ev = ((int64_t)blockIdx.x * ME_BLOCK + lane) >> lg;
     const bool valid = ev < nevt;
     if (!valid) ev = nevt - 1;
     using T = double;
@@ -148,10 +157,12 @@ __global__ __launch_bounds__(ME_BLOCK) void k_me_gg_cm(const double* __restrict_
     gg_ext<T, NG> x;
     gg_setup<P, T>(x, mom, ev, Qt, lane, prm);
     T acc = T(0);
+    const int passes = (nh + (1 << lg) - 1) >> lg;
 #pragma unroll 1
-    for (int ih = 0; ih < nh; ++ih) {
-        int h = hels[ih];
-        asm volatile("" : "+v"(h));  // per-lane copy: selects instead of branches in the externals
+    for (int it = 0; it < passes; ++it) {
+        const int ih = grp + (it << lg);
+        const bool used = ih < nh;
+        const int h = hels[used ? ih : nh - 1];
         gg_externals<P, T>(x, h);
         cx<T> J[P::ncol];
 #pragma unroll
@@ -170,10 +181,11 @@ __global__ __launch_bounds__(ME_BLOCK) void k_me_gg_cm(const double* __restrict_
             const double p = colour_mfma_group_sum(colour_mfma16<P::ncol>(Jt, 16 * eb, frag, lane));
             if (eb == (lane >> 4)) q = p;  // this lane's own column
         }
-        if (qhel && valid) qhel[ev * P::nhel + h] = double(q) / P::lcd;
-        acc += q;
+        if (qhel && valid && used) qhel[ev * P::nhel + h] = double(q) / P::lcd;
+        acc += used ? q : T(0);
     }
-    if (valid) out[ev] = double(acc) * (1.0 / (256.0 * P::identical * P::lcd));
+    const double tot = group_sum(double(acc), lg);
+    if (valid && grp == 0) out[ev] = tot * (1.0 / (256.0 * P::identical * P::lcd));
 }
 
 // Multi-channel form: the program of P (the unmerged plan: one amplitude per
@@ -213,14 +225,9 @@ __global__ __launch_bounds__(ME_BLOCK) void k_me_gg_mc(const double* __restrict_
     alpha[ev] = num / den;
 }
 
-// qhel as for k_me_gg.
+// qhel and lg as for k_me_gg.
 // idx (optional): evaluate only events idx[0..*count) (the survivors
 // of a first stage of unweighting); out is indexed the same way.
-// lg: helicity parallelism, 2^lg lanes per event (0 <= lg <= 6): lane
-// g = lane % 2^lg of an event takes the helicities ih = g, g + 2^lg, ... of
-// the list, and the group's partial sums are added across its lanes at the
-// end, so a block of 64 lanes holds 64 / 2^lg events (the paper's
-// helicity-level parallelism, Sec. 2: fewer events in flight fill the GPU).
 template <class P>
 __global__ __launch_bounds__(ME_BLOCK) void k_me_ee(const double* __restrict__ mom, int64_t nevt,
                                                     double* __restrict__ out, const int* __restrict__ hels,

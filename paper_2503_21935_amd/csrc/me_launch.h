@@ -9,8 +9,7 @@
 
 #define ME_BLOCK 64
 
-// lg: 2^lg lanes per event, each summing every 2^lg-th helicity (0 <= lg <= 6), for
-// e+ e- -> mu+ mu-; the others are called for single helicities and have one lane.
+// lg: 2^lg lanes per event, each summing every 2^lg-th helicity (0 <= lg <= 6).
 typedef hipError_t (*me_launch_fn)(const double* mom, int64_t nevt, double* out, const int* hels, int nh,
                                    const me_params& prm, double* qhel, int lg, hipStream_t stream);
 
@@ -73,6 +72,8 @@ struct me_process_desc {
     me_launch_sum_fn launch_sum;      // spin sum with one event per wave (nullptr: none)
     me_launch_chan_fn launch_chan;    // multi-channel form with shared wavefunctions (nullptr: none)
     bool mixed_part;                  // launch_mixed makes use of `part`
+    int hel_turn;                     // lanes of launch_f64 that the chip runs at full rate: a wave per SIMD, or a
+                                      // workgroup per CU (0: single helicities take one lane per event)
 };
 
 const me_process_desc* me_find_process(const char* name);

@@ -2,7 +2,7 @@
 // processes (a massless quark line with gluons and one photon/Z insertion
 // decaying to a lepton pair; g ubar -> tau+ tau- g g ubar is the DY+3j
 // subprocess of the paper's Sec. 3).  One event per lane, helicities looped
-// as the gluon-process kernel: externals, the
+// (or spread over 2^lg lanes), as the gluon-process kernel: externals, the
 // generated diagram program into the colour-flow amplitudes J, the colour sum.
 #pragma once
 #include "me_kernels.h"
@@ -88,12 +88,13 @@ MEV void qew_externals(qew_ext<double, P::ngluon>& x, int h, const me_params& pr
     }
 }
 
-// qhel as for k_me_gg.
+// qhel and lg as for k_me_gg.
 template <class P>
 __global__ __launch_bounds__(ME_BLOCK) void k_me_qew(const double* __restrict__ mom, int64_t nevt,
                                                      double* __restrict__ out, const int* __restrict__ hels,
-                                                     int nh, me_params prm, double* __restrict__ qhel) {
-    const int64_t ev = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                                     int nh, me_params prm, double* __restrict__ qhel, int lg) {
+    const int grp = threadIdx.x & ((1 << lg) - 1);
+    const int64_t ev = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> lg;
     if (ev >= nevt) return;
     using T = double;
     constexpr int NG = P::ngluon;
@@ -103,9 +104,8 @@ __global__ __launch_bounds__(ME_BLOCK) void k_me_qew(const double* __restrict__ 
     qew_setup<P>(x, mom, ev, Qt, threadIdx.x, prm);
     T acc = T(0);
 #pragma unroll 1
-    for (int ih = 0; ih < nh; ++ih) {
-        int h = hels[ih];
-        asm volatile("" : "+v"(h));  // per-lane copy: selects instead of branches in the externals
+    for (int ih = grp; ih < nh; ih += 1 << lg) {
+        const int h = hels[ih];
         qew_externals<P>(x, h, prm);
         cx<T> J[P::ncol];
 #pragma unroll
@@ -115,5 +115,6 @@ __global__ __launch_bounds__(ME_BLOCK) void k_me_qew(const double* __restrict__ 
         if (qhel) qhel[ev * P::nhel + h] = double(q) / P::lcd;
         acc += q;
     }
-    out[ev] = double(acc) * (1.0 / (P::avg * P::lcd));
+    const double tot = group_sum(double(acc), lg);
+    if (grp == 0) out[ev] = tot * (1.0 / (P::avg * P::lcd));
 }

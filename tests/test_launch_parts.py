@@ -1,7 +1,7 @@
-"""Batches that need more threads than one launch may have (2^32).
-
-Kernels with several threads per event are launched in parts there: the parts
-tile the events without gap or overlap, each below the limit."""
+"""Rules of the host that lay out launches, checked without a device, and a batch
+that needs more threads than one launch may have (2^32): kernels with several
+threads per event are launched in parts there, which tile the events without
+gap or overlap, each below the limit."""
 import os
 import subprocess
 
@@ -14,6 +14,10 @@ PROGRAM = r"""
 #include <cstdlib>
 #include "me_host.h"
 int main(int argc, char** argv) {
+    if (argc > 4) {
+        std::printf("%d 0\n", me_turn_lanes_lg(std::atoll(argv[1]), std::atoi(argv[2]), std::atoll(argv[3])));
+        return 0;
+    }
     me_each_launch(std::atoll(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]),
                    [&](int64_t first, unsigned blocks) { std::printf("%lld %u\n", (long long)first, blocks); });
 }
@@ -27,8 +31,8 @@ def parts(tmp_path_factory):
     src.write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-I" + os.path.join(ROOT, "paper_2503_21935_amd", "csrc"), str(src), "-o", str(exe)], check=True)
 
-    def run(nevt, per, threads):
-        out = subprocess.run([str(exe), str(nevt), str(per), str(threads)], check=True, capture_output=True, text=True)
+    def run(*args):
+        out = subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True)
         return [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
 
     return run
@@ -43,6 +47,16 @@ def test_parts_tile_the_events(parts, nevt, per, threads):
         assert first == done and 0 < blocks and blocks * threads < 2**32
         done = min(nevt, first + blocks * per)
     assert done == nevt
+
+
+@pytest.mark.parametrize("turn", [65536, 16384, 0])
+@pytest.mark.parametrize("nhel", [16, 64, 128])
+@pytest.mark.parametrize("nevt", [1, 2, 255, 256, 257, 8192, 8193, 16384, 32767, 32768, 32769, 65536, 2**31 - 1])
+def test_lanes_of_single_helicities(parts, nevt, nhel, turn):
+    """The largest power of two that stays within one turn, 64 and the helicities."""
+    ((lg, _),) = parts(nevt, nhel, turn, "lanes")
+    fits = [k for k in range(7) if 1 << k <= nhel and (k == 0 or nevt << k <= turn)]
+    assert lg == max(fits)
 
 
 @pytest.mark.gpu
