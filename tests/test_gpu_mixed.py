@@ -162,3 +162,34 @@ def test_mixed_mode_ee_stays_float64(me_mod, torch_cuda):
         m.eval_mixed_diag(torch.from_numpy(mom).cuda())
     assert e.value.status == me_mod.ME_ESTATE
     m.close()
+
+
+@pytest.mark.parametrize("proc,n", [("gg_tt", 65), ("gg_ttg", 1000), ("gg_ttgg", 129)])
+def test_wavefunctions_of_every_helicity(me_mod, torch_cuda, proc, n):
+    """The float32 form with its wavefunctions kept for both helicities: events
+    whose final particles lie along either direction of the z axis among them,
+    where spinors and polarisations take their special values.  Within the
+    estimate's tolerance of the oracle where the estimate says so."""
+    torch = torch_cuda
+    mom = process_points(proc, n, 17)
+    # turn each event so that one final particle after the other lies along +z or -z
+    for i in range(n):
+        k = mom[i, 2 + i % (mom.shape[1] - 2), 1:].copy()
+        z = k / np.linalg.norm(k) * (1 if i % 2 else -1)
+        x = np.cross(z, [1.0, 0, 0] if abs(z[0]) < 0.6 else [0, 1.0, 0])
+        x /= np.linalg.norm(x)
+        rot = np.stack([x, np.cross(z, x), z])
+        mom[i, :, 1:] = mom[i, :, 1:] @ rot.T
+        mom[i, 2 + i % (mom.shape[1] - 2), 1:3] = 0.0
+    m = me_mod.MatrixElement(proc)
+    m.set_precision(me_mod.ME_MIXED, TOL)
+    t = torch.from_numpy(mom).cuda()
+    raw, est, flag = m.eval_mixed_diag(t)
+    got = m.eval(t)
+    torch.cuda.synchronize()
+    want = oracle.me2(proc, mom)
+    ok = flag.cpu().numpy() == 0
+    assert ok.mean() > 0.5
+    assert np.abs(raw.cpu().numpy()[ok] / want[ok] - 1).max() <= TOL
+    assert np.abs(got.cpu().numpy() / want - 1).max() <= TOL
+    m.close()
