@@ -27,13 +27,8 @@ static int fail(int code, const std::string& msg) { return me_fail(code, msg); }
     } while (0)
 
 // Grow the flagged-event index list to hold nevt entries (synchronises the
-// device when it has to reallocate).
-// With the index list, room for the helicities' values of as many events, at most
-// ME_PART_MAX bytes of it (2^18 events of 64 helicities; beyond, a few percent in
-// a last turn of blocks are not worth it).  Both grow in the same calls, so a
-// call that needed no allocation before needs none for these; without them
-// (no memory, or more events) the mixed form works all the same.
-#define ME_PART_MAX ((size_t)128 << 20)
+// device when it has to reallocate).  The room for the helicities' values goes
+// with the list: what a captured graph holds lives until the list grows.
 static int ensure_scratch(me_ctx* c, int64_t nevt) {
     if (!c->d_count) HIP_CHECK(hipMalloc(&c->d_count, sizeof(int)));
     if (nevt > c->idx_cap) {
@@ -43,22 +38,45 @@ static int ensure_scratch(me_ctx* c, int64_t nevt) {
             c->d_idx = nullptr;
             c->idx_cap = 0;
         }
+        if (c->d_part) {
+            void* old = c->d_part;
+            c->d_part = nullptr;
+            HIP_CHECK(hipFree(old));
+        }
+        c->part_cap = 0;
+        c->part_asked = false;
         HIP_CHECK(hipMalloc(&c->d_idx, nevt * sizeof(int)));
         c->idx_cap = nevt;
-        const size_t want = std::min((size_t)nevt * c->nhel_good, ME_PART_MAX / sizeof(float2));
-        if (c->proc->mixed_part && want > c->part_cap) {
-            if (c->d_part) HIP_CHECK(hipFree(c->d_part));  // the device is idle: synchronised above
-            c->d_part = nullptr;
-            c->part_cap = 0;
-            if (hipMalloc(&c->d_part, want * sizeof(float2)) == hipSuccess) {
-                c->part_cap = want;
-            } else {
-                c->d_part = nullptr;
-                (void)hipGetLastError();
-            }
-        }
     }
     return ME_OK;
+}
+
+// Room for two floats per helicity and event of a mixed call that parts its helicities
+// over blocks, or null: the call does not, or would need more than ME_PART_MAX (2^18
+// events of 64 helicities; beyond, one lane takes all helicities and most of a turn of
+// blocks may be lost, a sixth of the time at 270,000 events).
+// Allocated by the first call that makes use of it, for all that the index list has
+// room for, so that it is not moved before the list is; the call need not be one that grows
+// the list, so it may come while a stream is being captured (hence the mode).
+// Without memory for it the mixed form works all the same.
+#define ME_PART_MAX ((size_t)128 << 20)
+static float2* part_room(me_ctx* c, int64_t nevt) {
+    const size_t most = ME_PART_MAX / sizeof(float2), need = (size_t)nevt * c->nhel_good;
+    if (!c->proc->mixed_part || need > most || mixed_per_block(nevt, c->nhel_good) >= c->nhel_good) return nullptr;
+    if (!c->d_part && !c->part_asked) {
+        c->part_asked = true;
+        const size_t want = std::min((size_t)c->idx_cap * c->nhel_good, most);
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
+            if (hipMalloc(&c->d_part, want * sizeof(float2)) == hipSuccess)
+                c->part_cap = want;
+            else
+                c->d_part = nullptr;
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+        }
+        if (!c->d_part) (void)hipGetLastError();
+    }
+    return need <= c->part_cap ? c->d_part : nullptr;
 }
 
 // ---------------------------------------------------------------------------
@@ -274,6 +292,7 @@ int me_init(const char* process, const double* couplings, int n_couplings, const
     c->idx_cap = 0;
     c->d_part = nullptr;
     c->part_cap = 0;
+    c->part_asked = false;
     c->uw_y = nullptr;
     c->uw_s = nullptr;
     c->uw_me2 = nullptr;
@@ -314,7 +333,7 @@ int me_eval(me_ctx* c, const double* momenta, int64_t nevt, double* out_me2, voi
         if (rc != ME_OK) return rc;
         HIP_CHECK(c->proc->launch_mixed(momenta, nevt, out_me2, c->d_good, c->nhel_good, c->prm, (float)c->tol,
                                         (float)c->proc->mixed_cest, c->d_count, c->d_idx, nullptr, nullptr,
-                                        (size_t)nevt * c->nhel_good <= c->part_cap ? c->d_part : nullptr, s));
+                                        part_room(c, nevt), s));
         // float64 rerun of the flagged events, in place, on the same stream
         HIP_CHECK(me_launch_idx(c, momenta, nevt, out_me2, c->d_idx, c->d_count, s));
         return ME_OK;

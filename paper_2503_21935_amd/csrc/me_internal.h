@@ -34,6 +34,7 @@ struct me_ctx {
     int64_t idx_cap;
     float2* d_part;  // values per helicity and event (part of launch_mixed)
     size_t part_cap;  // of them
+    bool part_asked;  // allocated, or refused, since the index list was
     // scratch of two-stage unweighting
     float* uw_y;
     double* uw_s;

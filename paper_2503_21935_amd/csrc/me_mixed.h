@@ -333,22 +333,6 @@ __global__ __launch_bounds__(64) void k_mixed_sum(const float2* __restrict__ par
     mixed_result<P>(ev, valid, threadIdx.x, acc, dacc, tol, out, flag_count, flag_idx, err_out, flag_out);
 }
 
-// Helicities per block where their values are added by a kernel of their own
-// (nh: not done).  One wave takes 45 us per helicity of g g -> t tbar g g and the
-// chip holds 1024 of these waves, so a call of up to 65,536 events took the 2.9 ms
-// of 64 helicities in turn (64 events now 72 us, 16,384 0.81 ms, with the
-// rerun), and one of a few more than a multiple of it a whole turn more (70,000
-// events 3.3 ms against 5.8).  Where the last turn is not nearly full the list is
-// parted until there are 8 turns of blocks, whose setup is a tenth of a
-// helicity's work; where it is full that costs 2 % (131,072 events 6.0 ms against 5.9).
-static inline int mixed_per_block(int64_t nevt, int nh) {
-    const int64_t tiles = (nevt + ME_BLOCK - 1) / ME_BLOCK, turns = (tiles + 1023) / 1024;
-    int per = nh;
-    if (10 * 1024 * turns <= 11 * tiles) return per;
-    while (per > 1 && tiles * ((nh + per - 1) / per) < 8 * 1024) per = (per + 1) / 2;
-    return per;
-}
-
 static __global__ void k_zero_int(int* p) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0;
 }
