@@ -25,6 +25,12 @@
  *     Inputs are not validated kinematically; NaN/Inf propagate to NaN
  *     outputs without trapping.
  *   - A context is used by one host thread at a time; me_init is thread-safe.
+ *   - me_eval in the mixed form and unweight_two_stage work in scratch memory of
+ *     the context (index lists, and values of the results themselves): two such calls on one
+ *     context that may overlap on the device (on different streams, or as replays of a
+ *     captured graph) race, and must be ordered by the caller; with a context per
+ *     stream they need not be.  The float64 form of me_eval,
+ *     me_eval_helicities, me_eval_multichannel and me_eval_mixed_diag touch no scratch.
  */
 #ifndef ME_H
 #define ME_H
@@ -112,6 +118,8 @@ int me_eval(me_ctx *ctx, const double *momenta, int64_t nevt, double *out_me2, v
  *   without a mixed form (e+e- -> mu+mu-) keep evaluating in float64.
  *   Mixed evaluation keeps a flagged-event index list in the context; it grows
  *   on the first call with a larger nevt (that call synchronises the device).
+ *   Calls of up to 2^18 events (of 64 helicities) may also keep the helicities' values
+ *   there, 128 MiB at most.  Calls on one context must not overlap (see above).
  * Errors: ME_EINVAL (unknown mode, rel_tol <= 0 for ME_MIXED).
  */
 int me_set_precision(me_ctx *ctx, int mode, double rel_tol);

@@ -266,7 +266,11 @@ def me_free(ctx) -> None:
 
 class MatrixElement:
     """One process on the current GPU.  ``eval`` takes float64 momenta
-    [nevt][npart][4] on the device and returns |M|^2 [nevt] (float64)."""
+    [nevt][npart][4] on the device and returns |M|^2 [nevt] (float64).
+
+    In the mixed form (``set_precision``) ``eval`` works in scratch memory of this
+    object, as ``unweight_two_stage`` does: calls that may overlap, on different
+    streams, need an object each."""
 
     def __init__(self, process: str, couplings=DEFAULT_COUPLINGS, masses=DEFAULT_MASSES):
         self.process = process

@@ -73,3 +73,19 @@ def test_first_parted_call_under_capture(env):
         torch.cuda.synchronize()
     del g
     m.close()
+
+
+def test_two_contexts_on_two_streams(env):
+    """Overlapping parted calls, each on a context of its own."""
+    torch, me, mom = env
+    a, b = mixed(me), mixed(me)
+    want_a, want_b = a.eval(mom[:20000]), b.eval(mom[500:9000])
+    streams = torch.cuda.Stream(), torch.cuda.Stream()
+    outs = [(torch.empty_like(want_a), torch.empty_like(want_b)) for _ in range(4)]
+    torch.cuda.synchronize()
+    for oa, ob in outs:
+        a.eval(mom[:20000], oa, stream=streams[0])
+        b.eval(mom[500:9000], ob, stream=streams[1])
+    torch.cuda.synchronize()
+    assert all(torch.equal(oa, want_a) and torch.equal(ob, want_b) for oa, ob in outs)
+    a.close(), b.close()
