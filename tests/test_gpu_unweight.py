@@ -74,3 +74,31 @@ def test_another_network_under_capture(env):
         assert r[0] == want[0] and np.array_equal(r[1], want[1]) and np.array_equal(r[2], want[2])
     del g
     m.close(), one.close(), layered.close()
+
+
+@pytest.mark.parametrize("proc,n", [("ee_mumu", 1500), ("gg_tt", 3001), ("gg_ttg", 3001), ("gg_ttgg", 2049),
+                                    ("gg_ttggg", 500), ("gux_taptamux", 3001), ("gux_taptamgux", 1025),
+                                    ("gux_taptamggux", 2000)])
+@pytest.mark.parametrize("width,depth", [(256, 4), (256, 6), (128, 2)])
+def test_every_process_and_form_of_network(env, proc, n, width, depth):
+    """Survivors (a part of the points, so that the exact weights go through a list) and
+    their weights, from the network's outputs on the features and me_eval's |M|^2.
+    The network gives the same bits from momenta as from features, and the exact
+    kernels from a list as from all points; exponential and products may differ by
+    rounding, so the weights agree to 1e-12 and no decision lies within 1e-12 of its bound."""
+    torch, me = env
+    print(f"[uw] {proc} width={width} depth={depth}", flush=True)
+    s = Sample(torch, me, proc, n, 83)
+    m, net = me.MatrixElement(proc), me.Surrogate(s.mom.shape[1] * 4, width, depth, 7)
+    s.thresholds(m, net)
+    s.run(m, net)
+    first, idx, wt = s.result()
+    p1, p2 = (s.s / s.s_max).clamp(max=1.0), (s.r / s.r_max).clamp(max=1.0)
+    assert not bool((((s.u[:, 0] / p1 - 1).abs() < 1e-12) | ((s.u[:, 1] / p2 - 1).abs() < 1e-12)).any())
+    one = s.u[:, 0] < p1
+    both = (one & (s.u[:, 1] < p2)).nonzero()[:, 0]
+    assert 0 < len(both) < first < n
+    assert first == int(one.sum()) and np.array_equal(idx, both.cpu().numpy())
+    want = (s.s / s.s_max).clamp(min=1.0) * (s.r / s.r_max).clamp(min=1.0)
+    np.testing.assert_allclose(wt, want[both].cpu().numpy(), rtol=1e-12)
+    m.close(), net.close()
