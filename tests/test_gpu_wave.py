@@ -147,3 +147,43 @@ def test_mixed_form_with_its_helicities_parted(env, proc, n):
     assert torch.equal(got[keep], raw[keep])
     assert torch.equal(m.eval(mom), got)
     m.close()
+
+
+@pytest.mark.parametrize("proc,n", [("gg_ttgg", 4097), ("gg_ttgg", 8193), ("gg_ttgg", 20000), ("gg_ttggg", 1025),
+                                    ("gg_ttggg", 2050)])
+def test_matrix_core_colour_sum_of_many_events(env, proc, n):
+    """Blocks with two events set up together, blocks that stride over the events, and
+    the staging of J used again behind the next event's preparation.  61 points over and
+    over: every copy has the bits of the first, in whichever slot of a block; the two
+    colour forms agree as two float64 evaluations do."""
+    torch, me = env
+    print(f"[wave] colour {proc} n={n}", flush=True)
+    pts = process_points(proc, 61, 67)
+    mom = torch.from_numpy(np.tile(pts, (-(-n // 61), 1, 1))[:n].copy()).cuda()
+    m = me.MatrixElement(proc)
+    got = {}
+    for form in (me.ME_COLOUR_VALU, me.ME_COLOUR_MFMA):
+        m.set_colour_form(form)
+        out = torch.full((n + 64,), -7.0, dtype=torch.float64, device="cuda")
+        me.me_eval(m.ctx, mom, n, out)
+        assert bool((out[n:] == -7.0).all())
+        first = out[:61]
+        assert all(torch.equal(out[k:min(k + 61, n)], first[:min(61, n - k)]) for k in range(0, n, 61))
+        got[form] = first.cpu().numpy()
+    close(got[me.ME_COLOUR_MFMA], got[me.ME_COLOUR_VALU])
+    close(got[me.ME_COLOUR_MFMA][:4], oracle.me2(proc, pts[:4]))
+    m.close()
+
+
+@pytest.mark.parametrize("proc,n", [("gg_tt", 300), ("gg_ttg", 300), ("gg_ttgg", 300), ("gg_ttggg", 60),
+                                    ("gux_taptamux", 300), ("gux_taptamgux", 300), ("gux_taptamggux", 300)])
+def test_lanes_setting_changes_nothing(env, proc, n):
+    """Accepted for every process, in effect for e+ e- -> mu+ mu- alone."""
+    torch, me = env
+    m = me.MatrixElement(proc)
+    mom = torch.from_numpy(process_points(proc, n, 68)).cuda()
+    want = m.eval(mom)
+    for lanes in (1, 4, 64, 0):
+        m.set_helicity_lanes(lanes)
+        assert torch.equal(m.eval(mom), want)
+    m.close()
