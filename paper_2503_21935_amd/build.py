@@ -163,6 +163,15 @@ _LAUNCH_GROUP = """    const dim3 grid((unsigned)(nevt < ME_GROUP_BLOCKS ? nevt 
         hipLaunchKernelGGL(({kernel}<proc_{name}, false>), grid, dim3(w5::THREADS), 0, s, mom, nevt, out, spins, prm,
                            idx, count);
 """
+# the same with four lanes per event, while the call is within one wave per SIMD that way
+_LAUNCH_FEW = """    if (nevt <= 16384) {{
+        me_each_launch(nevt, 16, 64, [&](int64_t first, unsigned blocks) {{
+            hipLaunchKernelGGL(({kernel}<proc_{name}, void, 4>), dim3(blocks), dim3(64), 0, s, mom, nevt, out, spins,
+                               prm, idx, count, first, nullptr, nullptr);
+        }});
+        return hipGetLastError();
+    }}
+"""
 # several events per wave
 _LAUNCH_LANES = """    (void)mfma;
     me_each_launch(nevt, {per}, 64, [&](int64_t first, unsigned blocks) {{
@@ -174,8 +183,9 @@ _LAUNCH_LANES = """    (void)mfma;
 
 def _wave_tu(name):
     if name in EVENTS_PER_WAVE:
+        launch = (_LAUNCH_FEW if name == "gg_tt" else "") + _LAUNCH_LANES
         return _TU_WAVE.format(name=name, header="me_gg_pol.h",
-                               launch=_LAUNCH_LANES.format(name=name, kernel=WAVE[name], per=EVENTS_PER_WAVE[name]))
+                               launch=launch.format(name=name, kernel=WAVE[name], per=EVENTS_PER_WAVE[name]))
     group = name in COOP
     launch = (_LAUNCH_GROUP if group else _LAUNCH_WAVE).format(name=name, kernel=WAVE[name])
     return _TU_WAVE.format(name=name, header="me_wave5.h" if group else "me_wave.h", launch=launch)

@@ -2,7 +2,7 @@
 // polarisation vectors.  Rules, signs and the row form of columns as in
 // me_wave.h.
 //
-// Two gluons: one event per lane, everything in registers.  The configurations
+// Two gluons: one event per lane (small calls: four lanes), everything in registers.  The configurations
 // share four one-gluon rows per ordering and spin.
 //   J_ab = L(a) W(b) v + ubar W(ab) v.
 // Three gluons: eight lanes per event, lane l the gluon polarisations l; the
@@ -47,7 +47,10 @@ MEV void currents_e(const row& f, const row& r, const vec& e1, const vec& e2, c2
 // idx, count and spins as for k_me_gg4_wave; first0: the launch's first event (or
 // entry of idx).  With IDS (the channel numbers of
 // the diagrams) also the single-diagram weight of each event's channel, as k_me_gg4_chan.
-template <class P, class IDS = void>
+// LANES: lanes per event, one for all spin pairs or four with one each, for calls
+// that leave most of the chip idle (2,049 events 4.9 us instead of 7.8; one helicity per
+// lane 5.7).  The pairs are added in the same order either way.
+template <class P, class IDS = void, int LANES = 1>
 __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__ mom, int64_t nevt,
                                                       double* __restrict__ out, unsigned spins, me_params prm,
                                                       const int* __restrict__ idx, const int* __restrict__ count,
@@ -56,7 +59,8 @@ __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__
                                                       double* __restrict__ alpha = nullptr) {
     using namespace g2;
     static_assert(P::ngluon == 2 && P::ncol == 2, "two gluons");
-    int64_t ev = first0 + (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const int64_t at = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    int64_t ev = first0 + at / LANES;
     if (count) {
         if (ev >= *count) return;
         ev = idx[ev];
@@ -64,6 +68,7 @@ __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__
         return;
     }
     constexpr bool MC = !std::is_void_v<IDS>;
+    static_assert(LANES == 1 || (LANES == 4 && !MC), "the weights are summed by one lane");
     const double m = prm.mt;
     const int ch = MC ? chan[ev] : 0;
     double num = 0.0, den = 0.0;
@@ -81,11 +86,18 @@ __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__
         };
         q[0] = ld(0), q[1] = ld(1), p3 = ld(2), p4 = ld(3);
     }
-    row n3[2], n4[2];  // end rows by spin
-    each<2>([&](auto S) __attribute__((always_inline)) {
-        n3[S] = end_row(p3, m, 0, S ? 1 : -1);
-        n4[S] = end_row(p4, m, 1, S ? 1 : -1);
-    });
+    // end rows by spin, or of this lane's spins
+    const int l = (int)threadIdx.x & (LANES - 1);
+    row n3[2], n4[2];
+    if constexpr (LANES == 1) {
+        each<2>([&](auto S) __attribute__((always_inline)) {
+            n3[S] = end_row(p3, m, 0, S ? 1 : -1);
+            n4[S] = end_row(p4, m, 1, S ? 1 : -1);
+        });
+    } else {
+        n3[0] = end_row(p3, m, 0, (l & 2) ? 1 : -1);
+        n4[0] = end_row(p4, m, 1, (l & 1) ? 1 : -1);
+    }
     vec e[2][2], K[2];
     c2 f[2];
     each<2>([&](auto A) __attribute__((always_inline)) {
@@ -104,40 +116,57 @@ __global__ __launch_bounds__(64, 2) void k_me_gg2_pol(const double* __restrict__
             w[PP] = mul(iq, t);
         });
     }
-    // Spin by spin: the rows L of all sixteen at once do not fit in registers (2^20
-    // events took 126 us).  The other end enters through the current of L with it,
-    // which both polarisations of the second gluon share (92 us; 110 with the
-    // end's rows slashed by each of them).
-    double acc = 0.0;
-    each<2>([&](auto S3) __attribute__((always_inline)) {
-        settle(n4[0].s), settle(n4[1].s);  // what is formed from them is not kept for the other spin
-        row L[2][2];  // L(a) up to the sign, by gluon and polarisation
+    // L(a) up to the sign, by gluon and polarisation, at one spin of t
+    auto lines = [&](const row& u, row(&L)[2][2]) __attribute__((always_inline)) {
         each<4>([&](auto I) __attribute__((always_inline)) {
-            L[I / 2][I % 2] = scale(f[I / 2], slash_m(slash_e<I % 2>(n3[S3], e[I / 2][I % 2]), K[I / 2], m));
+            L[I / 2][I % 2] = scale(f[I / 2], slash_m(slash_e<I % 2>(u, e[I / 2][I % 2]), K[I / 2], m));
         });
-        each<2>([&](auto S4) __attribute__((always_inline)) {
-            c2 t[4], J01[4], J10[4];  // by polarisations
-            {
-                const row V = current(n3[S3], n4[S4]);
-                each<4>([&](auto PP) __attribute__((always_inline)) { t[PP] = cdot(V, w[PP]); });
-                settle(t);
-            }
-            each<2>([&](auto A) __attribute__((always_inline)) {
-                currents_e(L[0][A], n4[S4], e[1][0], e[1][1], J01[A], J01[A + 2]);
-                currents_e(L[1][A], n4[S4], e[0][0], e[0][1], J10[2 * A], J10[1 + 2 * A]);
-            });
-            settle(J01), settle(J10);
-            double part = 0.0;
-            each<4>([&](auto PP) __attribute__((always_inline)) {
-                if constexpr (MC) found(IDS::tree[0], t[PP]), found(IDS::order[0], J01[PP]), found(IDS::order[1], J10[PP]);
-                c2 J[2] = {J01[PP] - t[PP], J10[PP] + t[PP]};  // (both with the sign of L)
-                part += P::colour_blocks(J);
-            });
-            acc += ((spins >> (S3 + 2 * S4)) & 1) ? part : 0.0;
-            asm volatile("" : "+v"(acc));  // or the sums sink below the next ones, their operands held
+    };
+    // colour sum over the polarisations at one spin pair
+    auto spin_pair = [&](const row& u, const row& v, const row(&L)[2][2]) __attribute__((always_inline)) {
+        c2 t[4], J01[4], J10[4];  // by polarisations
+        {
+            const row V = current(u, v);
+            each<4>([&](auto PP) __attribute__((always_inline)) { t[PP] = cdot(V, w[PP]); });
+            settle(t);
+        }
+        each<2>([&](auto A) __attribute__((always_inline)) {
+            currents_e(L[0][A], v, e[1][0], e[1][1], J01[A], J01[A + 2]);
+            currents_e(L[1][A], v, e[0][0], e[0][1], J10[2 * A], J10[1 + 2 * A]);
         });
-    });
-    out[ev] = acc * (1.0 / (256.0 * P::identical * P::lcd));
+        settle(J01), settle(J10);
+        double part = 0.0;
+        each<4>([&](auto PP) __attribute__((always_inline)) {
+            if constexpr (MC) found(IDS::tree[0], t[PP]), found(IDS::order[0], J01[PP]), found(IDS::order[1], J10[PP]);
+            c2 J[2] = {J01[PP] - t[PP], J10[PP] + t[PP]};  // (both with the sign of L)
+            part += P::colour_blocks(J);
+        });
+        return part;
+    };
+    double acc = 0.0;
+    if constexpr (LANES == 1) {
+        // Spin by spin: the rows L of all sixteen at once do not fit in registers (2^20
+        // events took 126 us).  The other end enters through the current of L with it,
+        // which both polarisations of the second gluon share (92 us; 110 with the
+        // end's rows slashed by each of them).
+        each<2>([&](auto S3) __attribute__((always_inline)) {
+            settle(n4[0].s), settle(n4[1].s);  // what is formed from them is not kept for the other spin
+            row L[2][2];
+            lines(n3[S3], L);
+            each<2>([&](auto S4) __attribute__((always_inline)) {
+                const double part = spin_pair(n3[S3], n4[S4], L);
+                acc += ((spins >> (S3 + 2 * S4)) & 1) ? part : 0.0;
+                asm volatile("" : "+v"(acc));  // or the sums sink below the next ones, their operands held
+            });
+        });
+    } else {
+        row L[2][2];
+        lines(n3[0], L);
+        double part = spin_pair(n3[0], n4[0], L);
+        part = ((spins >> ((l >> 1) + 2 * (l & 1))) & 1) ? part : 0.0;
+        each<4>([&](auto S) __attribute__((always_inline)) { acc += __shfl(part, S, 4); });
+    }
+    if (l == 0) out[ev] = acc * (1.0 / (256.0 * P::identical * P::lcd));
     if constexpr (MC) alpha[ev] = num / den;
 }
 
