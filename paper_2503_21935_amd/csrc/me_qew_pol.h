@@ -14,8 +14,9 @@
 //
 // Against one helicity per pass over the diagram program (k_me_qew) this is
 // about a tenth of the arithmetic: 2^20 events of g ubar -> tau+ tau- g g ubar
-// take 0.93 ms against 8.73 ms.  2,790 vector instructions per wave of eight
-// events, the VALU active 89 % of the time: bound by VALU issue.  Eight lanes
+// take 0.88 ms (0.96 to 1.1 when the clock has come down under a longer load) against
+// 8.73 ms.  3,430 vector instructions per wave of eight
+// events, the VALU active 91 % of the time: bound by VALU issue.  Eight lanes
 // share the externals in LDS; each lane forms its own currents and rows, since
 // sharing those too would save less than a fifth and cost a barrier per stage.
 #pragma once

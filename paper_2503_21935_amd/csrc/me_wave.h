@@ -24,9 +24,9 @@
 // over the products for configuration l (bits 0..3 the polarisations, 4 and 5
 // the spins of t and tbar) and takes the colour sum.  Against one helicity per
 // lane with every wavefunction computed per helicity (k_me_gg) this is about a
-// sixth of the arithmetic: 2^18 events take 1.79 ms against 11.1 ms, 48 events
-// (one wave's time) 15 us against 45 us.  Bound by VALU issue: 2,690 vector
-// instructions per event and wave, the VALU active 80 % of the time with two
+// sixth of the arithmetic: 2^18 events take 1.59 ms against 11.3 ms, 48 events
+// (one wave's time) 12 us against 45 us.  Bound by VALU issue: 2,690 vector
+// instructions per event and wave, the VALU active 76 % of the time with two
 // waves per SIMD (LDS capacity and registers allow no third).
 //
 // Columns are held as rows: with B = diag(eps, -eps) one has
@@ -398,7 +398,7 @@ MEV void gg4_setup(double2* T, const double* __restrict__ mom, int64_t base, int
 
 }  // namespace wv
 
-// idx, count as for k_me_gg.  spins: bit s3 + 2 s4 set for the spin pairs of t
+// idx, count as for k_me_ee.  spins: bit s3 + 2 s4 set for the spin pairs of t
 // and tbar that the helicity filter kept.  Blocks of one wave stride over the
 // events, eb (1 or 2) at a time.  CM: colour sum on the matrix cores from J
 // staged in LDS.

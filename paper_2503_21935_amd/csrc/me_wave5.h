@@ -19,16 +19,16 @@
 // Klein four-group and the reversal split the 120 x 120 form into eight blocks.
 // 159 kB of LDS: one workgroup per CU, three waves per SIMD.
 //
-// Measured: 2^15 events in 3.50 ms (9.4e6 per second) where the kernel with one
+// Measured: 2^15 events in 3.45 ms (9.5e6 per second) where the kernel with one
 // event per lane and a diagram program split over four waves (k_me_gg_coop)
-// takes 37 ms, 64 events in 33 us against 280 us.  An event takes a CU about 65,000
-// cycles: 38,000 vector instructions, the VALU active half the time; the rest
+// takes 37 ms, 64 events in 31 us against 280 us.  An event takes a CU about 65,000
+// cycles: 38,000 vector instructions, the VALU active 60 % of the time; the rest
 // is barriers between some twenty stages and the latency of LDS and tables
 // that three waves per SIMD leave open.  168 registers per lane are what three
 // waves leave; what was kept from phase to phase (lane indices, 64-bit table
 // addresses, the second unit's sums while the next event is prepared) spilled
 // 136 bytes per lane, now 100: 50,021 events write 1.0 GB of it instead of 2.7
-// and take 5.33 ms instead of 5.56.
+// and took 5.33 ms instead of 5.56 (now 5.26, with the priority of the preparing waves).
 #pragma once
 #include "gen/proc_gg_ttggg_wave.h"
 #include "me_wave.h"
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(w5::THREADS) void k_me_gg5_wave(const double* __res
         here();
         words<1> wx[2] = {ld_words<1>(tab_X3, N_X3, tid), ld_words<1>(tab_X3, N_X3, tid2())};
         // A chain of divisions and roots on few lanes: the wave issues it first, or the others wait for
-        // it at the barrier (50,021 events 5.31 -> 5.25 ms; any other wave or phase so raised is slower).
+        // it at the barrier (50,021 events 5.31 -> 5.26 ms; any other wave or phase so raised is slower).
         if (ahead) {
             __builtin_amdgcn_s_setprio(2);
             prepare0(T, NEXT, wave - 8, incoming(lane), lane, prm);

@@ -478,13 +478,14 @@ __global__ void k_to_bf16_t(const float* __restrict__ theta, int64_t o, int rows
 // barrier inside a step, one between steps).  The batch's rows are
 // independent through the whole forward and backward chain, so phase 1 gives
 // each block tiles of FT_R rows and carries them through every layer forward
-// (activations and pre-activations in LDS), the output layer and loss, and
+// (activations, and the derivatives of the activation functions, in LDS), the output layer and loss, and
 // every layer backward down to the first pre-activation gradient, reading the
 // BF16 weights (and their transposes) in MFMA fragment order from L2, each
 // layer's fragments loaded during the previous layer's epilogue.  Each tile's
-// activations and gradients also go to global memory transposed
-// ([feature][batch], fragment order, written from LDS), and its share of the
-// output layer's gradient to a per-tile partial.  The only cross-row work is
+// activations (but the last layer's) and gradients also go to global memory transposed
+// ([feature][batch], fragment order, from the registers that hold them; the input from
+// LDS), and its share of the output layer's gradient to a per-tile partial.  The
+// only cross-row work is
 // the weight and bias gradients, sums over the batch: after the barrier,
 // phase 2 computes them as GEMMs dW_l = dZ_l^T H_{l-1} on 32 x 32 tiles, one
 // per block, each wave over a quarter of the batch; the quarters are added in
@@ -497,8 +498,9 @@ __global__ void k_to_bf16_t(const float* __restrict__ theta, int64_t o, int rows
 // 1 us per product is one CU's share of the weights through its L1 and 5 the
 // first reads after the barrier, which come from memory; 11 in phase 2 (half a
 // megabyte of operands per block); the rest the two barriers with their cache
-// write-back and invalidation.  What the 27 us were: the loss added in one chain of
-// dependent loads by a block with an item of its own (20), 256 LDS reads for 16
+// write-back and invalidation.  What the 27 us were, by stamps of single blocks, which
+// run beside each other, so that the parts add up to more: the loss added in one
+// chain of dependent loads by a block with an item of its own (20), 256 LDS reads for 16
 // partial losses (2), operands left dirty for the barrier to write back (3),
 // moments read and written in every step (2), registers spilled to memory
 // that each barrier's invalidation makes cold, and loads under conditions that
@@ -506,7 +508,7 @@ __global__ void k_to_bf16_t(const float* __restrict__ theta, int64_t o, int rows
 // ---------------------------------------------------------------------------
 #define FT_R 16        // rows per phase-1 tile
 #define FT_S 4         // batch quarters of the weight-gradient sums, one per wave
-#define FT_MAXDEPTH 4  // pre-activations of every layer stay in LDS
+#define FT_MAXDEPTH 4  // the derivatives of every layer's activations stay in LDS
 
 struct ft_args {
     const float* x;           // [*][n_in]
@@ -600,9 +602,11 @@ __device__ __forceinline__ void ft_grid_sync(unsigned* bar, F&& meanwhile) {
     __syncthreads();
 }
 
-// Four batch rows of a feature, batch tile m0, to the [feature][batch] array dst in fragment order with K = M.  Written through
-// to memory as it is produced (17 MB per step in all): left dirty in the L2,
-// it is written back at the grid barrier, where every block waits for it.
+// Four batch rows of a feature, batch tile m0, to the [feature][batch] array dst in
+// fragment order with K = M.  Written through to memory as it is produced (three
+// layers' activations and four layers' gradients, 14.7 MB per step at depth 4 and 4096
+// rows): left dirty in the L2, it is written back at the grid barrier, where every
+// block waits for it.
 // Feature 16 f + li (f the same in the whole wave), rows 4 lg .. 4 lg + 3.
 __device__ __forceinline__ void ft_store4(bf16x4 h, int f, int li, int lg, bf16* dst, int64_t M, int64_t m0) {
     const int b = (int)(m0 & 31) + 4 * lg;
