@@ -84,17 +84,19 @@ def counters(process):
 
 
 def roofline(process, nevt, k_s):
-    """Counted HBM bytes per launch and executed float64 operations per event (from
+    """HBM bytes and executed float64 operations of a launch of nevt events, scaled
+    from the counted launch, and the rate that makes at k_s seconds per launch (from
     the counters: the kernels share wavefunctions between spins, so the
-    operation count of one program per helicity says nothing about them), and
-    the rate that makes at k_s seconds per launch; None without counters."""
+    operation count of one program per helicity says nothing about them); None
+    without counters."""
     rec = counters(process)
     if not rec:
         return {"traffic": None, "executed_flops_per_event": None, "achieved": None, "frac": None}
     ops = rec["fp64_flops_per_event"]
     achieved = ops * nevt / k_s / 1e12
-    return {"traffic": rec["fetch_kib"] * rec["fetch_factor"] * 1024 + rec["write_kib"] * rec["write_factor"] * 1024,
-            "executed_flops_per_event": ops, "achieved": achieved, "frac": achieved / PEAK["fp64"]}
+    counted = rec["fetch_kib"] * rec["fetch_factor"] * 1024 + rec["write_kib"] * rec["write_factor"] * 1024
+    return {"traffic": counted / rec["events"] * nevt, "executed_flops_per_event": ops, "achieved": achieved,
+            "frac": achieved / PEAK["fp64"]}
 
 
 def bench_fp64(m, mom, out, args, stream):
