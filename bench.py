@@ -84,19 +84,20 @@ def counters(process):
 
 
 def roofline(process, nevt, k_s):
-    """HBM bytes and executed float64 operations of a launch of nevt events, scaled
-    from the counted launch, and the rate that makes at k_s seconds per launch (from
-    the counters: the kernels share wavefunctions between spins, so the
-    operation count of one program per helicity says nothing about them); None
-    without counters."""
+    """HBM bytes and float64 operations of a launch of nevt events, scaled from the
+    counted launch, and the rate that makes at k_s seconds per launch; None without
+    counters.  The kernels share wavefunctions between spins, so the operation
+    count of one program per helicity says nothing about them.  The counters give
+    instructions; lanes that sit one out do no operation, so the count is that of
+    64 lanes times the mean share of lanes active in a vector instruction."""
     rec = counters(process)
     if not rec:
-        return {"traffic": None, "executed_flops_per_event": None, "achieved": None, "frac": None}
-    ops = rec["fp64_flops_per_event"]
+        return {"traffic": None, "executed_flops_per_event": None, "active_lanes": None, "achieved": None, "frac": None}
+    ops = rec["fp64_flops_per_event"] * rec["active_lanes"]
     achieved = ops * nevt / k_s / 1e12
     counted = rec["fetch_kib"] * rec["fetch_factor"] * 1024 + rec["write_kib"] * rec["write_factor"] * 1024
-    return {"traffic": counted / rec["events"] * nevt, "executed_flops_per_event": ops, "achieved": achieved,
-            "frac": achieved / PEAK["fp64"]}
+    return {"traffic": counted / rec["events"] * nevt, "executed_flops_per_event": ops,
+            "active_lanes": rec["active_lanes"], "achieved": achieved, "frac": achieved / PEAK["fp64"]}
 
 
 def bench_fp64(m, mom, out, args, stream):
@@ -140,7 +141,7 @@ def bench_process(me, proc, nevt, seed, steps, stream, check=8, tol=None):
     return {"workload": f"{proc}, {nevt} RAMBO points seed {seed}", "MEs_per_s": nevt / wall,
             "kernel": kernel_of(proc)[0], "traffic": roof["traffic"], "kernel_ms": k_s * 1e3,
             "flops_per_event_one_helicity_at_a_time": info["flops_per_event"],
-            "executed_flops_per_event": roof["executed_flops_per_event"],
+            "executed_flops_per_event": roof["executed_flops_per_event"], "active_lanes": roof["active_lanes"],
             "achieved_tflops": roof["achieved"], "frac_of_fp64_peak": roof["frac"],
             "max_rel_dev_vs_oracle": float(rel.max()), "checked_events": check, "mixed": mixed}
 
@@ -709,6 +710,7 @@ def main():
         "roofline": {"bound": "alu", "achieved": roof["achieved"], "peak": PEAK["fp64"], "unit": "TFLOP/s",
                      "frac": roof["frac"], "traffic": roof["traffic"], "kernel": kernel_of(args.process)[0],
                      "executed_flops_per_event": roof["executed_flops_per_event"],
+                     "active_lanes": roof["active_lanes"],
                      "flops_per_event_one_helicity_at_a_time": info["flops_per_event"], "kernel_ms": k_s * 1e3},
         "forms": {"fp64": {"MEs_per_s": value, "ms_per_step": wall * 1e3}},
     }
