@@ -28,8 +28,8 @@ static inline int me_turn_lanes_lg(int64_t nevt, int nhel, int64_t turn) {
     return lg;
 }
 
-// Mixed form, one event per lane: helicities per block where their values are added by a kernel of their own
-// (nh: not done).  One wave takes 45 us per helicity of g g -> t tbar g g and the
+// Mixed form, one event per lane: helicities per block where their values are added by a
+// kernel of their own (nh: not done).  One wave takes 45 us per helicity of g g -> t tbar g g and the
 // chip holds 1024 of these waves, so a call of up to 65,536 events took the 2.9 ms
 // of 64 helicities in turn (64 events now 72 us, 16,384 0.81 ms, with the
 // rerun), and one of a few more than a multiple of it a whole turn more (70,000
