@@ -163,11 +163,12 @@ _LAUNCH_GROUP = """    const dim3 grid((unsigned)(nevt < ME_GROUP_BLOCKS ? nevt 
         hipLaunchKernelGGL(({kernel}<proc_{name}, false>), grid, dim3(w5::THREADS), 0, s, mom, nevt, out, spins, prm,
                            idx, count);
 """
-# the same with four lanes per event, while the call is within one wave per SIMD that way
-_LAUNCH_FEW = """    if (nevt <= 16384) {{
-        me_each_launch(nevt, 16, 64, [&](int64_t first, unsigned blocks) {{
-            hipLaunchKernelGGL(({kernel}<proc_{name}, void, 4>), dim3(blocks), dim3(64), 0, s, mom, nevt, out, spins,
-                               prm, idx, count, first, nullptr, nullptr);
+# the same with four times the lanes per event, one for each spin pair, while the call is
+# within one wave per SIMD that way
+_LAUNCH_FEW = """    if (nevt <= 1024 * {per} / 4) {{
+        me_each_launch(nevt, {per} / 4, 64, [&](int64_t first, unsigned blocks) {{
+            hipLaunchKernelGGL(({kernel}<proc_{name}, void, 4 * 64 / {per}>), dim3(blocks), dim3(64), 0, s, mom, nevt,
+                               out, spins, prm, idx, count, first, nullptr, nullptr);
         }});
         return hipGetLastError();
     }}
@@ -183,7 +184,7 @@ _LAUNCH_LANES = """    (void)mfma;
 
 def _wave_tu(name):
     if name in EVENTS_PER_WAVE:
-        launch = (_LAUNCH_FEW if name == "gg_tt" else "") + _LAUNCH_LANES
+        launch = _LAUNCH_FEW + _LAUNCH_LANES
         return _TU_WAVE.format(name=name, header="me_gg_pol.h",
                                launch=launch.format(name=name, kernel=WAVE[name], per=EVENTS_PER_WAVE[name]))
     group = name in COOP

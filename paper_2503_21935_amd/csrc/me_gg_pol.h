@@ -5,7 +5,7 @@
 // Two gluons: one event per lane (small calls: four lanes), everything in registers.  The configurations
 // share four one-gluon rows per ordering and spin.
 //   J_ab = L(a) W(b) v + ubar W(ab) v.
-// Three gluons: eight lanes per event, lane l the gluon polarisations l; the
+// Three gluons: eight lanes per event (small calls: 32), lane l the gluon polarisations l; the
 // externals, one-gluon rows, pair currents and the current of the line's ends
 // are computed once per event and shared in LDS, the rest by each lane for its
 // polarisations and the four spin pairs.
@@ -200,7 +200,11 @@ MEV void st8(double* p, const row& f) {
 
 }  // namespace g3
 
-template <class P, class IDS = void>
+// LANES: lanes per event, eight for its polarisations, which take the spin pairs in
+// turn, or 32 with a spin pair each, for calls that leave most of the chip idle (511 events
+// 6.8 us instead of 10.0; one helicity per lane 9.8).  The pairs are added in the same
+// order either way.
+template <class P, class IDS = void, int LANES = 8>
 __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__ mom, int64_t nevt,
                                                       double* __restrict__ out, unsigned spins, me_params prm,
                                                       const int* __restrict__ idx, const int* __restrict__ count,
@@ -209,17 +213,19 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
                                                       double* __restrict__ alpha = nullptr) {
     using namespace g3;
     static_assert(P::ngluon == 3 && P::ncol == 6, "three gluons");
-    __shared__ double2 mem[8 * (STRIDE / 2)];
-    const int lane = threadIdx.x, l = lane & 7, e = lane >> 3;
+    constexpr bool MC = !std::is_void_v<IDS>;
+    static_assert(LANES == 8 || (LANES == 32 && !MC), "the weights are summed by eight lanes");
+    constexpr int EV = 64 / LANES;  // events per wave
+    __shared__ double2 mem[EV * (STRIDE / 2)];
+    const int lane = threadIdx.x, ln = lane & (LANES - 1), l = lane & 7, e = lane / LANES;
     const double m = prm.mt;
     const int64_t n = count ? (int64_t)*count : nevt;
-    const int64_t first = first0 + (int64_t)blockIdx.x * 8;
+    const int64_t first = first0 + (int64_t)blockIdx.x * EV;
     if (first >= n) return;
     int64_t i = first + e;
     const bool valid = i < n;
     if (!valid) i = n - 1;
     const int64_t ev = count ? (int64_t)idx[i] : i;
-    constexpr bool MC = !std::is_void_v<IDS>;
     const int ch = MC ? chan[ev] : 0;
     double num = 0.0, den = 0.0;
     auto found = [&](auto id, c2 a) __attribute__((always_inline)) {
@@ -229,13 +235,13 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
         asm volatile("" : "+v"(den), "+v"(num));
     };
     double* const D = reinterpret_cast<double*>(mem) + e * STRIDE;
-    if (l < 5) {  // slots: gluons 0, 1, 2 (particle 4), p3, p4
-        const double* p = mom + ev * 20 + 4 * (l < 2 ? l : l == 2 ? 4 : l - 1);
-        const double sg = l == 2 ? -1.0 : 1.0;
-        st4(D + Q + 4 * l, vec{{sg * p[0], sg * p[1], sg * p[2], sg * p[3]}});
+    if (ln < 5) {  // slots: gluons 0, 1, 2 (particle 4), p3, p4
+        const double* p = mom + ev * 20 + 4 * (ln < 2 ? ln : ln == 2 ? 4 : ln - 1);
+        const double sg = ln == 2 ? -1.0 : 1.0;
+        st4(D + Q + 4 * ln, vec{{sg * p[0], sg * p[1], sg * p[2], sg * p[3]}});
     }
     __syncthreads();
-    for (int k = l; k < 11; k += 8) {  // summed momenta and propagators
+    for (int k = ln; k < 11; k += LANES) {  // summed momenta and propagators
         const vec q0 = ld4(D + Q), q1 = ld4(D + Q + 4), q2 = ld4(D + Q + 8);
         const vec end = ld4(D + Q + (k < 3 || k == 10 ? 12 : 16));
         const int a = k < 3 ? k : k - 3;
@@ -257,23 +263,25 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
             D[IQ + k - 6] = f.r;
         }
     }
-    if (l < 6) {  // polarisation vectors (gluon, which)
-        const vec q = ld4(D + Q + 4 * (l >> 1));
-        st4(D + EPS + 4 * l, mul(prm.gs, polarisation(l < 4 ? q : mul(-1.0, q), l & 1)));
+    if (ln < 6) {  // polarisation vectors (gluon, which)
+        const vec q = ld4(D + Q + 4 * (ln >> 1));
+        st4(D + EPS + 4 * ln, mul(prm.gs, polarisation(ln < 4 ? q : mul(-1.0, q), ln & 1)));
     }
-    if (l < 4)  // end rows (end, spin)
-        st8(D + N0 + 8 * l, end_row(ld4(D + Q + 12 + 4 * (l >> 1)), m, l >> 1, (l & 1) ? 1 : -1));
+    if (ln < 4)  // end rows (end, spin)
+        st8(D + N0 + 8 * ln, end_row(ld4(D + Q + 12 + 4 * (ln >> 1)), m, ln >> 1, (ln & 1) ? 1 : -1));
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {  // one-gluon rows (end, gluon, pol, spin); L(a) up to the sign
-        const int k = 8 * r + l, en = k >= 12, a = (k >> 2) - 3 * en, pol = (k >> 1) & 1, s = k & 1;
+    for (int r = 0; r < (LANES == 8 ? 3 : 1); ++r) {  // one-gluon rows (end, gluon, pol, spin); L(a) up to the sign
+        if (LANES > 24 && ln >= 24) break;
+        const int k = 8 * r + ln, en = k >= 12, a = (k >> 2) - 3 * en, pol = (k >> 1) & 1, s = k & 1;
         const row f = slash_m(slash(ld8(D + N0 + 16 * en + 8 * s), ld4(D + EPS + 8 * a + 4 * pol)),
                               ld4(D + K + 4 * (3 * en + a)), m);
         st8(D + N1 + 8 * k, scale(c2{D[F + 2 * (3 * en + a)], D[F + 2 * (3 * en + a) + 1]}, f));
     }
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {  // pair currents (pair, pols), current of the ends (spins)
-        const int k = 8 * r + l;
+    for (int r = 0; r < (LANES == 8 ? 2 : 1); ++r) {  // pair currents (pair, pols), current of the ends (spins)
+        const int k = 8 * r + ln;
+        if (LANES > 16 && k >= 16) break;
         if (k < 12) {
             const int p = k >> 2, a = p == 2, b = p == 0 ? 1 : 2;
             vec w{{0.0, 0.0, 0.0, 0.0}};
@@ -321,8 +329,9 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
         return MC ? ld4(D + W2 + 16 * K + 4 * (bit(at, a) + 2 * bit(at, b))) : W[K];
     };
     double acc = 0.0;
+    const int pair_first = LANES == 8 ? 0 : ln >> 3;  // spin pair s3 + 2 s4: all in turn, or this lane's
 #pragma unroll 1
-    for (int s4 = 0; s4 < 2; ++s4) {
+    for (int s4 = pair_first >> 1; s4 < (LANES == 8 ? 2 : (pair_first >> 1) + 1); ++s4) {
         int l4 = l;
         asm volatile("" : "+v"(l4));
         // rows from p4: R(c), and W(b) R(c) + W(bc) v as r(c) slash(b) + r0 slash W(bc)
@@ -345,7 +354,7 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
             });
         });
 #pragma unroll 1
-        for (int s3 = 0; s3 < 2; ++s3) {
+        for (int s3 = pair_first & 1; s3 < (LANES == 8 ? 2 : (pair_first & 1) + 1); ++s3) {
             int l3 = l;
             if constexpr (MC) asm volatile("" : "+v"(l3));
             const row f0 = ld8(D + N0 + 8 * s3), V = ld8(D + C0 + 8 * (s3 + 2 * s4));
@@ -390,8 +399,13 @@ __global__ __launch_bounds__(64, 2) void k_me_gg3_pol(const double* __restrict__
             acc += ((spins >> (s3 + 2 * s4)) & 1) ? q : 0.0;
         }
     }
+    if constexpr (LANES == 32) {
+        const double part = acc;
+        acc = 0.0;
+        each<4>([&](auto S) __attribute__((always_inline)) { acc += __shfl(part, l + 8 * S, 32); });
+    }
     const double tot = group_sum(acc, 3);
-    if (valid && l == 0) out[ev] = tot * (1.0 / (256.0 * P::identical * P::lcd));
+    if (valid && ln == 0) out[ev] = tot * (1.0 / (256.0 * P::identical * P::lcd));
     if constexpr (MC) {
         num = group_sum(num, 3);
         den = group_sum(den, 3);

@@ -189,23 +189,25 @@ def test_lanes_setting_changes_nothing(env, proc, n):
     m.close()
 
 
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 1000, 16383, 16384, 16385])
-def test_two_gluons_at_four_lanes_and_at_one(env, n):
-    """g g -> t tbar: calls of up to 16,384 events spread the spin pairs over four
-    lanes; the same bits as one lane gives, also through a list."""
+@pytest.mark.parametrize("proc,n", [("gg_tt", n) for n in (1, 15, 16, 17, 1000, 16383, 16384, 16385)]
+                         + [("gg_ttg", n) for n in (1, 2, 3, 1000, 2047, 2048, 2049)])
+def test_spin_pairs_on_lanes_and_in_turn(env, proc, n):
+    """g g -> t tbar and g g -> t tbar g: calls of up to 16,384 and 2,048 events give each
+    spin pair lanes of its own; the same bits as all pairs in turn, also through a list."""
     torch, me = env
-    pts = process_points("gg_tt", 97, 69)
+    nf = {"gg_tt": 2, "gg_ttg": 3}[proc]
+    pts = process_points(proc, 97, 69)
     mom = torch.from_numpy(np.tile(pts, (207, 1, 1))[:20000].copy()).cuda()
-    m = me.MatrixElement("gg_tt")
+    m = me.MatrixElement(proc)
     want = m.eval(mom)
-    close(want[:97].cpu().numpy(), oracle.me2("gg_tt", pts))
+    close(want[:97].cpu().numpy(), oracle.me2(proc, pts))
     out = torch.full((n + 64,), -7.0, dtype=torch.float64, device="cuda")
     me.me_eval(m.ctx, mom, n, out)
     assert torch.equal(out[:n], want[:n]) and bool((out[n:] == -7.0).all())
     m.set_precision(me.ME_MIXED, 1e-14)
     assert torch.equal(m.eval(mom[:n]), want[:n]) and m.fallback_count() == n
     m.close()
-    m = me.MatrixElement("gg_tt", masses=(91.188, 2.4414, 0.0, 0.0))
-    mom = torch.from_numpy(np.tile(rambo(97, 13000.0, [0.0, 0.0], 63), (207, 1, 1))[:20000].copy()).cuda()
+    m = me.MatrixElement(proc, masses=(91.188, 2.4414, 0.0, 0.0))
+    mom = torch.from_numpy(np.tile(rambo(97, 13000.0, [0.0] * nf, 63), (207, 1, 1))[:20000].copy()).cuda()
     assert torch.equal(m.eval(mom[:n]), m.eval(mom)[:n])
     m.close()
